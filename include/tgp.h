@@ -162,7 +162,10 @@ const char *tgp_last_error(tgp_ctx ctx);
 /* Largest number of bytes the subtree-result cache of one evaluation may
  * occupy (default: 1/4 of the device memory).  Cached subtrees that would
  * exceed it are recomputed instead, except those needed to bound the
- * evaluator's stack, whose excess makes the evaluation fail with TGP_ENOMEM. */
+ * evaluator's stack, whose excess makes the evaluation fail with TGP_ENOMEM.
+ * The tables of subtrees that vary along a part of the axes only (one value
+ * per grid row or column) count towards it; without room for them those
+ * subtrees are evaluated at every case, like the others. */
 tgp_status tgp_ctx_set_cache_budget(tgp_ctx ctx, size_t bytes);
 
 /* Tuning of the evaluator (the autotuner sets these): cases_per_lane is K,
@@ -307,7 +310,7 @@ tgp_status tgp_fitness_noalloc(tgp_ctx ctx, tgp_dag dag, tgp_domain dom, const f
 typedef struct {
     int64_t credited_node_evals; /* DAG nodes x cases (each distinct subtree once) */
     int64_t executed_node_evals; /* interpreter instructions run x cases */
-    int64_t cached_nodes;        /* subtrees materialised in the cache */
+    int64_t cached_nodes;        /* subtrees materialised in cache rows and tables */
     int64_t stack_spills;        /* of which cached only to bound the register stack */
     int64_t cache_levels;        /* dependent cache-fill launches */
     int64_t programs;            /* root programs (distinct (root, channel) pairs) */

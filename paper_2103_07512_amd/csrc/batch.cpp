@@ -7,9 +7,10 @@
 // domain shapes, are evaluated together here.  Every job keeps its own plan
 // (DAG, cached subtrees, programs); the batch packs the plans into one set of
 // device buffers and runs
-//   * one persistent launch per cache-fill level (level l of every job),
-//   * one persistent launch for every job's root programs fused with the
-//     error reduction,
+//   * three launches per cache-fill level (level l of every job), one per
+//     form: the flat programs (the tables' among them), the wide, the ragged,
+//   * likewise three for every job's root programs fused with the error
+//     reduction,
 //   * one finalize launch for every individual of every job.
 // Resident waves draw work items from partitioned atomic counters, longest
 // program first across all jobs, so small and large jobs share the GPU
@@ -80,15 +81,19 @@ struct Dev {
 
 }  // namespace
 
+// Cache-fill levels a step can have (a plan with tables has one more than the flat
+// plan of the same DAG: its tables).
+constexpr int kMaxLevels = 64;
+
 struct tgp_batch_s {
     tgp_ctx ctx = nullptr;
     bool use_graph = true;
     bool persistent = true;  // persistent kernels, or one wave per work item
     bool ext = false;        // interpreter with the bitwise operators and warp
     int D = 0;               // stack slots: the register form's or the LDS form's
-    int K = 4;
+    int K = 4;               // cases per lane of the flat launches (others: kTableK)
     int levels_cap = 4;  // fill levels the graph has launches for
-    int grid_store = 0, grid_reduce = 0;
+    int grid[3][2] = {};     // resident waves: [form][store]
     std::vector<uint32_t> group_items;  // items per group of the current step
     uint32_t n_ind = 0;
     // device buffers
@@ -101,7 +106,7 @@ struct tgp_batch_s {
     Dev<int32_t> scalars;  // [0] = n_jobs, [1] = n_ind (as uint32)
     Dev<uint2> code;
     Dev<int32_t> rows;
-    Dev<float> cache;
+    Dev<float> cache, tables;
     Dev<float2> partial;
     // pinned staging
     Pinned<JobDesc> h_jobs;
@@ -112,7 +117,7 @@ struct tgp_batch_s {
     Pinned<int32_t> h_scalars;
     Pinned<uint2> h_code;
     Pinned<int32_t> h_rows;
-    // graph: reset, levels_cap fill launches, the root launch, the finalize
+    // graph: reset, 3 levels_cap fill launches, three root launches, the finalize
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     std::vector<hipGraphNode_t> nodes;
@@ -122,7 +127,7 @@ struct tgp_batch_s {
     tgp_batch_stats stats{};
     // kernel argument storage (launch i reads args[i])
     int32_t n_counters = 0;
-    int32_t group_index[64] = {};
+    int32_t group_index[3 * kMaxLevels + 3] = {};
     uint32_t *n_ind_ptr = nullptr;
 };
 
@@ -135,13 +140,15 @@ static void batch_release_graph(tgp_batch b) {
     b->stale = true;
 }
 
-// Kernel launch i of a step: 0 = counter reset, 1..levels_cap = fill level
-// i - 1, levels_cap + 1 = root programs, levels_cap + 2 = finalize.
-static int n_launches(tgp_batch b) { return b->levels_cap + 3; }
+// Launch groups of a step: 3 l + f = programs of form f (0 flat, 1 wide, 2
+// ragged) of fill level l, l = levels_cap = root programs.
+static int n_groups(tgp_batch b) { return 3 * b->levels_cap + 3; }
+// Kernel launch i of a step: 0 = counter reset, i = group i - 1, then the
+// finalize.
+static int n_launches(tgp_batch b) { return n_groups(b) + 2; }
 
 static hipKernelNodeParams launch_params(tgp_batch b, int i, void **args) {
     hipKernelNodeParams p{};
-    const int L = b->levels_cap;
     p.blockDim = dim3(64);
     if (i == 0) {
         p.func = const_cast<void *>(reset_kernel());
@@ -149,17 +156,16 @@ static hipKernelNodeParams launch_params(tgp_batch b, int i, void **args) {
         p.blockDim = dim3(256);
         args[0] = &b->counters.d;
         args[1] = &b->n_counters;
-    } else if (i <= L + 1) {
-        const bool store = i <= L;
+    } else if (i <= n_groups(b)) {
         const int g = i - 1;
+        const bool store = g < 3 * b->levels_cap;
+        const int f = g % 3;
         b->group_index[g] = g;
-        p.func = const_cast<void *>(batch_kernel(b->K, b->D, store, b->persistent, b->ext));
-        if (b->persistent) {
-            p.gridDim = dim3(store ? b->grid_store : b->grid_reduce);
-        } else {
-            const uint32_t n = g < (int)b->group_items.size() ? b->group_items[g] : 0;
-            p.gridDim = dim3(std::max<uint32_t>(1, n));
-        }
+        p.func = const_cast<void *>(f ? batch_kernel(kTableK, interp_max_stack(), store, b->persistent, f == 1 ? kWide : kRagged)
+                                      : batch_kernel(b->K, b->D, store, b->persistent, b->ext ? kExt : kFlat));
+        uint32_t n = g < (int)b->group_items.size() ? b->group_items[g] : 0;
+        if (b->persistent) n = std::min<uint32_t>(n, (uint32_t)b->grid[f][store]);
+        p.gridDim = dim3(std::max<uint32_t>(1, n));
         args[0] = &b->jobs.d;
         args[1] = &b->pairs.d;
         args[2] = &b->item_first.d;
@@ -214,12 +220,11 @@ static hipError_t build_graph(tgp_batch b) {
     return e;
 }
 
-// Grids that change with the step's sizes (direct form, finalize).
+// Grids follow the step's sizes.
 static hipError_t update_graph(tgp_batch b) {
     void *args[8];
     hipError_t e = hipSuccess;
     for (int i = 1; i < n_launches(b) && e == hipSuccess; ++i) {
-        if (b->persistent && i != n_launches(b) - 1) continue;
         hipKernelNodeParams p = launch_params(b, i, args);
         e = hipGraphExecKernelNodeSetParams(b->exec, b->nodes[i], &p);
     }
@@ -255,6 +260,7 @@ void tgp_batch_destroy(tgp_batch b) {
     b->code.release();
     b->rows.release();
     b->cache.release();
+    b->tables.release();
     b->partial.release();
     b->h_jobs.release();
     b->h_pairs.release();
@@ -281,7 +287,7 @@ tgp_status tgp_batch_run(tgp_batch b, int32_t n_jobs, const tgp_job *jobs) {
     const double t0 = now_ms();
     std::vector<StepJob> sj(n_jobs);
     std::vector<tgp_dag> dags(n_jobs);
-    std::vector<int64_t> cases(n_jobs);
+    std::vector<tgp_domain> doms(n_jobs);
     int64_t credited = 0;
     for (int32_t j = 0; j < n_jobs; ++j) {
         const tgp_job &J = jobs[j];
@@ -291,10 +297,10 @@ tgp_status tgp_batch_run(tgp_batch b, int32_t n_jobs, const tgp_job *jobs) {
         if (J.dag->n_ind > 0 && (!J.target_dev || !J.out_dev))
             return fail(ctx, TGP_EINVAL, "job %d: NULL target or output", j);
         dags[j] = J.dag;
-        cases[j] = J.domain->cases;
+        doms[j] = J.domain;
     }
     // every job's plan at once: host threads, one device round trip
-    tgp_status pst = build_plans(ctx, n_jobs, dags.data(), cases.data());
+    tgp_status pst = build_plans(ctx, n_jobs, dags.data(), doms.data());
     if (pst != TGP_OK) return pst;
     for (int32_t j = 0; j < n_jobs; ++j) {
         const tgp_job &J = jobs[j];
@@ -335,7 +341,7 @@ tgp_status batch_step(tgp_batch b, int32_t n_jobs, const StepJob *jobs, int64_t 
     }
     int K = ctx->force_K ? ctx->force_K : 4;
     if (ctx->stack_lds) K = 2;
-    if (!interp_variant_exists(K, D, ext)) K = 4;
+    if (!interp_variant_exists(K, D, ext ? kExt : kFlat)) K = 4;
     if (K != b->K || ext != b->ext || D != b->D) {
         b->K = K;
         b->ext = ext;
@@ -349,17 +355,18 @@ tgp_status batch_step(tgp_batch b, int32_t n_jobs, const StepJob *jobs, int64_t 
     }
     int max_levels = 0;
     for (int32_t j = 0; j < n_jobs; ++j)
-        max_levels = std::max(max_levels, (int)jobs[j].plan->level_first.size() - 1);
+        max_levels = std::max(max_levels, jobs[j].plan->levels());
+    if (max_levels > kMaxLevels) return fail(ctx, TGP_EINVAL, "more than %d cache-fill levels", kMaxLevels);
     if (max_levels > b->levels_cap) {
-        b->levels_cap = std::max(max_levels, 2 * b->levels_cap);
-        if (b->levels_cap > 63) return fail(ctx, TGP_EINVAL, "more than 63 cache-fill levels");
+        b->levels_cap = std::min(kMaxLevels, std::max(max_levels, 2 * b->levels_cap));
         b->stale = true;
     }
     // ---- launch shape: tiles per item from the whole batch's work
     int64_t total_tiles = 0;
     std::vector<int64_t> ntiles(n_jobs), tps(n_jobs);
     for (int32_t j = 0; j < n_jobs; ++j) {
-        ntiles[j] = (jobs[j].n_cases + 64 * K - 1) / (64 * K);
+        const int jk = jobs[j].plan->split ? kTableK : K;
+        ntiles[j] = (jobs[j].n_cases + 64 * jk - 1) / (64 * jk);
         total_tiles += ntiles[j] * std::max<int64_t>(jobs[j].plan->n_reduce, 0);
     }
     const int cap = ctx->tile_cap > 0 ? ctx->tile_cap : 16;
@@ -367,8 +374,13 @@ tgp_status batch_step(tgp_batch b, int32_t n_jobs, const StepJob *jobs, int64_t 
                           ? ctx->force_tiles
                           : std::max<int64_t>(1, std::min<int64_t>(cap, total_tiles / (1 << 19)));
     // ---- sizes
-    size_t n_code = 0, n_rows = 0, n_cache = 0, n_partial = 0, n_pairs = 0;
+    size_t n_code = 0, n_rows = 0, n_cache = 0, n_tables = 0, n_partial = 0, n_pairs = 0;
     uint32_t n_ind = 0;
+    // a job's tables are filled by two flat jobs of their own
+    int32_t n_desc = n_jobs;
+    auto table_floats = [](const StepJob &J) {
+        return (J.plan->tables_bytes(*J.domain) + 255) / 256 * 64;
+    };
     for (int32_t j = 0; j < n_jobs; ++j) {
         const Plan &P = *jobs[j].plan;
         const int64_t want = jobs[j].tiles_per_item > 0 ? jobs[j].tiles_per_item : tps_all;
@@ -378,13 +390,18 @@ tgp_status batch_step(tgp_batch b, int32_t n_jobs, const StepJob *jobs, int64_t 
         if (!jobs[j].rows_dev) n_rows += P.ind_rows_host.size();
         if (!jobs[j].cache) n_cache += (size_t)P.n_slots * (size_t)jobs[j].domain->cases;
         n_partial += (size_t)P.n_reduce * (size_t)stripes;
+        if (!jobs[j].tables) n_tables += table_floats(jobs[j]);
+        if (P.split && jobs[j].fill_tables) {
+            n_desc += 2;
+            n_pairs += P.tab_host.size();
+        }
         n_pairs += P.fill_host.size() + P.reduce_host.size();
         n_ind += (uint32_t)jobs[j].n_ind;
     }
-    const int G = b->levels_cap + 1;
+    const int G = n_groups(b);
     hipError_t e = hipSuccess;
     bool moved = false;
-    moved |= b->jobs.ensure(std::max<int32_t>(n_jobs, 1), &e);
+    moved |= b->jobs.ensure(std::max<int32_t>(n_desc, 1), &e);
     if (e == hipSuccess) moved |= b->pairs.ensure(std::max<size_t>(n_pairs, 1), &e);
     if (e == hipSuccess) moved |= b->item_first.ensure(n_pairs + 1, &e);
     if (e == hipSuccess) moved |= b->groups.ensure(G, &e);
@@ -394,6 +411,7 @@ tgp_status batch_step(tgp_batch b, int32_t n_jobs, const StepJob *jobs, int64_t 
     if (e == hipSuccess) moved |= b->code.ensure(n_code + 1, &e);
     if (e == hipSuccess) moved |= b->rows.ensure(std::max<size_t>(n_rows, 1), &e);
     if (e == hipSuccess) moved |= b->cache.ensure(std::max<size_t>(n_cache, 1), &e);
+    if (e == hipSuccess) moved |= b->tables.ensure(std::max<size_t>(n_tables, 1), &e);
     if (e == hipSuccess) moved |= b->partial.ensure(std::max<size_t>(n_partial, 1), &e);
     if (e != hipSuccess) return fail(ctx, TGP_ENOMEM, "batch buffers: %s", hipGetErrorString(e));
     if (moved) b->stale = true;
@@ -401,7 +419,7 @@ tgp_status batch_step(tgp_batch b, int32_t n_jobs, const StepJob *jobs, int64_t 
         b->n_counters = G * (int32_t)batch_parts();
         b->stale = true;
     }
-    e = b->h_jobs.ensure(std::max<int32_t>(n_jobs, 1));
+    e = b->h_jobs.ensure(std::max<int32_t>(n_desc, 1));
     if (e == hipSuccess) e = b->h_pairs.ensure(std::max<size_t>(n_pairs, 1));
     if (e == hipSuccess) e = b->h_first.ensure(n_pairs + 1);
     if (e == hipSuccess) e = b->h_groups.ensure(G);
@@ -418,8 +436,9 @@ tgp_status batch_step(tgp_batch b, int32_t n_jobs, const StepJob *jobs, int64_t 
         uint32_t items;
     };
     std::vector<std::vector<PairSort>> groups(G);
-    size_t code_at = 0, rows_at = 0, cache_at = 0, part_at = 0;
+    size_t code_at = 0, rows_at = 0, cache_at = 0, tables_at = 0, part_at = 0;
     uint32_t ind_at = 0;
+    int32_t desc_at = n_jobs;
     for (int32_t j = 0; j < n_jobs; ++j) {
         const StepJob &J = jobs[j];
         const Plan &P = *J.plan;
@@ -438,6 +457,30 @@ tgp_status batch_step(tgp_batch b, int32_t n_jobs, const StepJob *jobs, int64_t 
         jd.target = J.target;
         jd.target_stride = dom_cases;
         jd.partial = b->partial.d + part_at;
+        float *tables = J.tables ? J.tables : b->tables.d + tables_at;
+        fill_table_fields(jd, P, J.domain, tables);
+        // (slabs start at multiples of a tile; a wide job needs them inside one row)
+        const int kind = form_of(P, *J.domain);
+        const int form = kind == kWide ? 1 : (kind == kRagged ? 2 : 0);
+        if (P.split && J.fill_tables) {
+            for (int which = 0; which < 2; ++which) {
+                JobDesc &td = b->h_jobs.h[desc_at + which];
+                fill_table_job(td, P, J.domain, jd.code, tables, which);
+                const int64_t nt = (td.n_cases + 64 * K - 1) / (64 * K);
+                const int64_t per = std::max<int64_t>(1, std::min<int64_t>(16, nt * P.n_tab[which] >> 19));
+                td.tiles_per_stripe = (int32_t)per;
+                td.n_stripes = (int32_t)((nt + per - 1) / per);
+            }
+            for (size_t l = 0; l < P.tab_level.size(); ++l)
+                for (int32_t q = P.tab_level[l].first; q < P.tab_level[l].last; ++q) {
+                    const ProgDesc &pd = P.tab_host[q];
+                    const int32_t d = desc_at + (q < P.tab_level[l].mid ? 0 : 1);
+                    groups[3 * l].push_back({(double)pd.len * b->h_jobs.h[d].tiles_per_stripe,
+                                             {d, pd.code_off, pd.dest, pd.chan},
+                                             (uint32_t)b->h_jobs.h[d].n_stripes});
+                }
+            desc_at += 2;
+        }
         if (!J.code_dev)
             memcpy(b->h_code.h + code_at, P.code_host.data(), sizeof(uint2) * P.code_host.size());
         if (!J.rows_dev)
@@ -457,15 +500,16 @@ tgp_status batch_step(tgp_batch b, int32_t n_jobs, const StepJob *jobs, int64_t 
         for (size_t l = 0; l + 1 < P.level_first.size(); ++l)
             for (int32_t q = P.level_first[l]; q < P.level_first[l + 1]; ++q) {
                 const ProgDesc &pd = P.fill_host[q];
-                groups[l].push_back({(double)pd.len * tps[j], {j, pd.code_off, pd.dest, pd.chan},
+                groups[3 * l + form].push_back({(double)pd.len * tps[j], {j, pd.code_off, pd.dest, pd.chan},
                                      (uint32_t)stripes});
             }
         for (const ProgDesc &pd : P.reduce_host)
-            groups[G - 1].push_back({(double)pd.len * tps[j], {j, pd.code_off, pd.dest, pd.chan},
+            groups[G - 3 + form].push_back({(double)pd.len * tps[j], {j, pd.code_off, pd.dest, pd.chan},
                                      (uint32_t)stripes});
         if (!J.code_dev) code_at += P.code_host.size();
         if (!J.rows_dev) rows_at += P.ind_rows_host.size();
         if (!J.cache) cache_at += (size_t)P.n_slots * (size_t)dom_cases;
+        if (!J.tables) tables_at += table_floats(J);
         part_at += (size_t)P.n_reduce * (size_t)stripes;
         ind_at += (uint32_t)J.n_ind;
     }
@@ -499,7 +543,7 @@ tgp_status batch_step(tgp_batch b, int32_t n_jobs, const StepJob *jobs, int64_t 
     auto up = [&](void *dst, const void *src, size_t bytes) {
         if (e == hipSuccess && bytes) e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, ctx->stream);
     };
-    up(b->jobs.d, b->h_jobs.h, sizeof(JobDesc) * n_jobs);
+    up(b->jobs.d, b->h_jobs.h, sizeof(JobDesc) * n_desc);
     up(b->pairs.d, b->h_pairs.h, sizeof(PairDesc) * n_pairs);
     up(b->item_first.d, b->h_first.h, sizeof(uint32_t) * (n_pairs + 1));
     up(b->groups.d, b->h_groups.h, sizeof(GroupDesc) * G);
@@ -511,11 +555,10 @@ tgp_status batch_step(tgp_batch b, int32_t n_jobs, const StepJob *jobs, int64_t 
     if (e == hipSuccess) e = hipEventRecord(b->staged_ev, ctx->stream);
     if (e != hipSuccess) return fail(ctx, TGP_EHIP, "batch upload: %s", hipGetErrorString(e));
     b->staged = true;
-    const int gs = batch_grid(K, D, true, ext), gr = batch_grid(K, D, false, ext);
-    if (gs != b->grid_store || gr != b->grid_reduce) {
-        b->grid_store = gs;
-        b->grid_reduce = gr;
-        b->stale = true;
+    for (int store = 0; store < 2; ++store) {
+        b->grid[0][store] = batch_grid(K, D, store != 0, ext ? kExt : kFlat);
+        b->grid[1][store] = batch_grid(kTableK, interp_max_stack(), store != 0, kWide);
+        b->grid[2][store] = batch_grid(kTableK, interp_max_stack(), store != 0, kRagged);
     }
     const double t1 = now_ms();
     record(ctx, 2);
@@ -621,7 +664,7 @@ tgp_status tgp_autotune(tgp_ctx ctx, int32_t n_jobs, const tgp_job *jobs, const 
     tgp_tune_result r{};
     int K = 0, cap = 0, pers = 1, lds = 0;
     if (lookup(cache_path, key, &K, &cap, &pers, &lds) &&
-        interp_variant_exists(K, lds ? interp_lds_stack() : interp_max_stack(), lds != 0)) {
+        interp_variant_exists(K, lds ? interp_lds_stack() : interp_max_stack(), lds ? kExt : kFlat)) {
         ctx->force_K = K;
         ctx->tile_cap = cap;
         ctx->force_tiles = 0;
@@ -650,7 +693,7 @@ tgp_status tgp_autotune(tgp_ctx ctx, int32_t n_jobs, const tgp_job *jobs, const 
               oldP = ctx->batch_persistent, oldL = ctx->stack_lds;
     for (const auto &f : forms) {
         const int lf = f[0], kk = f[1];
-        if (!interp_variant_exists(kk, lf ? interp_lds_stack() : interp_max_stack(), lf != 0)) continue;
+        if (!interp_variant_exists(kk, lf ? interp_lds_stack() : interp_max_stack(), lf ? kExt : kFlat)) continue;
         for (int cp = 0; cp < 4; ++cp) {
             const int c = caps[cp % 2], pf = cp / 2 == 0 ? 1 : 0;
             ctx->force_K = kk;

@@ -23,6 +23,16 @@ operand is a terminal -- x, y, a constant or a cached subtree row -- reads
 that operand itself (code FUSE_BASE + 16 * kind + v, v the index in FUSED),
 which saves the terminal's own dispatch and the copy into a stack slot.
 
+The same loop is generated for three forms.  The flat form reads the
+coordinates x and y from registers.  The other two have no coordinate
+registers: the operands kFuseX / I_X and kFuseY / I_Y name rows of two small
+tables of subtree values instead, with one entry per grid row (values that
+depend only on the leading axes) and one per column (on the trailing axes).
+In the wide form a tile lies inside one grid row, so an entry of the row table
+is one scalar load, used as a scalar operand, and the column table is read
+like a cache row; in the ragged form every case reads both tables at its own
+offsets.
+
 Operators with long bodies (transcendentals, floored modulo, the FP64 image
 operators) are compiled once as out-of-line functions that take and return
 the K-vectors by value in registers; the cheap operators are written into
@@ -63,6 +73,9 @@ TERNARY = ("clip", "if", "lerp")
 PERMS = [(0, 1, 2), (0, 2, 1), (1, 0, 2), (1, 2, 0), (2, 0, 1), (2, 1, 0)]
 # Operators compiled once, out of line.
 CALLED = {"sin", "cos", "tan", "exp", "log", "pow", "mod", "sstep", "sstepp", "len", "lerp"}
+# Operators written in asm with vector operands: their forms whose second
+# operand is a scalar register (f_<name>_s).
+SCALAR_OPERAND = {"min", "max"}
 # The bitwise operators share one opcode (that of "or"); the instruction's
 # .y says which (0 or, 1 xor, 2 and).  They, warp (I_WARP) and the third
 # axis (I_Z) are compiled only into the interpreters instantiated with
@@ -80,6 +93,11 @@ FUSED = [("add", False), ("sub", False), ("mult", False), ("div", False), ("pow"
 FUSE_KINDS = [("kFuseX", "xv.v[k]"), ("kFuseY", "yv.v[k]"), ("kFuseConst", "c"), ("kFuseCache", "row_load(row, coff[k])")]
 
 
+def cache_read(form):
+    """How case k of a cache row (`row`) is read: at the case's byte offset."""
+    return "row_load(row, coff[k])" if form == "flat" else "row_load(row, wt.case_off(k))"
+
+
 def fused_checks():
     """static_asserts tying FUSED to the C++ table the emitter uses."""
     L = ["// The fused forms' table as the emitter sees it (tgp_internal.h)."]
@@ -92,11 +110,33 @@ def fused_checks():
     return "\n".join(L)
 
 
-def fused_case(e, key_expr, name, rev, kind, read, dst, ind, end):
+def fused_case(e, key_expr, name, rev, kind, read, dst, ind, end, form="flat"):
     """One fused case: dst = name(dst, T) (or name(T, dst) when reversed),
     T the terminal operand of the given kind; ends with `end`.  With key_expr
     None only the braced body is written (the dispatch tree's leaves)."""
     e(f"{ind}case {key_expr}: {{" if key_expr is not None else f"{ind}{{")
+    if form != "flat" and kind in ("kFuseX", "kFuseY"):
+        # table operands: one scalar for all cases, or a value per case
+        uniform = form == "wide" and kind == "kFuseX"
+        if uniform:
+            e(f"{ind}    const float c = table_row(wt, ins.y);")
+        if not uniform or name in CALLED:
+            fn = "c" if uniform else f"table_{'row' if kind == 'kFuseX' else 'column'}(wt, ins.y, k)"
+            e(f"{ind}    FV<K> tv;")
+            e("#pragma unroll")
+            e(f"{ind}    for (int k = 0; k < K; ++k) tv.v[k] = {fn};")
+        if name in CALLED:
+            args = f"tv, {dst}" if rev else f"{dst}, tv"
+            e(f"{ind}    {dst} = vcall_{name}<K>({args});")
+        else:
+            read = "c" if uniform else "tv.v[k]"
+            fn = f"f_{name}_s" if uniform and name in SCALAR_OPERAND else f"f_{name}"
+            x, y = (read, f"{dst}.v[k]") if rev else (f"{dst}.v[k]", read)
+            e("#pragma unroll")
+            e(f"{ind}    for (int k = 0; k < K; ++k) {dst}.v[k] = {fn}({x}, {y});")
+        e(f"{ind}    {end}")
+        e(f"{ind}}}")
+        return
     if kind == "kFuseConst":
         e(f"{ind}    const float c = __uint_as_float(ins.y);")
     if kind == "kFuseCache":
@@ -163,10 +203,11 @@ def code_checks():
     return "\n".join(L)
 
 
-def dispatch_weights():
-    """Measured frequency of each instruction word (dispatch_weights.txt):
-    key -> count.  Words it does not list weigh 1."""
-    path = os.path.join(HERE, "dispatch_weights.txt")
+def dispatch_weights(form):
+    """Measured frequency of each instruction word (dispatch_weights.txt for
+    the flat form, dispatch_weights_wide.txt for the others): key -> count.
+    Words a file does not list weigh 1."""
+    path = os.path.join(HERE, "dispatch_weights.txt" if form == "flat" else "dispatch_weights_wide.txt")
     w = {}
     for line in open(path):
         line = line.split("#")[0].split()
@@ -201,25 +242,32 @@ def tree(e, keys, bodies, weight, ind):
     e(f"{ind}}}")
 
 
-def body_for_depth(D):
+def body_for_depth(D, form):
     L = []
     e = L.append
-    e(f"// Stack of {D} register slots, one dispatch loop over (depth, opcode).")
-    e("template <int K, bool EXT>")
-    e(f"__device__ __forceinline__ void run_prog_d{D}(const uint2 *__restrict__ ip, const FV<K> &xv0,")
-    e("        const FV<K> &yv0, const FV<K> &zv, const float *__restrict__ cache, int64_t cache_stride,")
-    e("        const uint32_t (&coff)[K], const WarpGeom &wg, FV<K> &res)")
+    wide = form != "flat"
+    e(f"// Stack of {D} register slots, one dispatch loop over (depth, opcode), {form} form.")
+    e("template <int K>" if wide else "template <int K, bool EXT>")
+    if wide:
+        tile = "WideTile" if form == "wide" else "RaggedTile"
+        e(f"__device__ __forceinline__ void run_prog_w{D}(const uint2 *__restrict__ ip, const {tile}<K> &wt,")
+        e("        const float *__restrict__ cache, int64_t cache_stride, FV<K> &res)")
+    else:
+        e(f"__device__ __forceinline__ void run_prog_d{D}(const uint2 *__restrict__ ip, const FV<K> &xv0,")
+        e("        const FV<K> &yv0, const FV<K> &zv, const float *__restrict__ cache, int64_t cache_stride,")
+        e("        const uint32_t (&coff)[K], const WarpGeom &wg, FV<K> &res)")
     e("{")
     e("    " + " ".join(f"FV<K> s{j};" for j in range(D)))
-    e("    FV<K> xv = xv0, yv = yv0;")
-    # One opaque pass before the loop as well: it waits for the coordinate
-    # loads there, so the passes inside the loop find no load pending on
-    # those registers and the loop head carries no wait for them.
-    e("#pragma unroll")
-    e("    for (int k = 0; k < K; ++k) {")
-    e("        asm volatile(\"\" : \"+v\"(xv.v[k]));")
-    e("        asm volatile(\"\" : \"+v\"(yv.v[k]));")
-    e("    }")
+    if not wide:
+        e("    FV<K> xv = xv0, yv = yv0;")
+        # One opaque pass before the loop as well: it waits for the coordinate
+        # loads there, so the passes inside the loop find no load pending on
+        # those registers and the loop head carries no wait for them.
+        e("#pragma unroll")
+        e("    for (int k = 0; k < K; ++k) {")
+        e("        asm volatile(\"\" : \"+v\"(xv.v[k]));")
+        e("        asm volatile(\"\" : \"+v\"(yv.v[k]));")
+        e("    }")
     e("    uint2 ins;")
     e("    // one scalar load of the next whole word, issued a dispatch ahead,")
     e("    // through the constant address space at a 32-bit byte offset (one")
@@ -231,15 +279,16 @@ def body_for_depth(D):
     e("    uint64_t nxt = *(cword *)(cb + off);")
     e("    for (;;) {")
     e("    ins = make_uint2((uint32_t)nxt, (uint32_t)(nxt >> 32));")
-    # The coordinates pass through an empty asm at every dispatch, so the
-    # compiler sees them redefined in the loop and does not hoist the cases'
-    # expressions of them (x / 2 for mdist, x == 0 for div, ...) out of it
-    # into registers that then spill: fewer VGPRs, no per-tile spill stores.
-    e("#pragma unroll")
-    e("    for (int k = 0; k < K; ++k) {")
-    e("        asm volatile(\"\" : \"+v\"(xv.v[k]));")
-    e("        asm volatile(\"\" : \"+v\"(yv.v[k]));")
-    e("    }")
+    if not wide:
+        # The coordinates pass through an empty asm at every dispatch, so the
+        # compiler sees them redefined in the loop and does not hoist the cases'
+        # expressions of them (x / 2 for mdist, x == 0 for div, ...) out of it
+        # into registers that then spill: fewer VGPRs, no per-tile spill stores.
+        e("#pragma unroll")
+        e("    for (int k = 0; k < K; ++k) {")
+        e("        asm volatile(\"\" : \"+v\"(xv.v[k]));")
+        e("        asm volatile(\"\" : \"+v\"(yv.v[k]));")
+        e("    }")
     e("    if (ins.x == ((1u << 8) | I_END)) break;")
     e("    __builtin_amdgcn_sched_barrier(0);")
     e("    off += 8;")
@@ -265,18 +314,30 @@ def body_for_depth(D):
     for S in range(D + 1):
         key = lambda c: (S << 8) | c
         if S < D:
-            for name, reg in (("I_X", "xv"), ("I_Y", "yv")):
-                case(key(CODES[name]), [f"s{S} = {reg};", "continue;"])
-            # the third axis only in the extended interpreter (3-D domains)
-            case(key(CODES["I_Z"]), ["if constexpr (EXT) {", f"    s{S} = zv;", "    continue;", "} else {",
-                                     "    goto BAD;", "}"])
+            if wide:
+                if form == "wide":
+                    case(key(CODES["I_X"]), ["const float c = table_row(wt, ins.y);", "#pragma unroll",
+                                             f"for (int k = 0; k < K; ++k) s{S}.v[k] = c;", "continue;"])
+                else:
+                    case(key(CODES["I_X"]), ["#pragma unroll",
+                                             f"for (int k = 0; k < K; ++k) s{S}.v[k] = table_row(wt, ins.y, k);",
+                                             "continue;"])
+                case(key(CODES["I_Y"]), ["#pragma unroll",
+                                         f"for (int k = 0; k < K; ++k) s{S}.v[k] = table_column(wt, ins.y, k);",
+                                         "continue;"])
+            else:
+                for name, reg in (("I_X", "xv"), ("I_Y", "yv")):
+                    case(key(CODES[name]), [f"s{S} = {reg};", "continue;"])
+                # the third axis only in the extended interpreter (3-D domains)
+                case(key(CODES["I_Z"]), ["if constexpr (EXT) {", f"    s{S} = zv;", "    continue;", "} else {",
+                                         "    goto BAD;", "}"])
             case(key(CODES["I_CONST"]), ["const float c = __uint_as_float(ins.y);", "#pragma unroll",
                                          f"for (int k = 0; k < K; ++k) s{S}.v[k] = c;", "continue;"])
             case(key(CODES["I_CACHE"]), ["const Row row = row_at(cache, cache_stride, ins.y);",
                                          "#pragma unroll",
-                                         f"for (int k = 0; k < K; ++k) s{S}.v[k] = row_load(row, coff[k]);",
+                                         f"for (int k = 0; k < K; ++k) s{S}.v[k] = {cache_read(form)};",
                                          "continue;"])
-        if S >= 2:
+        if S >= 2 and not wide:
             case(key(CODES["I_WARP"]), [
                 "if constexpr (EXT) {",
                 "    const Row row = row_at(cache, cache_stride, ins.y);",
@@ -291,6 +352,8 @@ def body_for_depth(D):
                 continue
             dst = S - ar
             src = [f"s{dst + order.index(i)}" for i in range(ar)]
+            if name == BITWISE[0] and wide:
+                continue  # plans with bitwise operators or warp are flat
             if name == BITWISE[0]:
                 case(key(c), [
                     "if constexpr (EXT) {",
@@ -309,17 +372,20 @@ def body_for_depth(D):
                               "continue;"])
         if S >= 1:
             for kind, read in FUSE_KINDS:
+                if kind == "kFuseCache":
+                    read = cache_read(form)
                 for v, (name, rev) in enumerate(FUSED):
                     lines = []
-                    fused_case(lines.append, None, name, rev, kind, read, f"s{S - 1}", "", "continue;")
+                    fused_case(lines.append, None, name, rev, kind, read, f"s{S - 1}", "", "continue;", form)
                     case(key(FUSE_BASE + 16 * KINDS[kind] + v), lines)
-    tree(e, sorted(bodies), bodies, dispatch_weights(), "    ")
+    tree(e, sorted(bodies), bodies, dispatch_weights(form), "    ")
     e("    }")
     e("    res = s0;")
-    e("    return;")
-    e("BAD:")
-    e("#pragma unroll")
-    e("    for (int k = 0; k < K; ++k) res.v[k] = __builtin_nanf(\"\");")
+    if not wide:
+        e("    return;")
+        e("BAD:")
+        e("#pragma unroll")
+        e("    for (int k = 0; k < K; ++k) res.v[k] = __builtin_nanf(\"\");")
     e("}")
     e("")
     return "\n".join(L)
@@ -442,7 +508,7 @@ def generate():
            code_checks(),
            called_functions()]
     for D in DEPTHS:
-        out.append(body_for_depth(D))
+        out += [body_for_depth(D, form) for form in ("flat", "wide", "ragged")]
     out.append(body_lds())
     return "\n".join(out) + "\n"
 

@@ -12,6 +12,17 @@
 // tables, constants from the instruction stream, and cached subtree values
 // from the HBM cache rows.
 //
+// Where a grid has rows and columns, most subtrees of a tree depend on one of
+// the two alone (54% of the operator cost of the 1000 x 3 depth-2-to-12
+// population): the wide and ragged forms read those from tables of one value
+// per row or column, filled by k_tables, instead of evaluating them at every
+// case.  The values are those of the same operators on the same operands and
+// the cases are summed in the flat form's order, so every result keeps its
+// bits.  That population's fitness launch on 1024 x 1024 cases: 55.5 ms flat,
+// 31.6 ms wide, its cache fill 2.9 ms flat, 0.7 ms with the tables (37k
+// subtrees, 0.08 ms); executed instructions 358 G flat, 190 G.  The launch
+// is bound by vector issue in both forms.
+//
 // Fitness form (Sec. 4.1, RMSE against a target): each lane accumulates
 // (v - t)^2 over its cases with Kahan-compensated FP32, the wave merges its
 // 64 (sum, compensation) pairs exactly-summed (TwoSum) through cross-lane
@@ -22,6 +33,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "ops_device.h"
 #include "tgp_internal.h"
@@ -61,6 +73,49 @@ __device__ __forceinline__ float row_load(const Row &row, uint32_t off) {
 }
 __device__ __forceinline__ void row_store(const Row &row, uint32_t off, float v) {
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), row.r, off, 0, 0);
+}
+// The same with a scalar part of the offset.
+__device__ __forceinline__ float row_load(const Row &row, uint32_t off, uint32_t soff) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(row.r, off, soff, 0));
+}
+
+// Where a tile of the wide form reads: its one grid row's entry of the row
+// table (subtree 0), its first column's offset, its cases.
+template <int K>
+struct WideTile {
+    const __attribute__((address_space(4))) char *row;  // row table, subtree 0, at the tile's grid row
+    Row cols;                                           // the column table
+    uint32_t row_bytes, col_bytes;                      // strides of the tables' subtrees
+    uint32_t coff, voff;  // byte offsets of the lane's first column and case; the next ones are 256 apart
+    __device__ __forceinline__ uint32_t case_off(int k) const { return voff + 256u * (uint32_t)k; }
+};
+// Subtree idx at the tile's grid row: one scalar load.
+template <int K>
+__device__ __forceinline__ float table_row(const WideTile<K> &t, uint32_t idx) {
+    return *(const __attribute__((address_space(4))) float *)(t.row + idx * t.row_bytes);
+}
+// Subtree idx at the column of case k.
+template <int K>
+__device__ __forceinline__ float table_column(const WideTile<K> &t, uint32_t idx, int k) {
+    return row_load(t.cols, t.coff + 256u * (uint32_t)k, idx * t.col_bytes);
+}
+
+// A tile of the ragged form: every case has offsets of its own into the
+// tables and the cache rows.
+template <int K>
+struct RaggedTile {
+    Row rows, cols;
+    uint32_t row_bytes, col_bytes;
+    uint32_t roff[K], coff[K], voff[K];
+    __device__ __forceinline__ uint32_t case_off(int k) const { return voff[k]; }
+};
+template <int K>
+__device__ __forceinline__ float table_row(const RaggedTile<K> &t, uint32_t idx, int k) {
+    return row_load(t.rows, t.roff[k], idx * t.row_bytes);
+}
+template <int K>
+__device__ __forceinline__ float table_column(const RaggedTile<K> &t, uint32_t idx, int k) {
+    return row_load(t.cols, t.coff[k], idx * t.col_bytes);
 }
 
 // The case warp reads for a case c: the points named by t0 and t1 along
@@ -123,10 +178,93 @@ __device__ __forceinline__ float *lds_stack() {
     return rows;
 }
 
+// The error sum of one (program, stripe): the wave's 64 compensated pairs
+// merged, written by lane 0.
+template <typename Job>
+__device__ __forceinline__ void write_partial(const Job &a, float ks, float kc, int32_t dest, uint32_t stripe,
+                                              int lane) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const float s2 = __shfl_xor(ks, off, 64);
+        const float c2 = __shfl_xor(kc, off, 64);
+        kahan_merge(ks, kc, s2, c2);
+    }
+    if (lane == 0) a.partial[(size_t)dest * (size_t)a.n_stripes + stripe] = make_float2(ks, kc);
+}
+
+// One work item of a wide or ragged job: program `code` over
+// tiles_per_stripe tiles of one stripe.
+template <int K, int MODE, int FORM, typename Job>
+__device__ __forceinline__ void run_item_tables(const Job &a, const uint2 *code, int32_t dest, int32_t chan,
+                                                uint32_t stripe, int lane) {
+    constexpr bool WIDE = FORM == kWide;
+    const uint32_t n = (uint32_t)a.n_cases, gb = (uint32_t)a.case_base;
+    const uint32_t first = stripe * (uint32_t)a.tiles_per_stripe * (64u * K);
+    float ks = 0.0f, kc = 0.0f;
+    for (int t = 0; t < a.tiles_per_stripe; ++t) {
+        const uint32_t base = first + (uint32_t)t * (64u * K);
+        if (base >= n) break;
+        std::conditional_t<WIDE, WideTile<K>, RaggedTile<K>> wt;
+        wt.row_bytes = a.row_bytes;
+        wt.col_bytes = a.col_bytes;
+        wt.cols = row_at(a.col_tab, 0, 0);
+        bool valid[K];
+        if constexpr (WIDE) {
+            const uint32_t c = gb + base;
+            const uint32_t row = div_by_magic(c, a.col_m, a.col_s);
+            wt.row = (const __attribute__((address_space(4))) char *)(a.row_tab + row);
+            wt.coff = (c - row * a.n_cols + (uint32_t)lane) * 4u;
+            wt.voff = (c + (uint32_t)lane) * 4u;
+#pragma unroll
+            for (int k = 0; k < K; ++k) valid[k] = true;
+        } else {
+            wt.rows = row_at(a.row_tab, 0, 0);
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const uint32_t i = base + 64u * (uint32_t)k + (uint32_t)lane;
+                valid[k] = i < n;
+                const uint32_t c = gb + (valid[k] ? i : n - 1);
+                const uint32_t row = div_by_magic(c, a.col_m, a.col_s);
+                wt.roff[k] = row * 4u;
+                wt.coff[k] = (c - row * a.n_cols) * 4u;
+                wt.voff[k] = c * 4u;
+            }
+        }
+        // the target values are loaded before the program runs, so that
+        // their latency overlaps its execution
+        FV<K> tv;
+        if constexpr (MODE != MODE_STORE) {
+            const Row trow = row_at(a.target, a.target_stride, (uint32_t)chan);
+#pragma unroll
+            for (int k = 0; k < K; ++k) tv.v[k] = row_load(trow, wt.case_off(k));
+        }
+        FV<K> res;
+        run_prog_w8<K>(code - 1, wt, a.cache, a.cache_stride, res);  // fetches pre-increment
+        if constexpr (MODE == MODE_STORE) {
+            const Row out = row_at(a.out, a.out_stride, (uint32_t)dest);
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                if (valid[k]) row_store(out, wt.case_off(k), res.v[k]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const float e = res.v[k] - tv.v[k];
+                if (valid[k]) kahan_add(ks, kc, e * e);
+            }
+        }
+    }
+    if constexpr (MODE == MODE_REDUCE) write_partial(a, ks, kc, dest, stripe, lane);
+}
+
 // One work item: program `code` over tiles_per_stripe tiles of one stripe.
-template <int K, int D, int MODE, bool EXT, typename Job>
+template <int K, int D, int MODE, int FORM, typename Job>
 __device__ __forceinline__ void run_item(const Job &a, const uint2 *code, int32_t dest, int32_t chan,
                                          uint32_t stripe, int lane) {
+    if constexpr (FORM == kWide || FORM == kRagged) {
+        run_item_tables<K, MODE, FORM>(a, code, dest, chan, stripe, lane);
+        return;
+    }
+    constexpr bool EXT = FORM == kExt;
     const int32_t n = a.n_cases;
     const int64_t tile_cases = 64 * K;
     const int64_t first = (int64_t)stripe * a.tiles_per_stripe * tile_cases;
@@ -197,19 +335,10 @@ __device__ __forceinline__ void run_item(const Job &a, const uint2 *code, int32_
             }
         }
     }
-    if constexpr (MODE == MODE_REDUCE) {
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            const float s2 = __shfl_xor(ks, off, 64);
-            const float c2 = __shfl_xor(kc, off, 64);
-            kahan_merge(ks, kc, s2, c2);
-        }
-        if (lane == 0)
-            a.partial[(size_t)dest * (size_t)a.n_stripes + stripe] = make_float2(ks, kc);
-    }
+    if constexpr (MODE == MODE_REDUCE) write_partial(a, ks, kc, dest, stripe, lane);
 }
 
-// Waves per SIMD the plain interpreter asks for.  The fitness form runs at
+// Waves per SIMD the plain interpreter asks for.  The fitness form (flat) runs at
 // seven (72 VGPRs): its dispatch chain waits on scalar loads and its cache
 // rows on vector loads, and a seventh resident wave hides more of that than
 // the few values that then live in scratch cost (only the z vector of 3-D
@@ -218,16 +347,37 @@ __device__ __forceinline__ void run_item(const Job &a, const uint2 *code, int32_
 // six, where it spills less.  The batched kernels hold more descriptor state
 // and spill far more at these counts (measured slower), so they keep the
 // compiler's choice.
-template <int MODE>
+template <int MODE, int FORM>
 constexpr int min_waves() { return MODE == MODE_REDUCE ? 7 : 6; }
 
-template <int K, int D, int MODE, bool EXT>
-__global__ __launch_bounds__(64, min_waves<MODE>()) void k_interp(const InterpArgs a) {
+template <int K, int D, int MODE, int FORM>
+__global__ __launch_bounds__(64, (min_waves<MODE, FORM>())) void k_interp(const InterpArgs a) {
     const uint32_t item = blockIdx.x;
     const uint32_t p = item / (uint32_t)a.job.n_stripes;
     const uint32_t stripe = item - p * (uint32_t)a.job.n_stripes;
     const ProgDesc pd = a.progs[p];
-    run_item<K, D, MODE, EXT>(a.job, a.job.code + pd.code_off, pd.dest, pd.chan, stripe, threadIdx.x);
+    run_item<K, D, MODE, FORM>(a.job, a.job.code + pd.code_off, pd.dest, pd.chan, stripe, threadIdx.x);
+}
+
+// A job descriptor read in place through the constant address space: each
+// field is a scalar load the compiler may repeat where it is used, so the
+// descriptor does not occupy scalar registers for a whole work item.
+typedef const __attribute__((address_space(4))) JobDesc CJobDesc;
+
+// One level of table fills (TableArgs): the waves of the row table's programs,
+// then those of the column table's, each over its own flat job, read in place
+// from the kernel's arguments.
+template <int K>
+__global__ __launch_bounds__(64, (min_waves<MODE_STORE, kFlat>())) void k_tables(const TableArgs a) {
+    const uint32_t items0 = (uint32_t)a.n_progs[0] * (uint32_t)a.job[0].n_stripes;
+    const uint32_t sel = blockIdx.x >= items0 ? 1u : 0u;
+    const uint32_t item = blockIdx.x - (sel ? items0 : 0u);
+    typedef const __attribute__((address_space(4))) char cchar;
+    const CJobDesc &jd = *(CJobDesc *)((cchar *)__builtin_amdgcn_kernarg_segment_ptr() + sel * sizeof(JobDesc));
+    const uint32_t p = item / (uint32_t)jd.n_stripes;
+    const ProgDesc pd = a.progs[(sel ? (uint32_t)a.n_progs[0] : 0u) + p];
+    run_item<K, 8, MODE_STORE, kFlat>(jd, jd.code + pd.code_off, pd.dest, pd.chan,
+                                      item - p * (uint32_t)jd.n_stripes, threadIdx.x);
 }
 
 // Batched interpreter, two launch forms over the work items of group g
@@ -251,11 +401,6 @@ __device__ __forceinline__ T load_const(const T *p) {
     return r;
 }
 
-// A job descriptor read in place through the constant address space: each
-// field is a scalar load the compiler may repeat where it is used, so the
-// descriptor does not occupy scalar registers for a whole work item.
-typedef const __attribute__((address_space(4))) JobDesc CJobDesc;
-
 __device__ __forceinline__ uint32_t load_const_u32(const uint32_t *p) {
     typedef const __attribute__((address_space(4))) uint32_t cword;
     return *(cword *)(p);
@@ -275,8 +420,8 @@ __device__ __forceinline__ uint32_t find_pair(const uint32_t *__restrict__ item_
     return lo;
 }
 
-template <int K, int D, int MODE, bool EXT>
-__global__ __launch_bounds__(64, min_waves<MODE>()) void k_batch(const JobDesc *__restrict__ jobs,
+template <int K, int D, int MODE, int FORM>
+__global__ __launch_bounds__(64, (min_waves<MODE, FORM>())) void k_batch(const JobDesc *__restrict__ jobs,
                                               const PairDesc *__restrict__ pairs,
                                               const uint32_t *__restrict__ item_first,
                                               const GroupDesc *__restrict__ groups, int32_t g,
@@ -300,7 +445,7 @@ __global__ __launch_bounds__(64, min_waves<MODE>()) void k_batch(const JobDesc *
                 const PairDesc pd = load_const(pairs + lo);
                 const CJobDesc &jd = *(CJobDesc *)(jobs + pd.job);
                 const uint32_t stripe = item - load_const_u32(item_first + lo);
-                run_item<K, D, MODE, EXT>(jd, jd.code + pd.code_off, pd.dest, pd.chan, stripe, threadIdx.x);
+                run_item<K, D, MODE, FORM>(jd, jd.code + pd.code_off, pd.dest, pd.chan, stripe, threadIdx.x);
             }
         }
     }
@@ -308,8 +453,8 @@ __global__ __launch_bounds__(64, min_waves<MODE>()) void k_batch(const JobDesc *
 
 // Direct form: one wave per item (grid = the group's item count, or more);
 // the hardware dispatcher hands out the waves in item order.
-template <int K, int D, int MODE, bool EXT>
-__global__ __launch_bounds__(64, min_waves<MODE>()) void k_batch_direct(const JobDesc *__restrict__ jobs,
+template <int K, int D, int MODE, int FORM>
+__global__ __launch_bounds__(64, (min_waves<MODE, FORM>())) void k_batch_direct(const JobDesc *__restrict__ jobs,
                                                      const PairDesc *__restrict__ pairs,
                                                      const uint32_t *__restrict__ item_first,
                                                      const GroupDesc *__restrict__ groups, int32_t g) {
@@ -319,7 +464,7 @@ __global__ __launch_bounds__(64, min_waves<MODE>()) void k_batch_direct(const Jo
     const uint32_t lo = find_pair(item_first, gd.pair_begin, gd.pair_end, item);
     const PairDesc pd = load_const(pairs + lo);
     const CJobDesc &jd = *(CJobDesc *)(jobs + pd.job);
-    run_item<K, D, MODE, EXT>(jd, jd.code + pd.code_off, pd.dest, pd.chan, item - load_const_u32(item_first + lo),
+    run_item<K, D, MODE, FORM>(jd, jd.code + pd.code_off, pd.dest, pd.chan, item - load_const_u32(item_first + lo),
                          threadIdx.x);
 }
 
@@ -401,46 +546,57 @@ __global__ __launch_bounds__(256) void k_finalize_batch(const FinJob *jobs, cons
 }
 
 // ------------------------------------------------------------- launchers
-template <int K, int D, bool EXT>
+template <int K, int D, int FORM>
 static hipError_t launch_kd(bool store, const InterpArgs &a, hipStream_t s) {
     const uint32_t items = (uint32_t)a.n_progs * (uint32_t)a.job.n_stripes;
     if (items == 0) return hipSuccess;
     if (store)
-        hipLaunchKernelGGL((k_interp<K, D, MODE_STORE, EXT>), dim3(items), dim3(64), 0, s, a);
+        hipLaunchKernelGGL((k_interp<K, D, MODE_STORE, FORM>), dim3(items), dim3(64), 0, s, a);
     else
-        hipLaunchKernelGGL((k_interp<K, D, MODE_REDUCE, EXT>), dim3(items), dim3(64), 0, s, a);
+        hipLaunchKernelGGL((k_interp<K, D, MODE_REDUCE, FORM>), dim3(items), dim3(64), 0, s, a);
     return hipGetLastError();
 }
 
-template <int K, int D, bool EXT>
-static const void *batch_fn(bool store, bool persistent) {
-    if (persistent)
-        return store ? (const void *)k_batch<K, D, MODE_STORE, EXT> : (const void *)k_batch<K, D, MODE_REDUCE, EXT>;
-    return store ? (const void *)k_batch_direct<K, D, MODE_STORE, EXT>
-                 : (const void *)k_batch_direct<K, D, MODE_REDUCE, EXT>;
+hipError_t launch_tables(int K, const TableArgs &a, hipStream_t s) {
+    const uint32_t items = (uint32_t)a.n_progs[0] * (uint32_t)a.job[0].n_stripes +
+                           (uint32_t)a.n_progs[1] * (uint32_t)a.job[1].n_stripes;
+    if (items == 0) return hipSuccess;
+    if (K == 4)
+        hipLaunchKernelGGL(k_tables<4>, dim3(items), dim3(64), 0, s, a);
+    else
+        hipLaunchKernelGGL(k_tables<2>, dim3(items), dim3(64), 0, s, a);
+    return hipGetLastError();
 }
 
-template <int K, int D, bool EXT>
+template <int K, int D, int FORM>
+static const void *batch_fn(bool store, bool persistent) {
+    if (persistent)
+        return store ? (const void *)k_batch<K, D, MODE_STORE, FORM> : (const void *)k_batch<K, D, MODE_REDUCE, FORM>;
+    return store ? (const void *)k_batch_direct<K, D, MODE_STORE, FORM>
+                 : (const void *)k_batch_direct<K, D, MODE_REDUCE, FORM>;
+}
+
+template <int K, int D, int FORM>
 static int grid_bd(bool store) {
     int per_cu = 0, dev = 0, cus = 0;
     hipGetDevice(&dev);
     hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (store)
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_batch<K, D, MODE_STORE, EXT>, 64, 0);
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_batch<K, D, MODE_STORE, FORM>, 64, 0);
     else
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_batch<K, D, MODE_REDUCE, EXT>, 64, 0);
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_batch<K, D, MODE_REDUCE, FORM>, 64, 0);
     return std::max(1, per_cu) * std::max(1, cus);
 }
 
-// Instantiated interpreters: (cases per lane, stack slots, bitwise operators
-// and warp).  The LDS-stack form knows every operator.
+// Instantiated interpreters: (cases per lane, stack slots, form).  The
+// LDS-stack form knows every operator.
 #ifndef TGP_VARIANTS
-#define TGP_VARIANTS(X) X(4, 8, false) X(2, 8, false) X(4, 8, true) X(2, 16, true)
+#define TGP_VARIANTS(X) X(4, 8, kFlat) X(2, 8, kFlat) X(4, 8, kExt) X(2, 16, kExt) X(kTableK, 8, kWide) X(kTableK, 8, kRagged)
 #endif
 
-bool interp_variant_exists(int K, int D, bool bit) {
-    if (D == kLdsSlots) bit = true;
-#define X(k, d, b) if (K == k && D == d && bit == b) return true;
+bool interp_variant_exists(int K, int D, int form) {
+    if (D == kLdsSlots) form = kExt;
+#define X(k, d, f) if (K == k && D == d && form == f) return true;
     TGP_VARIANTS(X)
 #undef X
     return false;
@@ -449,25 +605,25 @@ bool interp_variant_exists(int K, int D, bool bit) {
 int interp_max_stack() { return 8; }
 int interp_lds_stack() { return kLdsSlots; }
 
-hipError_t launch_interp(int K, int D, bool store, const InterpArgs &a, hipStream_t s, bool bit) {
-    if (D == kLdsSlots) bit = true;
-#define X(k, d, b) if (K == k && D == d && bit == b) return launch_kd<k, d, b>(store, a, s);
+hipError_t launch_interp(int K, int D, bool store, const InterpArgs &a, hipStream_t s, int form) {
+    if (D == kLdsSlots) form = kExt;
+#define X(k, d, f) if (K == k && D == d && form == f) return launch_kd<k, d, f>(store, a, s);
     TGP_VARIANTS(X)
 #undef X
     return hipErrorInvalidValue;
 }
 
-const void *batch_kernel(int K, int D, bool store, bool persistent, bool bit) {
-    if (D == kLdsSlots) bit = true;
-#define X(k, d, b) if (K == k && D == d && bit == b) return batch_fn<k, d, b>(store, persistent);
+const void *batch_kernel(int K, int D, bool store, bool persistent, int form) {
+    if (D == kLdsSlots) form = kExt;
+#define X(k, d, f) if (K == k && D == d && form == f) return batch_fn<k, d, f>(store, persistent);
     TGP_VARIANTS(X)
 #undef X
     return nullptr;
 }
 
-int batch_grid(int K, int D, bool store, bool bit) {
-    if (D == kLdsSlots) bit = true;
-#define X(k, d, b) if (K == k && D == d && bit == b) return grid_bd<k, d, b>(store);
+int batch_grid(int K, int D, bool store, int form) {
+    if (D == kLdsSlots) form = kExt;
+#define X(k, d, f) if (K == k && D == d && form == f) return grid_bd<k, d, f>(store);
     TGP_VARIANTS(X)
 #undef X
     return 0;

@@ -116,6 +116,18 @@ __device__ __forceinline__ float f_max(float a, float b) {
     asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
     return r;
 }
+// The same with the second operand in a scalar register (it takes the first
+// source of the instruction; both are bitwise commutative, see above).
+__device__ __forceinline__ float f_min_s(float a, float b) {
+    float r;
+    asm("v_min_f32 %0, %2, %1" : "=v"(r) : "v"(a), "s"(b));
+    return r;
+}
+__device__ __forceinline__ float f_max_s(float a, float b) {
+    float r;
+    asm("v_max_f32 %0, %2, %1" : "=v"(r) : "v"(a), "s"(b));
+    return r;
+}
 // Halving each operand first is exact in the normal range and cannot overflow.
 __device__ __forceinline__ float f_mdist(float a, float b) { return a * 0.5f + b * 0.5f; }
 __device__ __forceinline__ float f_neg(float a) { return -a; }

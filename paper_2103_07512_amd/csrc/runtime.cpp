@@ -7,6 +7,8 @@
 //   * a shared subtree is materialised once in an HBM cache row when
 //     re-computing it at each use costs more VALU work than writing the row
 //     once and reading it at each use (HBM traffic priced in VALU slots);
+//   * on a grid with rows and columns, a subtree that depends on one of the
+//     two alone is evaluated once per row or column into a table;
 //   * subtrees whose evaluation would need more stack slots than the
 //     interpreter keeps in registers are materialised as well, so every
 //     program fits the register stack;
@@ -22,6 +24,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <array>
 #include <atomic>
 #include <chrono>
 #include <cmath>
@@ -127,6 +130,9 @@ const double kOpCost[TGP_NUM_OPS] = {
 // per device (hipGetSymbolAddress, at context creation, with the device
 // current) and that address is what kernels and copies receive.
 constexpr size_t kNoAllocScratchBytes = size_t(64) << 20;
+// Smallest domain evaluated by table programs (a smaller one is a few waves
+// per program either way, and the tables cost a launch).
+constexpr int64_t kTableCases = 1024;
 __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
 
 namespace {
@@ -295,6 +301,30 @@ tgp_status tgp_debug_set_hash_bits(int32_t bits) {
 }
 
 // ---------------------------------------------------------------- domains
+}  // extern "C"
+
+// Where table programs split the axes of a domain (0: nowhere, it is
+// evaluated flat).  Either side must hold at least 8 entries, so that a table
+// entry costs at most an eighth of evaluating its subtree at every case, and
+// the domain at least kTableCases cases.  Columns in multiples of kWideCols
+// make the wide form; otherwise the split with the shorter tables is taken.
+static int32_t domain_split(const tgp_domain_s &d) {
+    if (d.cases < kTableCases) return 0;
+    int best = 0;
+    double best_score = 0;
+    for (int s = d.ndim - 1; s >= 1; --s) {
+        const int64_t r = d.rows(s), c = d.cols(s);
+        if (r < 8 || c < 8) continue;
+        const double score = 1.0 / (double)(r + c) + (c % kWideCols == 0 ? 1.0 : 0.0);
+        if (score > best_score) {
+            best = s;
+            best_score = score;
+        }
+    }
+    return best;
+}
+
+extern "C" {
 tgp_status tgp_domain_create(tgp_ctx ctx, int32_t ndim, const int64_t *shape, const double *lo,
                              const double *hi, tgp_domain *out) {
     if (!ctx || !out || !shape) return fail(ctx, TGP_EINVAL, "NULL argument");
@@ -334,6 +364,7 @@ tgp_status tgp_domain_create(tgp_ctx ctx, int32_t ndim, const int64_t *shape, co
             return fail(ctx, TGP_EHIP, "coordinate table: %s", hipGetErrorString(e));
         }
     }
+    d->split = domain_split(*d);
     *out = d;
     return TGP_OK;
 }
@@ -414,6 +445,7 @@ tgp_status tgp_build_dag(tgp_ctx ctx, const tgp_population *pop, tgp_dag *out) {
             return fail(ctx, (tgp_status)br.status, "build_dag: %s", msg);
         }
         const int64_t U = br.U;
+        d->swap(ctx->spare_dag);
         d->op.resize(U);
         d->value.resize(U);
         d->kid.resize(3 * U);
@@ -452,6 +484,7 @@ tgp_status tgp_build_dag(tgp_ctx ctx, const tgp_population *pop, tgp_dag *out) {
                 ++di;
                 if (d->mult[i] >= 2) ++sh;
             }
+            d->image_ops |= op == TGP_WARP || op == TGP_OR || op == TGP_XOR || op == TGP_AND;
         }
         d->stats.dag_internal = di;
         d->stats.shared_internal = sh;
@@ -495,12 +528,74 @@ void tgp_dag_destroy(tgp_dag dag) {
     hipStreamSynchronize(ctx->stream);  // no queued kernel reads the blocks any more
     dag->plan.release(ctx->pool);
     dag_device_free(&dag->dev, ctx->pool);
+    if (dag->op.capacity() > ctx->spare_dag.op.capacity()) dag->swap(ctx->spare_dag);
+    if (dag->plan.code_host.capacity() > ctx->spare_code.capacity()) dag->plan.code_host.swap(ctx->spare_code);
     delete dag;
 }
 
 }  // extern "C"
 
 // ------------------------------------------------------------------ planner
+namespace {
+
+// A spin-wait hint to the host processor.
+inline void cpu_relax() {
+#if defined(__x86_64__) || defined(__i386__)
+    __builtin_ia32_pause();
+#endif
+}
+
+}  // namespace
+
+HostTeam::~HostTeam() {
+    {
+        std::lock_guard<std::mutex> lk(m_);
+        stop_ = true;
+    }
+    cv_.notify_all();
+    for (auto &t : workers_) t.join();
+}
+
+void HostTeam::run(int T, const std::function<void(int)> &fn) {
+    T = std::min(T, kMaxWorkers + 1);
+    while ((int)workers_.size() < T - 1) {
+        const int id = (int)workers_.size() + 1;
+        workers_.emplace_back(&HostTeam::work, this, id, round_.load());
+    }
+    {
+        std::lock_guard<std::mutex> lk(m_);
+        fn_ = &fn;
+        want_ = T;
+        left_.store(T - 1, std::memory_order_relaxed);
+        round_.fetch_add(1, std::memory_order_release);
+    }
+    cv_.notify_all();
+    fn(0);
+    for (int i = 0; left_.load(std::memory_order_acquire) > 0; ++i) {
+        if (i < 4000) cpu_relax();
+        else std::this_thread::yield();
+    }
+}
+
+// Worker id waits for a round it takes part in (spinning for some
+// microseconds first: the phases of one plan follow each other closely).
+void HostTeam::work(int id, uint64_t seen) {
+    for (;;) {
+        for (int i = 0; i < 2000 && round_.load(std::memory_order_acquire) == seen; ++i) cpu_relax();
+        const std::function<void(int)> *fn = nullptr;
+        {
+            std::unique_lock<std::mutex> lk(m_);
+            cv_.wait(lk, [&] { return stop_ || round_.load(std::memory_order_relaxed) != seen; });
+            if (stop_) return;
+            seen = round_.load(std::memory_order_relaxed);
+            if (id < want_) fn = fn_;
+        }
+        if (!fn) continue;
+        (*fn)(id);
+        left_.fetch_sub(1, std::memory_order_release);
+    }
+}
+
 namespace {
 
 // Processors this process may use: its affinity mask (the machine's count
@@ -527,19 +622,28 @@ unsigned usable_cpus() {
     return n;
 }
 
-// A spin-wait hint to the host processor.
-inline void cpu_relax() {
-#if defined(__x86_64__) || defined(__i386__)
-    __builtin_ia32_pause();
-#endif
+// Runs fn(t) for t = 0 .. T-1 on the team's threads, or (without a team) on
+// threads of its own; the caller's thread is t = 0.
+template <class F>
+void run_threads(HostTeam *team, int T, F &&fn) {
+    if (T <= 1) {
+        fn(0);
+    } else if (team) {
+        team->run(T, fn);
+    } else {
+        std::vector<std::thread> th;
+        for (int t = 1; t < T; ++t) th.emplace_back([&, t] { fn(t); });
+        fn(0);
+        for (auto &x : th) x.join();
+    }
 }
 
-// Runs fn(t, barrier) on T host threads (the caller's thread is t = 0);
+// Runs fn(t, barrier) on T host threads as run_threads does;
 // barrier() returns once all T threads have reached it.  A waiting thread
 // spins for a few microseconds first (the threads of one level usually
 // arrive close together), then yields its processor.
 template <class F>
-void run_team(int T, F &&fn) {
+void run_team(HostTeam *team, int T, F &&fn) {
     std::atomic<int> arrived{0}, generation{0};
     auto barrier = [&]() {
         const int g = generation.load(std::memory_order_acquire);
@@ -552,20 +656,17 @@ void run_team(int T, F &&fn) {
             while (generation.load(std::memory_order_acquire) == g) std::this_thread::yield();
         }
     };
-    std::vector<std::thread> th;
-    for (int t = 1; t < T; ++t) th.emplace_back([&, t] { fn(t, barrier); });
-    fn(0, barrier);
-    for (auto &x : th) x.join();
+    run_threads(team, T, [&](int t) { fn(t, barrier); });
 }
 
 // The nodes 0..U-1 ordered by height (id order within a height) on T
 // threads: order[first[h] .. first[h+1]) are the nodes of height h.
-void height_order(const int32_t *hgt, int64_t U, int T, std::vector<int32_t> &order,
+void height_order(HostTeam *team, const int32_t *hgt, int64_t U, int T, std::vector<int32_t> &order,
                   std::vector<int64_t> &first) {
     std::vector<std::vector<int64_t>> hist(T);
     int32_t H = 0;
     order.resize(U);
-    run_team(T, [&](int t, auto &barrier) {
+    run_team(team, T, [&](int t, auto &barrier) {
         const int64_t b = U * t / T, e = U * (t + 1) / T;
         std::vector<int64_t> &c = hist[t];
         for (int64_t n = b; n < e; ++n) {
@@ -605,41 +706,231 @@ struct Planner {
 
     bool reorder = true;
     double access_cost = 20.0;
+    HostTeam *team = nullptr;  // the planning context's threads (null: own ones)
+
+    // Table programs: programs of subtrees that depend on axes on both sides of the
+    // split read every other variable-dependent subtree from a table, where it
+    // is evaluated once per grid row or column instead of once per case (with
+    // the same operators, so bit for bit the same value).  cls: bit 0, the
+    // subtree depends on an axis below the split (grid rows), bit 1, on
+    // another one (columns); a cached node of class 1 or 2 is a table entry.
+    // A table entry's own program is self-contained, except that it reads the
+    // nested entries (those that bound its stack) from lower levels.
+    int split = 0;
+    double table_slots_per[2] = {0, 0};  // a table entry's size in cache slots
+    std::vector<uint8_t> cls, nested;
+    size_t table_slots = 0;              // the tables' size in cache slots
+    bool tables_over = false;            // the tables do not fit the budget
 
     Planner(const tgp_dag_s &dag, int stack, size_t slots) : d(dag), D(stack), budget_slots(slots) {}
+
+    bool in_table(int64_t n) const { return split > 0 && (cls[n] == 1 || cls[n] == 2); }
+    int axis(int64_t n) const { return (d.op[n] >> 8) & 0xff; }
+    // the tables' size once every entry is marked; false: over the budget
+    bool set_table_slots(const int64_t (&entries)[2]) {
+        const double slots = entries[0] * table_slots_per[0] + entries[1] * table_slots_per[1];
+        table_slots = (size_t)std::ceil(slots);
+        const double row = table_slots_per[0] * slot_bytes, col = table_slots_per[1] * slot_bytes;
+        // 32-bit byte offsets into either table
+        tables_over = table_slots > budget_slots / 2 || entries[0] * row >= 0xffffff00u || entries[1] * col >= 0xffffff00u;
+        return !tables_over;
+    }
+    double slot_bytes = 0;               // bytes of a cache slot
 
     // nodes by height (filled by the parallel preparation or decisions)
     std::vector<int32_t> lorder;
     std::vector<int64_t> lfirst;
     std::vector<uint8_t> folded;  // constant subtrees replaced by their value
     std::vector<float> fold_val;
-    // Operator and arity of every node as the planner sees it (a folded node
-    // is a constant leaf), filled at the start of decide.
-    std::vector<uint8_t> opv, arv;
+    // A node as the planner sees it (a folded node is a constant leaf).  An
+    // absent child is node U, which costs nothing and needs no stack, so that
+    // the passes below have few branches (random trees make them
+    // unpredictable).
+    struct Node {
+        int32_t k[3];
+        uint8_t op, ar;
+    };
+    std::vector<Node> node;
+    // Stack slots a node needs as the child of a program that reads cached
+    // values (g) or, in a table entry's own program, nested ones (t), and
+    // whether that program's operators can fuse it.
+    struct Need {
+        uint8_t g, t, fuse_g, fuse_t;
+    };
+    std::vector<Need> need;
+    std::vector<std::vector<uint2>> emitted;  // each emitting thread's programs
+    std::vector<int64_t> uses;
+    std::vector<int32_t> dep;
     double valu_dag = 0;  // cost-model slots of every DAG node once (unfolded)
-    int op(int64_t n) const { return opv[n]; }
-    int arity(int64_t n) const { return arv[n]; }
+    int op(int64_t n) const { return node[n].op; }
+    int arity(int64_t n) const { return node[n].ar; }
 
-    // Whether child j of binary node n, evaluated last, is read by the
-    // node's fused form (x, y, a constant or a cached row under an operator
-    // with a fused form): it then never occupies a stack slot.  The emitter
-    // fuses exactly these (cached only grows, so a later decision can only
-    // fuse more).
-    bool fuses_last(int64_t n, int j) const {
-        const int o = opv[n];
-        if (fused_index(o, j == 0 && !is_commutative(o)) < 0) return false;
-        const int32_t c = d.kid[3 * n + j];
-        if (cached[c]) return true;
-        if (opv[c] == TGP_CONST) return true;
-        return opv[c] == TGP_VAR && ((d.op[c] >> 8) & 0xff) <= 1;
+    // Exchanges the arrays that a context keeps between plans.
+    void swap_scratch(PlanScratch &o);
+
+    void resize(int64_t U) {
+        node.resize(U + 1);
+        node[U] = Node{{(int32_t)U, (int32_t)U, (int32_t)U}, TGP_CONST, 0};
+        cached.assign(U + 1, 0);
+        pre.assign(U + 1, 0);
+        cost.resize(U + 1);
+        cost[U] = 0.0;
+        perm.assign(U + 1, 0);
+        need.resize(U + 1);
+        need[U] = Need{0, 0, 0, 0};
+        uses.assign(U + 1, 0);
+        dep.assign(U + 1, 0);
+        level.assign(U + 1, -1);
+        slot.assign(U + 1, -1);
+        cls.assign(split > 0 ? U + 1 : 0, 0);
+        nested.assign(split > 0 ? U + 1 : 0, 0);
     }
-    // Stack slots a node needs with its children in order o: the i-th
-    // child evaluated sits on i values; a fused last child takes none.
-    int order_need(int64_t n, int a, const uint8_t *o, const int *r) const {
-        if (a == 2 && fuses_last(n, o[1])) return r[o[0]];
-        int v = 0;
-        for (int q = 0; q < a; ++q) v = std::max(v, q + r[o[q]]);
-        return v;
+    // The decisions of planned nodes end at node U - 1.
+    void trim(int64_t U) {
+        cached.resize(U);
+        level.resize(U);
+        slot.resize(U);
+    }
+
+    // Node n's record; returns its unfolded cost.
+    double load(int64_t n, int64_t U) {
+        const int o = d.op[n] & 0xff;
+        const bool leaf = !folded.empty() && folded[n];
+        Node &x = node[n];
+        for (int j = 0; j < 3; ++j) {
+            const int32_t c = d.kid[3 * n + j];
+            x.k[j] = leaf || c < 0 ? (int32_t)U : c;
+        }
+        x.op = (uint8_t)(leaf ? TGP_CONST : o);
+        x.ar = (uint8_t)(leaf ? 0 : kArity[o]);
+        return kOpCost[o];
+    }
+    // Marks are made by several threads at once in the level-parallel passes.
+    static bool mark(std::vector<uint8_t> &v, int64_t n) {  // returns whether n was not marked before
+        if (__atomic_load_n(&v[n], __ATOMIC_RELAXED)) return false;
+        return __atomic_exchange_n(&v[n], (uint8_t)1, __ATOMIC_RELAXED) == 0;
+    }
+
+    // Class and cost of node n from its children's, whether it stays resident
+    // (its values over this domain are kept from an earlier evaluation and
+    // recomputing them costs more than the read), and the table entries that
+    // it reads when the plan has tables.
+    void up_cost(int64_t n, bool resident, bool is_root) {
+        const Node &x = node[n];
+        double c = kOpCost[x.op];
+        if (split > 0) {
+            const uint8_t own = x.op == TGP_VAR ? (axis(n) < split ? 1 : 2) : 0;
+            const uint8_t k0 = cls[x.k[0]], k1 = cls[x.k[1]], k2 = cls[x.k[2]];
+            const uint8_t m = own | k0 | k1 | k2;
+            cls[n] = m;
+            if (m == 3) {
+                for (int j = 0; j < 3; ++j) {
+                    const bool tab = in_table(x.k[j]);
+                    c += tab ? 1.0 : cost[x.k[j]];
+                    if (tab) __atomic_store_n(&cached[x.k[j]], (uint8_t)1, __ATOMIC_RELAXED);
+                }
+            } else {
+                c += cost[x.k[0]] + cost[x.k[1]] + cost[x.k[2]];
+                if (m && is_root) __atomic_store_n(&cached[n], (uint8_t)1, __ATOMIC_RELAXED);
+            }
+        } else {
+            c += cost[x.k[0]] + cost[x.k[1]] + cost[x.k[2]];
+        }
+        cost[n] = c;
+        if (resident && d.precached[n] && x.ar > 0 && !in_table(n) && c > access_cost) cached[n] = pre[n] = 1;
+    }
+
+    // Stack need and child order of node n.  Children are evaluated in
+    // decreasing order of the stack they need (Sethi-Ullman, a fused last
+    // operand taking no slot: x, y, a constant or a value read from a row
+    // under an operator with a fused form); a node whose children still
+    // cannot be evaluated within D slots gets its most demanding child's
+    // subtree spilled: spill(child) is called, once per spilled child.
+    template <class S>
+    void up_need(int64_t n, S &&spill) {
+        const Node &x = node[n];
+        const bool tab = in_table(n);
+        auto r_of = [&](int32_t c) { return (int)(tab ? need[c].t : need[c].g); };
+        auto f_of = [&](int32_t c) { return (int)(tab ? need[c].fuse_t : need[c].fuse_g); };
+        int r[3] = {r_of(x.k[0]), r_of(x.k[1]), r_of(x.k[2])};
+        int best = 0, best_p = 0;
+        for (;;) {
+            int worst = 0;  // the most demanding child (the first one of several)
+            if (x.op == TGP_WARP) {  // t0 then t1 on the stack, in that order
+                best = std::max(r[1], 1 + r[2]);
+                best_p = 0;
+                worst = r[1] >= r[2] ? 1 : 2;
+            } else if (x.ar < 3) {
+                // (an absent child needs nothing and fuses nothing: the same
+                // arithmetic serves every arity below three)
+                const int f0 = (kOpForms.forward[x.op] >= 0) & f_of(x.k[1]);
+                const int f1 = (kOpForms.backward[x.op] >= 0) & f_of(x.k[0]);
+                const int v0 = std::max(r[0], f0 ? 0 : 1 + r[1]);
+                const int v1 = std::max(r[1], f1 ? 0 : 1 + r[0]) | (x.ar == 2 && reorder ? 0 : 256);
+                best = std::min(v0, v1);
+                best_p = v1 < v0 ? 2 : 0;
+                worst = r[1] > r[0] ? 1 : 0;
+            } else {
+                best = 1 << 30;
+                for (int p = 0; p < (reorder ? 6 : 1); ++p) {
+                    const uint8_t *o = kPerms[p];
+                    const int v = std::max(r[o[0]], std::max(1 + r[o[1]], 2 + r[o[2]]));
+                    if (v < best) {
+                        best = v;
+                        best_p = p;
+                    }
+                }
+                for (int j = 1; j < 3; ++j)
+                    if (r[j] > r[worst]) worst = j;
+            }
+            if (best <= D) break;
+            const int32_t c = x.k[worst];
+            spill(c);
+            for (int j = 0; j < 3; ++j)
+                if (x.k[j] == c) r[j] = 1;
+        }
+        best = x.ar == 0 ? 1 : best;
+        perm[n] = (uint8_t)best_p;
+        // as a child: a terminal or a value can be fused, a value takes one slot
+        const bool value = in_table(n) || cached[n];
+        const bool var = x.op == TGP_VAR && (split > 0 || axis(n) <= 1), cst = x.op == TGP_CONST;
+        need[n] = Need{(uint8_t)(value ? 1 : best), (uint8_t)best, (uint8_t)(value || cst || (var && split == 0)),
+                       (uint8_t)(cst || var)};
+    }
+    // Node c becomes a value: a cache row, or (in a table's own program) a
+    // nested table entry.  Returns whether it was not one before.
+    bool spill_node(int32_t c) {
+        if (!in_table(c)) {
+            need[c].g = 1;
+            need[c].fuse_g = 1;
+            return mark(cached, c);
+        }
+        mark(cached, c);
+        need[c].t = 1;
+        need[c].fuse_t = 1;
+        return mark(nested, c);
+    }
+
+    // Whether caching node n, evaluated uses[n] times, pays for its traffic.
+    bool pays(int64_t n) const {
+        const double un = (double)uses[n];
+        return un >= 2 && !cached[n] && access_cost >= 0 && node[n].ar > 0 && !in_table(n) &&
+               cost[n] * (un - 1) > access_cost * (un + 1);
+    }
+    // How often node n evaluates each of its children.
+    int64_t contribution(int64_t n) const { return pre[n] ? 0 : (cached[n] ? 1 : uses[n]); }
+    // Fill level of node n, after the levels of its children.
+    void up_level(int64_t n) {
+        const Node &x = node[n];
+        if (cached[n] && !pre[n] && uses[n] == 0) cached[n] = 0;  // a spill that nothing reads
+        int32_t dp = 0;
+        const std::vector<uint8_t> &value = in_table(n) ? nested : cached;
+        for (int j = 0; j < 3; ++j) {
+            const int32_t c = x.k[j];
+            dp = std::max(dp, value[c] ? level[c] + 1 : dep[c]);
+        }
+        dep[n] = dp;
+        level[n] = cached[n] && !pre[n] ? dp : -1;  // resident: available before the first level
     }
 
     // The same decisions made level by level (DAG node heights) on T host
@@ -652,163 +943,91 @@ struct Planner {
     // once.  Cache-budget admissions are made in node order within a level.
     tgp_status decide_parallel(const std::vector<int32_t> &rootrefs, std::string &why, int T) {
         const int64_t U = (int64_t)d.op.size();
-        const int32_t *kid = d.kid.data();
-        const int32_t *hgt = d.height.data();
-        opv.resize(U);
-        arv.resize(U);
-        cached.assign(U, 0);
-        pre.assign(U, 0);
-        cost.resize(U);
-        perm.assign(U, 0);
-        std::vector<uint8_t> need(U, 1);
-        std::vector<int64_t> uses(U, 0);
-        std::vector<int32_t> dep(U, 0);
-        level.assign(U, -1);
-        slot.assign(U, -1);
-        const bool any_folded = !folded.empty();
-        auto range = [U, T](int t, int64_t &b, int64_t &e) {
-            b = U * t / T;
-            e = U * (t + 1) / T;
-        };
-        if (lorder.size() != (size_t)U) height_order(hgt, U, T, lorder, lfirst);
+        if (lorder.size() != (size_t)U) height_order(team, d.height.data(), U, T, lorder, lfirst);
         const std::vector<int32_t> &order = lorder;
-        const std::vector<int64_t> &lvl_first = lfirst;
-        const int32_t H = (int32_t)lvl_first.size() - 2;
+        const int32_t H = (int32_t)lfirst.size() - 2;
+        resize(U);
         std::vector<double> valu_part(T, 0.0);
         std::vector<std::vector<int32_t>> spill(T), cand(T);
-        std::vector<int64_t> slot_part(T + 1, 0);
-        std::atomic<int64_t> used{0};
+        std::vector<std::array<int64_t, 3>> slot_part(T + 1);  // cache rows, row table, column table
+        for (auto &c : slot_part) c.fill(0);
+        std::vector<std::array<int64_t, 2>> tab_part(T);
+        std::atomic<int64_t> used{0}, table_spills{0};
+        std::atomic<bool> warps{false};
+        const bool resident = !d.precached.empty() && access_cost >= 0;
         tgp_status result = TGP_OK;
-        auto level_nodes = [&](int32_t h, int t, int64_t &b, int64_t &e) {
-            const int64_t n0 = lvl_first[h], n1 = lvl_first[h + 1];
-            b = n0 + (n1 - n0) * t / T;
-            e = n0 + (n1 - n0) * (t + 1) / T;
-        };
-        auto mark = [&](int32_t c) {  // returns whether c was not cached before
-            return __atomic_exchange_n(&cached[c], (uint8_t)1, __ATOMIC_RELAXED) == 0;
-        };
-        run_team(T, [&](int t, auto &barrier) {
-            int64_t b, e;
-            range(t, b, e);
-            // operators, arities, cost-model work
+        run_team(team, T, [&](int t, auto &barrier) {
+            const int64_t b = U * t / T, e = U * (t + 1) / T;
+            auto for_level = [&](int32_t h, auto &&fn) {
+                const int64_t n0 = lfirst[h], n1 = lfirst[h + 1];
+                for (int64_t i = n0 + (n1 - n0) * t / T; i < n0 + (n1 - n0) * (t + 1) / T; ++i) fn(order[i]);
+            };
             double v = 0;
+            bool w = false;
             for (int64_t n = b; n < e; ++n) {
-                const int o = d.op[n] & 0xff;
-                v += kOpCost[o];
-                const int x = any_folded && folded[n] ? TGP_CONST : o;
-                opv[n] = (uint8_t)x;
-                arv[n] = (uint8_t)kArity[x];
+                v += load(n, U);
+                w |= node[n].op == TGP_WARP;
             }
             valu_part[t] = v;
+            if (w) warps = true;
             barrier();
-            // cost, bottom-up
-            for (int32_t h = 0; h <= H; ++h) {
-                int64_t lb, le;
-                level_nodes(h, t, lb, le);
-                for (int64_t i = lb; i < le; ++i) {
-                    const int32_t n = order[i];
-                    double c = kOpCost[opv[n]];
-                    const int32_t *k = kid + 3 * (int64_t)n;
-                    const int a = arv[n];
-                    if (a > 0) c += cost[k[0]];
-                    if (a > 1) c += cost[k[1]];
-                    if (a > 2) c += cost[k[2]];
-                    cost[n] = c;
+            const bool warp_first = warps;
+            if (warp_first) {  // every cost, then the values warps gather from
+                for (int32_t h = 0; h <= H; ++h) {
+                    for_level(h, [&](int32_t n) { up_cost(n, resident, rootrefs[n] > 0); });
+                    barrier();
                 }
+                int64_t u = 0;
+                for (int64_t n = b; n < e; ++n)
+                    if (node[n].op == TGP_WARP && mark(cached, node[n].k[0])) ++u;
+                used.fetch_add(u);
                 barrier();
             }
-            // resident subtrees and warp sources
-            if (!d.precached.empty() && access_cost >= 0)
-                for (int64_t n = b; n < e; ++n)
-                    if (d.precached[n] && arv[n] > 0 && cost[n] > access_cost) cached[n] = pre[n] = 1;
-            barrier();
-            int64_t u = 0;
-            for (int64_t n = b; n < e; ++n)
-                if (opv[n] == TGP_WARP && mark(kid[3 * n])) ++u;
-            used.fetch_add(u);
-            barrier();
-            // stack need, bottom-up; spills of one level applied after it
+            // bottom-up; the spills of one level are applied after it
             for (int32_t h = 0; h <= H; ++h) {
-                int64_t lb, le;
-                level_nodes(h, t, lb, le);
                 spill[t].clear();
-                for (int64_t i = lb; i < le; ++i) {
-                    const int32_t n = order[i];
-                    const int a = arv[n];
-                    if (a == 0) continue;
-                    const int32_t *k = kid + 3 * (int64_t)n;
-                    auto ref_need = [&](int32_t c) { return cached[c] ? 1 : (int)need[c]; };
-                    if (opv[n] == TGP_WARP) {  // t0 then t1 on the stack, in that order
-                        int r1 = ref_need(k[1]), r2 = ref_need(k[2]);
-                        while (std::max(r1, 1 + r2) > D) {
-                            const int32_t c = r1 >= r2 ? k[1] : k[2];
-                            spill[t].push_back(c);
-                            if (k[1] == c) r1 = 1;
-                            if (k[2] == c) r2 = 1;
-                        }
-                        need[n] = (uint8_t)std::max(r1, 1 + r2);
-                        continue;
-                    }
-                    if (a == 1) {
-                        need[n] = (uint8_t)ref_need(k[0]);
-                        continue;
-                    }
-                    int r[3] = {0, 0, 0};
-                    for (int j = 0; j < a; ++j) r[j] = ref_need(k[j]);
-                    for (;;) {
-                        int best_p = 0, best = 1 << 30;
-                        const int n_orders = reorder ? (a == 3 ? 6 : 2) : 1;
-                        for (int p = 0; p < n_orders; ++p) {
-                            const uint8_t *o = a == 2 ? (p ? kPerms[2] : kPerms[0]) : kPerms[p];
-                            const int vv = order_need(n, a, o, r);
-                            if (vv < best) {
-                                best = vv;
-                                best_p = a == 2 ? (p ? 2 : 0) : p;
-                            }
-                        }
-                        if (best <= D) {
-                            need[n] = (uint8_t)best;
-                            perm[n] = (uint8_t)best_p;
-                            break;
-                        }
-                        int wj = 0;
-                        for (int j = 1; j < a; ++j)
-                            if (r[j] > r[wj]) wj = j;
-                        spill[t].push_back(k[wj]);
-                        for (int j = 0; j < a; ++j)
-                            if (k[j] == k[wj]) r[j] = 1;
-                    }
-                }
+                for_level(h, [&](int32_t n) {
+                    if (!warp_first) up_cost(n, resident, rootrefs[n] > 0);
+                    up_need(n, [&](int32_t c) { spill[t].push_back(c); });
+                });
                 barrier();
-                int64_t su = 0;
+                int64_t su = 0, st = 0;
                 for (int32_t c : spill[t])
-                    if (mark(c)) ++su;
-                used.fetch_add(su);
+                    if (spill_node(c)) ++(in_table(c) ? st : su);
+                if (su) used.fetch_add(su);
+                if (st) table_spills.fetch_add(st);
+                barrier();
+            }
+            if (split > 0) {
+                tab_part[t] = {0, 0};
+                for (int64_t n = b; n < e; ++n)
+                    if (cached[n] && in_table(n)) ++tab_part[t][cls[n] - 1];
                 barrier();
             }
             if (t == 0) {
-                spills = used.load();
-                if ((size_t)spills > budget_slots) {
+                spills = used.load() + table_spills.load();
+                if (split > 0) {
+                    int64_t entries[2] = {0, 0};
+                    for (int i = 0; i < T; ++i)
+                        for (int q = 0; q < 2; ++q) entries[q] += tab_part[i][q];
+                    if (!set_table_slots(entries)) result = TGP_ENOMEM;
+                    used.fetch_add((int64_t)table_slots);
+                }
+                if ((size_t)used.load() > budget_slots) {
+                    tables_over = split > 0;
                     why = "the subtree cache needed to bound the evaluator stack exceeds the cache budget";
                     result = TGP_ENOMEM;
                 }
             }
-            barrier();
-            if (result != TGP_OK) return;
             // use counts, top-down; caching where it pays for its HBM traffic
             for (int64_t n = b; n < e; ++n) uses[n] = rootrefs[n];
             barrier();
+            if (result != TGP_OK) return;
             for (int32_t h = H; h >= 0; --h) {
-                int64_t lb, le;
-                level_nodes(h, t, lb, le);
                 cand[t].clear();
-                for (int64_t i = lb; i < le; ++i) {
-                    const int32_t n = order[i];
-                    const double un = (double)uses[n];
-                    if (!cached[n] && access_cost >= 0 && arv[n] > 0 && un >= 2 &&
-                        cost[n] * (un - 1) > access_cost * (un + 1))
-                        cand[t].push_back(n);
-                }
+                for_level(h, [&](int32_t n) {
+                    if (pays(n)) cand[t].push_back(n);
+                });
                 barrier();
                 if (t == 0) {  // admissions in node order (within the budget)
                     for (int i = 0; i < T; ++i)
@@ -822,202 +1041,106 @@ struct Planner {
                 // A count is at most the number of occurrences of the node in
                 // the population's trees (each unit is one root-to-node path),
                 // so it cannot overflow.  Leaves are skipped unless cached (a
-                // warp source): nothing reads their counts, and they are the
-                // most shared nodes, so their additions would contend most.
-                for (int64_t i = lb; i < le; ++i) {
-                    const int32_t n = order[i];
-                    const int64_t contrib = pre[n] ? 0 : (cached[n] ? 1 : uses[n]);
+                // warp source, a table entry): nothing reads their counts, and
+                // they are the most shared nodes, so their additions would
+                // contend most.
+                for_level(h, [&](int32_t n) {
+                    const int64_t contrib = contribution(n);
                     if (contrib > 0)
-                        for (int j = 0; j < arv[n]; ++j) {
-                            const int32_t c = kid[3 * (int64_t)n + j];
-                            if (arv[c] > 0 || cached[c]) __atomic_fetch_add(&uses[c], contrib, __ATOMIC_RELAXED);
+                        for (int j = 0; j < node[n].ar; ++j) {
+                            const int32_t c = node[n].k[j];
+                            if (node[c].ar > 0 || (cached[c] && __atomic_load_n(&uses[c], __ATOMIC_RELAXED) == 0))
+                                __atomic_fetch_add(&uses[c], contrib, __ATOMIC_RELAXED);
                         }
-                }
+                });
                 barrier();
             }
-            // spills below resident subtrees that nothing else reads
-            for (int64_t n = b; n < e; ++n)
-                if (cached[n] && !pre[n] && uses[n] == 0) cached[n] = 0;
-            barrier();
-            // levels of the cached nodes, bottom-up
             for (int32_t h = 0; h <= H; ++h) {
-                int64_t lb, le;
-                level_nodes(h, t, lb, le);
-                for (int64_t i = lb; i < le; ++i) {
-                    const int32_t n = order[i];
-                    int32_t dp = 0;
-                    for (int j = 0; j < arv[n]; ++j) {
-                        const int32_t c = kid[3 * (int64_t)n + j];
-                        dp = std::max(dp, cached[c] ? level[c] + 1 : dep[c]);
-                    }
-                    dep[n] = dp;
-                    if (pre[n]) level[n] = -1;  // available before the first fill level
-                    else if (cached[n]) level[n] = dp;
-                }
+                for_level(h, [&](int32_t n) { up_level(n); });
                 barrier();
             }
             // slots in node order
-            int64_t cnt = 0;
-            for (int64_t n = b; n < e; ++n) cnt += cached[n];
+            std::array<int64_t, 3> cnt{0, 0, 0};
+            for (int64_t n = b; n < e; ++n)
+                if (cached[n]) ++cnt[in_table(n) ? cls[n] : 0];
             slot_part[t + 1] = cnt;
             barrier();
-            if (t == 0)
-                for (int i = 0; i < T; ++i) slot_part[i + 1] += slot_part[i];
-            barrier();
-            int32_t ns = (int32_t)slot_part[t];
+            std::array<int64_t, 3> ns{0, 0, 0};
+            for (int i = 0; i <= t; ++i)
+                for (int q = 0; q < 3; ++q) ns[q] += slot_part[i][q];
             for (int64_t n = b; n < e; ++n)
-                if (cached[n]) slot[n] = ns++;
+                if (cached[n]) slot[n] = (int32_t)ns[in_table(n) ? cls[n] : 0]++;
         });
         valu_dag = 0;
         for (double v : valu_part) valu_dag += v;
+        trim(U);
         return result;
     }
 
     // Decide the cached nodes; returns TGP_OK or an error.
     tgp_status decide(const std::vector<int32_t> &rootrefs, std::string &why) {
         const int64_t U = (int64_t)d.op.size();
-        const int32_t *kid = d.kid.data();
-        opv.resize(U);
-        arv.resize(U);
+        resize(U);
         valu_dag = 0;
-        const bool any_folded = !folded.empty();
+        bool warps = false;
         for (int64_t n = 0; n < U; ++n) {
-            const int o = d.op[n] & 0xff;
-            valu_dag += kOpCost[o];
-            const int v = any_folded && folded[n] ? TGP_CONST : o;
-            opv[n] = (uint8_t)v;
-            arv[n] = (uint8_t)kArity[v];
+            valu_dag += load(n, U);
+            warps |= node[n].op == TGP_WARP;
         }
-        cached.assign(U, 0);
-        pre.assign(U, 0);
-        cost.resize(U);
-        for (int64_t n = 0; n < U; ++n) {
-            double c = kOpCost[opv[n]];
-            const int32_t *k = kid + 3 * n;
-            const int a = arv[n];
-            if (a > 0) c += cost[k[0]];
-            if (a > 1) c += cost[k[1]];
-            if (a > 2) c += cost[k[2]];
-            cost[n] = c;
-        }
-        // Subtrees whose values over this domain are already resident (kept
-        // from an earlier evaluation) are read instead of recomputed when
-        // recomputing costs more than the read.
-        if (!d.precached.empty() && access_cost >= 0)
-            for (int64_t n = 0; n < U; ++n)
-                if (d.precached[n] && arv[n] > 0 && cost[n] > access_cost) cached[n] = pre[n] = 1;
-        // The value a warp gathers from is read at other cases than the one
-        // being evaluated, so it is always materialised (a cached row).
+        const bool resident = !d.precached.empty() && access_cost >= 0;
         size_t used = 0;
-        for (int64_t n = 0; n < U; ++n)
-            if (opv[n] == TGP_WARP && !cached[kid[3 * n]]) {
-                cached[kid[3 * n]] = 1;
-                ++used;
-            }
-        // Bottom-up: bound the register stack of every program.  Children are
-        // evaluated in decreasing order of the stack they need (Sethi-Ullman,
-        // a fused last operand taking no slot); a node whose children still
-        // cannot be evaluated within D slots gets its most demanding child's
-        // subtree spilled to a cache row.
-        std::vector<uint8_t> need(U, 1);
-        perm.assign(U, 0);
-        auto ref_need = [&](int32_t c) { return cached[c] ? 1 : (int)need[c]; };
-        for (int64_t n = 0; n < U; ++n) {
-            const int a = arv[n];
-            if (a == 0) continue;
-            const int32_t *k = kid + 3 * n;
-            if (opv[n] == TGP_WARP) {  // t0 then t1 on the stack, in that order
-                for (;;) {
-                    const int32_t c1 = k[1], c2 = k[2];
-                    const int r1 = ref_need(c1), r2 = ref_need(c2);
-                    const int v = std::max(r1, 1 + r2);
-                    if (v <= D) {
-                        need[n] = (uint8_t)v;
-                        break;
-                    }
-                    cached[r1 >= r2 ? c1 : c2] = 1;
-                    ++used;
-                }
-                continue;
-            }
-            if (a == 1) {  // a unary node needs what its operand needs
-                need[n] = (uint8_t)ref_need(k[0]);
-                continue;
-            }
-            for (;;) {
-                int r[3] = {0, 0, 0};
-                for (int j = 0; j < a; ++j) r[j] = ref_need(k[j]);
-                // stable sort of child positions by need, largest first
-                int best_p = 0, best = 1 << 30;
-                const int n_orders = reorder ? (a == 3 ? 6 : 2) : 1;
-                for (int p = 0; p < n_orders; ++p) {
-                    const uint8_t *o = a == 2 ? (p ? kPerms[2] : kPerms[0]) : kPerms[p];
-                    const int v = order_need(n, a, o, r);
-                    if (v < best) {
-                        best = v;
-                        best_p = a == 2 ? (p ? 2 : 0) : p;
-                    }
-                }
-                if (best <= D) {
-                    need[n] = (uint8_t)best;
-                    perm[n] = (uint8_t)best_p;
-                    break;
-                }
-                int wj = 0;
-                for (int j = 1; j < a; ++j)
-                    if (r[j] > r[wj]) wj = j;
-                cached[k[wj]] = 1;
-                ++used;
-            }
+        int64_t table_spills = 0;  // table entries only a table's own program needs
+        // The value a warp gathers from is read at other cases than the one
+        // being evaluated, so it is always materialised (a cached row), which
+        // every other parent of it then reads.
+        if (warps) {
+            for (int64_t n = 0; n < U; ++n) up_cost(n, resident, rootrefs[n] > 0);
+            for (int64_t n = 0; n < U; ++n)
+                if (node[n].op == TGP_WARP && mark(cached, node[n].k[0])) ++used;
         }
-        spills = (int64_t)used;
+        // Bottom-up (children have smaller ids).
+        for (int64_t n = 0; n < U; ++n) {
+            if (!warps) up_cost(n, resident, rootrefs[n] > 0);
+            up_need(n, [&](int32_t c) {
+                const bool fresh = spill_node(c);
+                if (in_table(c)) table_spills += fresh;
+                else used += fresh;
+            });
+        }
+        spills = (int64_t)used + table_spills;
+        if (split > 0) {
+            int64_t entries[2] = {0, 0};
+            for (int64_t n = 0; n < U; ++n)
+                if (cached[n] && in_table(n)) ++entries[cls[n] - 1];
+            if (!set_table_slots(entries)) return TGP_ENOMEM;
+            used += table_slots;
+        }
         if (used > budget_slots) {
+            tables_over = split > 0;
             why = "the subtree cache needed to bound the evaluator stack exceeds the cache budget";
             return TGP_ENOMEM;
         }
         // Top-down: how often each node would be evaluated, and whether
         // caching it pays for its HBM traffic (within the remaining budget).
-        std::vector<double> uses(rootrefs.begin(), rootrefs.end());
+        for (int64_t n = 0; n < U; ++n) uses[n] = rootrefs[n];
         for (int64_t n = U - 1; n >= 0; --n) {
-            const int a = arv[n];
-            if (!cached[n] && access_cost >= 0 && a > 0 && uses[n] >= 2 && used < budget_slots) {
-                const double save = cost[n] * (uses[n] - 1);
-                const double pay = access_cost * (uses[n] + 1);
-                if (save > pay) {
-                    cached[n] = 1;
-                    ++used;
-                }
+            if (pays(n) && used < budget_slots) {
+                cached[n] = 1;
+                ++used;
             }
-            const double contrib = pre[n] ? 0.0 : (cached[n] ? 1.0 : uses[n]);
-            if (contrib > 0)
-                for (int j = 0; j < a; ++j) uses[kid[3 * n + j]] += contrib;
+            const int64_t contrib = contribution(n);
+            const Node &x = node[n];
+            uses[x.k[0]] += contrib;
+            uses[x.k[1]] += contrib;
+            uses[x.k[2]] += contrib;
         }
-        // A spill below a resident subtree that nothing else reads is dropped
-        // (its fill would be wasted).  Then levels and slots.
-        std::vector<int32_t> dep(U, 0);
-        level.assign(U, -1);
-        slot.assign(U, -1);
-        int32_t ns = 0;
+        // Levels and slots.
+        int32_t ns[3] = {0, 0, 0};  // cache rows, row table, column table
         for (int64_t n = 0; n < U; ++n) {
-            if (cached[n] && !pre[n] && uses[n] == 0) {
-                cached[n] = 0;
-                --used;
-            }
-            int32_t dp = 0;
-            const int32_t *k = kid + 3 * n;
-            for (int j = 0; j < arv[n]; ++j) {
-                const int32_t c = k[j];
-                dp = std::max(dp, cached[c] ? level[c] + 1 : dep[c]);
-            }
-            dep[n] = dp;
-            if (pre[n]) {
-                level[n] = -1;  // available before the first fill level
-                slot[n] = ns++;
-            } else if (cached[n]) {
-                level[n] = dp;
-                slot[n] = ns++;
-            }
+            up_level(n);
+            if (cached[n]) slot[n] = ns[in_table(n) ? cls[n] : 0]++;
         }
+        trim(U);
         return TGP_OK;
     }
 
@@ -1033,14 +1156,15 @@ struct Planner {
 
     // The fused-form kind and .y word of child c when c can be a fused
     // operand (x, y, a constant or a cached row), else -1.
-    int fuse_operand(int32_t c, uint32_t &y) const {
-        if (cached[c]) {
+    // uc: the class of the program (3 unless it fills a table).
+    int fuse_operand(int32_t c, uint32_t &y, int uc) const {
+        if (uc == 3 ? cached[c] : nested[c]) {
             y = (uint32_t)slot[c];
-            return kFuseCache;
+            return uc == 3 && in_table(c) ? (cls[c] == 1 ? kFuseX : kFuseY) : kFuseCache;
         }
         const int o = op(c);
         if (o == TGP_VAR) {
-            const int v = (d.op[c] >> 8) & 0xff;
+            const int v = axis(c) - (uc == 2 ? split : 0);
             return v == 0 ? kFuseX : (v == 1 ? kFuseY : -1);
         }
         if (o == TGP_CONST) {
@@ -1056,97 +1180,170 @@ struct Planner {
     // fused form and reads that child itself.  Adds the cost-model slots of
     // its instructions to *valu; sets *ext when it emits a bitwise operator,
     // warp or the third axis, *warp_used for warp.
+    // The program of a table entry is a flat one over its own axes; with `ref`
+    // a root that is a table entry is read from its table instead.
     void emit(int32_t root, std::vector<uint2> &code, int64_t &cache_reads, double *valu, bool *ext,
-              bool *warp_used) const {
+              bool *warp_used, bool ref) const {
+        if (ref && in_table(root)) {
+            code.push_back(uint2{cls[root] == 1 ? (uint32_t)I_X : (uint32_t)I_Y, (uint32_t)slot[root]});
+            code.push_back(uint2{(1u << 8) | I_END, 0});
+            *valu += 1.0;
+            return;
+        }
+        const int uc = in_table(root) ? cls[root] : 3;
+        auto value = [&](int32_t n) { return n != root && (uc == 3 ? cached[n] : nested[n]) != 0; };
+        // An operator whose operands are being emitted: its stacked children
+        // in evaluation order, and the operand its fused form reads itself.
         struct Frame {
-            int32_t n, done;  // node, children emitted
-            int32_t fv;       // fused form index, or -1
+            int32_t n;
+            int32_t kid[3];
+            uint8_t done, stacked;
+            int8_t fv;         // fused form index, or -1
+            uint8_t kind;      // fused operand kind
+            uint32_t y;        // and its instruction word
+            int32_t operand;   // and node
         };
-        std::vector<Frame> st;
+        thread_local std::vector<Frame> st;
+        st.clear();
+        int64_t reads = 0;
+        double slots = 0;
         uint32_t S = 0;  // stack depth before the next instruction
-        auto frame = [&](int32_t n) {
-            Frame f{n, 0, -1};
-            const int o = op(n);
-            if (n == root || !cached[n]) {
-                if (arity(n) == 2 && o != TGP_WARP) {
-                    const int last = kPerms[perm[n]][1];
+        auto put = [&](uint32_t c, uint32_t y) { code.push_back(uint2{c | S << 8, y}); };
+        // a value read from a row or a terminal is one instruction; an
+        // operator opens a frame
+        auto open = [&](int32_t n) {
+            if (value(n)) {
+                const bool tab = uc == 3 && in_table(n);
+                put(tab ? (cls[n] == 1 ? I_X : I_Y) : I_CACHE, (uint32_t)slot[n]);
+                if (uc == 3 && !tab) ++reads;
+                slots += 1.0;
+                ++S;
+                return;
+            }
+            const int o = op(n), a = arity(n);
+            slots += kOpCost[o];
+            if (a == 0) {
+                if (o == TGP_VAR) {
+                    const int v = axis(n) - (uc == 2 ? split : 0);
+                    put(v == 0 ? I_X : (v == 1 ? I_Y : I_Z), 0);
+                    if (v > 1) *ext = true;  // the third axis: extended interpreter only
+                } else {
+                    put(I_CONST, const_word(n));
+                }
+                ++S;
+                return;
+            }
+            Frame f;
+            f.n = n;
+            f.done = 0;
+            f.fv = -1;
+            f.stacked = (uint8_t)a;
+            const int32_t *k = node[n].k;
+            if (o == TGP_WARP) {  // stack children t0, t1 only
+                f.kid[0] = k[1];
+                f.kid[1] = k[2];
+                f.stacked = 2;
+            } else {
+                const uint8_t *order = kPerms[perm[n]];
+                for (int j = 0; j < a; ++j) f.kid[j] = k[order[j]];
+                if (a == 2) {
+                    const int fv = order[1] ? kOpForms.forward[o] : kOpForms.backward[o];
                     uint32_t y = 0;
-                    if (fuse_operand(d.kid[3 * n + last], y) >= 0) {
-                        const bool rev = last == 0 && !is_commutative(o);
-                        f.fv = fused_index(o, rev);
+                    const int kind = fv >= 0 ? fuse_operand(f.kid[1], y, uc) : -1;
+                    if (kind >= 0) {
+                        f.fv = (int8_t)fv;
+                        f.kind = (uint8_t)kind;
+                        f.y = y;
+                        f.operand = f.kid[1];
+                        f.stacked = 1;
                     }
                 }
             }
-            return f;
+            st.push_back(f);
         };
-        st.push_back(frame(root));
+        open(root);
         while (!st.empty()) {
             Frame &top = st.back();
-            const int32_t n = top.n;
-            const bool leafish = arity(n) == 0 || (n != root && cached[n]);
-            const bool warp = op(n) == TGP_WARP;  // stack children t0, t1 only
-            const int stacked = leafish ? 0 : (warp ? 2 : arity(n)) - (top.fv >= 0 ? 1 : 0);
-            if (top.done < stacked) {
-                const int32_t c = warp ? d.kid[3 * n + 1 + top.done] : d.kid[3 * n + kPerms[perm[n]][top.done]];
-                ++top.done;
-                st.push_back(frame(c));
+            if (top.done < top.stacked) {
+                open(top.kid[top.done++]);  // may move the frames
                 continue;
             }
-            uint2 ins{0, 0};
-            uint32_t after = S + 1;
-            if (n != root && cached[n]) {
-                ins.x = I_CACHE;
-                ins.y = (uint32_t)slot[n];
-                ++cache_reads;
-                *valu += 1.0;
-            } else {
-                const int o = op(n);
-                *valu += kOpCost[o];
-                if (o == TGP_VAR) {
-                    const int v = (d.op[n] >> 8) & 0xff;
-                    ins.x = v == 0 ? I_X : (v == 1 ? I_Y : I_Z);
-                    if (v > 1) *ext = true;  // the third axis: extended interpreter only
-                } else if (o == TGP_CONST) {
-                    ins.x = I_CONST;
-                    ins.y = const_word(n);
-                } else if (top.fv >= 0) {
-                    const int32_t c = d.kid[3 * n + kPerms[perm[n]][1]];
-                    const int kind = fuse_operand(c, ins.y);
-                    ins.x = kFuseBase + 16 * (uint32_t)kind + (uint32_t)top.fv;
-                    if (kind == kFuseCache) {
-                        ++cache_reads;
-                        *valu += 1.0;
-                    } else {
-                        *valu += kOpCost[op(c)];
-                    }
-                    after = S;
-                } else if (o == TGP_OR || o == TGP_XOR || o == TGP_AND) {
-                    ins.x = kFnBase + TGP_OR;
-                    ins.y = (uint32_t)(o - TGP_OR);
-                    *ext = true;
-                    after = S - 1;
-                } else if (o == TGP_WARP) {
-                    ins.x = I_WARP;
-                    *ext = *warp_used = true;
-                    ins.y = (uint32_t)slot[d.kid[3 * n]];
-                    ++cache_reads;
-                    after = S - 1;
+            const int32_t n = top.n;
+            const int o = op(n);
+            if (top.fv >= 0) {
+                if (value(top.operand)) {
+                    if (top.kind == kFuseCache && uc == 3) ++reads;
+                    slots += 1.0;
                 } else {
-                    if (perm[n] == 0 || (kArity[o] == 2 && is_commutative(o)))
-                        ins.x = kFnBase + o;
-                    else if (kArity[o] == 2)
-                        ins.x = kRevBase + o;
-                    else
-                        ins.x = kPermBase + 6 * ternary_index(o) + perm[n];
-                    after = S + 1 - (uint32_t)kArity[o];
+                    slots += kOpCost[op(top.operand)];
                 }
+                put(kFuseBase + 16 * (uint32_t)top.kind + (uint32_t)top.fv, top.y);
+            } else if (o == TGP_OR || o == TGP_XOR || o == TGP_AND) {
+                put(kFnBase + TGP_OR, (uint32_t)(o - TGP_OR));
+                *ext = true;
+                --S;
+            } else if (o == TGP_WARP) {
+                put(I_WARP, (uint32_t)slot[node[n].k[0]]);
+                *ext = *warp_used = true;
+                ++reads;
+                --S;
+            } else {
+                const int a = kArity[o];
+                if (perm[n] == 0 || (a == 2 && is_commutative(o))) put(kFnBase + o, 0);
+                else if (a == 2) put(kRevBase + o, 0);
+                else put(kPermBase + 6 * ternary_index(o) + perm[n], 0);
+                S -= (uint32_t)a - 1;
             }
-            ins.x |= S << 8;
-            S = after;
-            code.push_back(ins);
             st.pop_back();
         }
         code.push_back(uint2{(S << 8) | I_END, 0});
+        cache_reads += reads;
+        *valu += slots;
+    }
+};
+
+}  // namespace
+
+// (named in the context, so not in this file's own namespace)
+struct PlanScratch {
+    std::vector<uint8_t> cached, pre, perm, cls, nested;
+    std::vector<int32_t> slot, level, lorder, dep;
+    std::vector<double> cost;
+    std::vector<int64_t> uses;
+    std::vector<Planner::Node> node;
+    std::vector<Planner::Need> need;
+    std::vector<std::vector<uint2>> emitted;
+};
+
+namespace {
+
+void Planner::swap_scratch(PlanScratch &o) {
+    cached.swap(o.cached);
+    pre.swap(o.pre);
+    perm.swap(o.perm);
+    cls.swap(o.cls);
+    nested.swap(o.nested);
+    slot.swap(o.slot);
+    level.swap(o.level);
+    lorder.swap(o.lorder);
+    dep.swap(o.dep);
+    cost.swap(o.cost);
+    uses.swap(o.uses);
+    node.swap(o.node);
+    need.swap(o.need);
+    emitted.swap(o.emitted);
+    lorder.clear();
+}
+
+// Lends a context's arrays to the planner of one plan.
+struct ScratchLoan {
+    Planner &pl;
+    PlanScratch &sc;
+    ScratchLoan(tgp_ctx ctx, Planner &p) : pl(p), sc(get(ctx)) { pl.swap_scratch(sc); }
+    ~ScratchLoan() { pl.swap_scratch(sc); }
+    static PlanScratch &get(tgp_ctx ctx) {
+        if (!ctx->plan_scratch) ctx->plan_scratch = std::make_shared<PlanScratch>();
+        return *ctx->plan_scratch;
     }
 };
 
@@ -1159,31 +1356,42 @@ struct Emitted {
     bool ext, warp;  // uses the bitwise operators or warp
 };
 
-void emit_all(const Planner &pl, const std::vector<int32_t> &nodes, std::vector<uint2> &code,
-              std::vector<Emitted> &out, int threads) {
+void emit_all(Planner &pl, const std::vector<int32_t> &nodes, std::vector<uint2> &code,
+              std::vector<Emitted> &out, int threads, bool ref) {
     const size_t n = nodes.size();
     out.assign(n, Emitted{0, 0, 0, 0.0, false, false});
-    const unsigned hw = usable_cpus();
-    const int T = n < 512 ? 1 : (int)std::min<unsigned>((unsigned)std::max(threads, 1), hw);
-    std::vector<std::vector<uint2>> local(T);
+    // (a thread for every 128 programs; threads of its own only for 512)
+    const int per = pl.team ? 128 : 512;
+    const int T = std::max(1, std::min({(int)(n / per) * (pl.team ? 1 : threads), threads, (int)usable_cpus()}));
+    if (T == 1) {
+        for (size_t i = 0; i < n; ++i) {
+            Emitted &m = out[i];
+            m.off = (uint32_t)code.size();
+            pl.emit(nodes[i], code, m.reads, &m.valu, &m.ext, &m.warp, ref);
+            m.len = (uint32_t)(code.size() - m.off);
+        }
+        return;
+    }
+    std::vector<std::vector<uint2>> &local = pl.emitted;
+    if ((int)local.size() < T) local.resize(T);
     auto work = [&](int t) {
         const size_t b = n * t / T, e = n * (t + 1) / T;
+        local[t].clear();
         for (size_t i = b; i < e; ++i) {
             Emitted &m = out[i];
             m.off = (uint32_t)local[t].size();
-            pl.emit(nodes[i], local[t], m.reads, &m.valu, &m.ext, &m.warp);
+            pl.emit(nodes[i], local[t], m.reads, &m.valu, &m.ext, &m.warp, ref);
             m.len = (uint32_t)(local[t].size() - m.off);
         }
     };
-    std::vector<std::thread> th;
-    for (int t = 1; t < T; ++t) th.emplace_back(work, t);
-    work(0);
-    for (auto &x : th) x.join();
-    for (int t = 0; t < T; ++t) {
-        const uint32_t base = (uint32_t)code.size();
-        code.insert(code.end(), local[t].begin(), local[t].end());
-        for (size_t i = n * t / T; i < n * (t + 1) / T; ++i) out[i].off += base;
-    }
+    run_threads(pl.team, T, work);
+    std::vector<uint32_t> base(T + 1, (uint32_t)code.size());
+    for (int t = 0; t < T; ++t) base[t + 1] = base[t] + (uint32_t)local[t].size();
+    code.resize(base[T]);
+    run_threads(pl.team, T, [&](int t) {
+        std::copy(local[t].begin(), local[t].end(), code.begin() + base[t]);
+        for (size_t i = n * t / T; i < n * (t + 1) / T; ++i) out[i].off += base[t];
+    });
 }
 
 }  // namespace
@@ -1211,6 +1419,7 @@ struct PlanJob {
     std::vector<int32_t> fold_first, fold_list;
     size_t fold_list_at = 0, fold_val_at = 0;
     double t_decide = 0, t_emit = 0;
+    std::vector<uint2> code;  // becomes the plan's code
     // fill-program figures carried from the fill emission to the root one
     int64_t cache_reads_fill = 0;
     double valu_fill = 0;
@@ -1271,10 +1480,10 @@ static void plan_prepare(PlanJob &w, bool fold, int threads = 1) {
         // parallel decisions
         std::vector<int32_t> &order = w.pl.lorder;
         std::vector<int64_t> &first = w.pl.lfirst;
-        height_order(height, U, T, order, first);
+        height_order(w.pl.team, height, U, T, order, first);
         const int32_t H = (int32_t)first.size() - 2;
         std::atomic<int64_t> marked{0};
-        run_team(T, [&](int t, auto &barrier) {
+        run_team(w.pl.team, T, [&](int t, auto &barrier) {
             int64_t m = 0;
             for (int32_t h = 0; h <= H; ++h) {
                 const int64_t n0 = first[h], n1 = first[h + 1];
@@ -1427,21 +1636,67 @@ static tgp_status plan_decide_emit_fill(PlanJob &w, int D, bool reorder, double 
     pl.access_cost = access_cost;
     const unsigned hw = usable_cpus();
     const int dt = (int)std::min<unsigned>((unsigned)std::max(emit_threads, 1), hw);
-    tgp_status st = U >= kParallelDecideNodes && dt > 1 ? pl.decide_parallel(w.rootrefs, w.err, dt)
-                                                        : pl.decide(w.rootrefs, w.err);
+    auto decide = [&]() {
+        return U >= kParallelDecideNodes && dt > 1 ? pl.decide_parallel(w.rootrefs, w.err, dt)
+                                                   : pl.decide(w.rootrefs, w.err);
+    };
+    P.asked = pl.split;
+    tgp_status st = decide();
+    if (st != TGP_OK && pl.tables_over) {  // no room for the tables: flat programs
+        pl.split = 0;
+        pl.tables_over = false;
+        w.err.clear();
+        st = decide();
+    }
     if (st != TGP_OK) return st;
+    P.split = pl.split;
     const double t1 = now_ms();
     w.t_decide = t1 - t0;
 
-    std::vector<uint2> code;
+    std::vector<uint2> &code = w.code;
     std::vector<ProgDesc> fill;
     int32_t max_level = -1;
-    std::vector<int32_t> cached_nodes;
+    std::vector<int32_t> cached_nodes, tab_nodes[2];
+    int32_t max_tab = -1;
     for (int64_t n = 0; n < U; ++n)
         if (pl.cached[n]) {
+            if (pl.in_table(n)) {
+                tab_nodes[pl.cls[n] - 1].push_back((int32_t)n);
+                max_tab = std::max(max_tab, pl.level[n]);
+                continue;
+            }
             cached_nodes.push_back((int32_t)n);
             max_level = std::max(max_level, pl.level[n]);
         }
+    // the tables' programs, by level, row table first
+    P.tab_host.clear();
+    P.tab_level.assign(max_tab + 1, Plan::TabLevel{0, 0, 0});
+    P.exec_tab[0] = P.exec_tab[1] = 0;
+    std::vector<Emitted> em_tab;
+    if (max_tab >= 0) {
+        std::vector<int32_t> nodes(tab_nodes[0]);
+        nodes.insert(nodes.end(), tab_nodes[1].begin(), tab_nodes[1].end());
+        emit_all(pl, nodes, code, em_tab, emit_threads, false);
+        std::vector<std::vector<ProgDesc>> part(2 * (size_t)(max_tab + 1));
+        for (size_t i = 0; i < nodes.size(); ++i) {
+            const int which = i < tab_nodes[0].size() ? 0 : 1;
+            part[2 * (size_t)pl.level[nodes[i]] + which].push_back(
+                ProgDesc{em_tab[i].off, em_tab[i].len, pl.slot[nodes[i]], 0});
+            P.exec_tab[which] += em_tab[i].len - 1;
+        }
+        for (int32_t l = 0; l <= max_tab; ++l) {
+            Plan::TabLevel &t = P.tab_level[l];
+            t.first = (int32_t)P.tab_host.size();
+            for (int which = 0; which < 2; ++which) {
+                auto &v = part[2 * (size_t)l + which];
+                longest_first(v);
+                P.tab_host.insert(P.tab_host.end(), v.begin(), v.end());
+                (which ? t.last : t.mid) = (int32_t)P.tab_host.size();
+            }
+        }
+    }
+    P.tab_code_end = (int64_t)code.size();
+    for (int which = 0; which < 2; ++which) P.n_tab[which] = (int32_t)tab_nodes[which].size();
     P.slot_node.assign(cached_nodes.size(), -1);
     P.slot_pre.assign(cached_nodes.size(), 0);
     for (int32_t n : cached_nodes) {
@@ -1456,7 +1711,7 @@ static tgp_status plan_decide_emit_fill(PlanJob &w, int D, bool reorder, double 
     for (int32_t n : cached_nodes)
         if (!pl.pre[n]) fill_nodes.push_back(n);
     std::vector<Emitted> em;
-    emit_all(pl, fill_nodes, code, em, emit_threads);
+    emit_all(pl, fill_nodes, code, em, emit_threads, false);
     for (size_t i = 0; i < fill_nodes.size(); ++i) {
         const int32_t n = fill_nodes[i];
         ProgDesc pd{em[i].off, em[i].len, pl.slot[n], 0};
@@ -1498,20 +1753,20 @@ static tgp_status plan_decide_emit_fill(PlanJob &w, int D, bool reorder, double 
 static void plan_emit_roots(PlanJob &w, int emit_threads) {
     const double t0 = now_ms();
     Plan &P = w.d->plan;
-    const Planner &pl = w.pl;
+    Planner &pl = w.pl;
     std::vector<uint2> &code = P.code_host;
     std::vector<ProgDesc> reduce, store;
     std::vector<Emitted> em;
     int64_t cache_reads_roots = 0;
     double exec_roots = 0;
-    emit_all(pl, w.store_list, code, em, emit_threads);
-    // program of each distinct root: store_list[i] <-> em[i]
-    std::unordered_map<int32_t, int32_t> prog_of;
-    prog_of.reserve(w.store_list.size() * 2);
-    for (size_t i = 0; i < w.store_list.size(); ++i) prog_of.emplace(w.store_list[i], (int32_t)i);
+    emit_all(pl, w.store_list, code, em, emit_threads, true);
+    // program of each distinct root: store_list[i] <-> em[i], found through
+    // the root's first row
+    std::vector<int32_t> prog_of(w.d->roots.size(), -1);
+    for (size_t i = 0; i < w.store_list.size(); ++i) prog_of[w.store_of[w.store_list[i]]] = (int32_t)i;
     double valu_roots = 0;
     for (size_t p = 0; p < w.reduce_list.size(); ++p) {
-        const Emitted &m = em[prog_of[w.reduce_list[p].first]];
+        const Emitted &m = em[prog_of[w.store_of[w.reduce_list[p].first]]];
         ProgDesc pd{m.off, m.len, (int32_t)p, w.reduce_list[p].second};
         reduce.push_back(pd);
         exec_roots += m.len - 1;
@@ -1593,11 +1848,12 @@ static hipError_t upload_parts(tgp_ctx ctx, int n, const UploadPart *part, void 
 
 // The fill programs: code_host up to root_code_at and the fill descriptors.
 static tgp_status plan_upload_fill(tgp_ctx ctx, Plan &P) {
-    const UploadPart part[2] = {{P.code_host.data(), sizeof(uint2) * (size_t)P.root_code_at, 0},
-                                {P.fill_host.data(), sizeof(ProgDesc) * P.fill_host.size(), 0}};
-    size_t off[2];
+    const UploadPart part[3] = {{P.code_host.data(), sizeof(uint2) * (size_t)P.root_code_at, 0},
+                                {P.fill_host.data(), sizeof(ProgDesc) * P.fill_host.size(), 0},
+                                {P.tab_host.data(), sizeof(ProgDesc) * P.tab_host.size(), 0}};
+    size_t off[3];
     char *b = nullptr;
-    hipError_t e = upload_parts(ctx, 2, part, &P.blob, &b, off);
+    hipError_t e = upload_parts(ctx, 3, part, &P.blob, &b, off);
     if (e != hipSuccess) {
         hipStreamSynchronize(ctx->stream);
         P.release(ctx->pool);
@@ -1605,6 +1861,7 @@ static tgp_status plan_upload_fill(tgp_ctx ctx, Plan &P) {
     }
     P.code_dev = reinterpret_cast<uint2 *>(b + off[0]);
     P.fill_dev = reinterpret_cast<ProgDesc *>(b + off[1]);
+    P.tab_dev = reinterpret_cast<ProgDesc *>(b + off[2]);
     return TGP_OK;
 }
 
@@ -1639,6 +1896,25 @@ static tgp_status plan_upload(tgp_ctx ctx, Plan &P) {
 
 int ctx_stack_slots(tgp_ctx ctx) { return ctx->stack_lds ? interp_lds_stack() : interp_max_stack(); }
 
+// The split that d's programs get on dom under the context's settings: a
+// chosen two cases per lane, the LDS stack, "no caching" (a negative access
+// cost), unfolded constants and the image operators keep flat programs.
+static int32_t wanted_split(tgp_ctx ctx, tgp_dag d, tgp_domain dom) {
+    if (ctx->stack_lds || ctx->force_K == 2 || ctx->cache_access_cost < 0 || !ctx->fold || d->image_ops) return 0;
+    return dom->split;
+}
+
+// Gives the planner of w the split `split` of dom.
+static void set_split(PlanJob &w, tgp_domain dom, int32_t split) {
+    w.pl.split = split;
+    if (!split) return;
+    w.pl.slot_bytes = sizeof(float) * (double)dom->cases;
+    w.pl.table_slots_per[0] = (double)row_table_stride(*dom, split) / w.pl.slot_bytes;
+    w.pl.table_slots_per[1] = (double)col_table_stride(*dom, split) / w.pl.slot_bytes;
+}
+
+// Whether P holds programs for any domain of `cases` cases (a plan with tables
+// runs on any shape).
 static bool plan_current(tgp_ctx ctx, const Plan &P, int64_t cases) {
     return P.cases == cases && P.D == ctx_stack_slots(ctx) && P.reorder == (ctx->reorder != 0) &&
            P.access_cost == ctx->cache_access_cost && P.fold == ctx->fold;
@@ -1648,10 +1924,12 @@ static size_t budget_slots(tgp_ctx ctx, int64_t cases) {
     return (size_t)(ctx->cache_budget / (sizeof(float) * (size_t)std::max<int64_t>(cases, 1)));
 }
 
-tgp_status build_plan(tgp_ctx ctx, tgp_dag d, int64_t cases, const std::function<tgp_status()> &after_fill) {
+tgp_status build_plan(tgp_ctx ctx, tgp_dag d, tgp_domain dom, const std::function<tgp_status()> &after_fill) {
     const double t0 = now_ms();
     Plan &P = d->plan;
-    if (plan_current(ctx, P, cases)) {
+    const int64_t cases = dom->cases;
+    const int32_t split = wanted_split(ctx, d, dom);
+    if (plan_current(ctx, P, cases) && P.asked == split) {
         tgp_status st = ctx->plan_upload && !P.blob ? plan_upload(ctx, P) : TGP_OK;
         ctx->times.plan_ms = now_ms() - t0;
         return st;
@@ -1663,6 +1941,11 @@ tgp_status build_plan(tgp_ctx ctx, tgp_dag d, int64_t cases, const std::function
     P.cases = -1;
     const int D = ctx_stack_slots(ctx);
     PlanJob w(d, cases, D, budget_slots(ctx, cases));
+    set_split(w, dom, split);
+    w.pl.team = &ctx->team;
+    ScratchLoan loan(ctx, w.pl);
+    w.code.swap(ctx->spare_code);
+    w.code.clear();
     plan_prepare(w, ctx->fold != 0, kPlanThreads);
     const double tf0 = now_ms();
     tgp_status st = fold_run(ctx, {&w});
@@ -1688,27 +1971,37 @@ tgp_status build_plan(tgp_ctx ctx, tgp_dag d, int64_t cases, const std::function
     return TGP_OK;
 }
 
-tgp_status build_plans(tgp_ctx ctx, int32_t n, const tgp_dag *dags, const int64_t *cases) {
+tgp_status build_plans(tgp_ctx ctx, int32_t n, const tgp_dag *dags, const tgp_domain *doms) {
     const double t0 = now_ms();
     // one plan per distinct DAG, for the largest domain it is evaluated on
     // (the cache budget in rows is tightest there)
-    std::unordered_map<tgp_dag, int64_t> want;
+    // (split: the domain's, when every domain of the DAG has one shape: the
+    // tables are planned for it)
+    struct Want {
+        tgp_domain dom;
+        int32_t split;
+    };
+    std::unordered_map<tgp_dag, Want> want;
     std::vector<tgp_dag> order;
     for (int32_t i = 0; i < n; ++i) {
+        const int32_t split = wanted_split(ctx, dags[i], doms[i]);
         auto it = want.find(dags[i]);
         if (it == want.end()) {
-            want.emplace(dags[i], cases[i]);
+            want.emplace(dags[i], Want{doms[i], split});
             order.push_back(dags[i]);
         } else {
-            it->second = std::max(it->second, cases[i]);
+            Want &w = it->second;
+            if (split != w.split || memcmp(doms[i]->shape, w.dom->shape, sizeof w.dom->shape) != 0) w.split = 0;
+            if (doms[i]->cases > w.dom->cases) w.dom = doms[i];
         }
     }
     const int D = ctx_stack_slots(ctx);
     std::vector<std::unique_ptr<PlanJob>> jobs;
     bool synced = false;
     for (tgp_dag d : order) {
-        const int64_t c = want[d];
-        if (plan_current(ctx, d->plan, c)) continue;
+        const Want &wd = want[d];
+        const int64_t c = wd.dom->cases;
+        if (plan_current(ctx, d->plan, c) && d->plan.asked == wd.split) continue;
         if (d->plan.blob) {
             if (!synced) HCHK(ctx, hipStreamSynchronize(ctx->stream));
             synced = true;
@@ -1716,6 +2009,7 @@ tgp_status build_plans(tgp_ctx ctx, int32_t n, const tgp_dag *dags, const int64_
         }
         d->plan.cases = -1;
         jobs.emplace_back(new PlanJob(d, c, D, budget_slots(ctx, c)));
+        set_split(*jobs.back(), wd.dom, wd.split);
     }
     if (jobs.empty()) {
         ctx->times.plan_ms = now_ms() - t0;
@@ -1732,10 +2026,7 @@ tgp_status build_plans(tgp_ctx ctx, int32_t n, const tgp_dag *dags, const int64_
         auto run = [&]() {
             for (size_t i; (i = next.fetch_add(1)) < jobs.size();) fn(*jobs[i]);
         };
-        std::vector<std::thread> th;
-        for (int t = 1; t < T; ++t) th.emplace_back(run);
-        run();
-        for (auto &x : th) x.join();
+        run_threads(&ctx->team, T, [&](int) { run(); });
     };
     const bool fold = ctx->fold != 0;
     parallel([&](PlanJob &w) { plan_prepare(w, fold); });
@@ -1749,6 +2040,8 @@ tgp_status build_plans(tgp_ctx ctx, int32_t n, const tgp_dag *dags, const int64_
     const double access = ctx->cache_access_cost;
     const int fold_flag = ctx->fold;
     const int emit_threads = T > 1 ? 1 : 8;
+    if (T == 1)
+        for (auto &w : jobs) w->pl.team = &ctx->team;
     parallel([&](PlanJob &w) {
         w.st = plan_decide_emit(w, D, reorder, access, fold_flag, emit_threads);
         if (w.st != TGP_OK) w.d->plan.cases = -1;
@@ -1785,9 +2078,10 @@ void choose_split(tgp_ctx ctx, int64_t n_progs, int64_t cases, int K, int32_t *s
     *stripes = (int32_t)((n_tiles + tps - 1) / tps);
 }
 
-int choose_K(tgp_ctx ctx, int64_t cases, bool ext) {
+int choose_K(tgp_ctx ctx, int64_t cases, const Plan &P) {
+    if (P.split) return kTableK;
     if (ctx->stack_lds) return 2;  // the LDS-stack interpreter
-    if (ext) return 4;  // the register-stack interpreter built with the bitwise operators and warp
+    if (P.ext) return 4;  // the register-stack interpreter built with the bitwise operators and warp
     if (ctx->force_K) return ctx->force_K;
     return cases >= 64 * 4 * 4 ? 4 : 2;
 }
@@ -1812,41 +2106,111 @@ void fill_job(JobDesc &j, tgp_domain dom, const uint2 *code, const float *cache)
     }
 }
 
+void fill_table_fields(JobDesc &j, const Plan &P, tgp_domain dom, float *tables) {
+    if (!P.split) return;
+    j.row_tab = tables;
+    j.col_tab = tables + P.row_bytes(*dom) / sizeof(float);
+    j.row_bytes = (uint32_t)row_table_stride(*dom, P.split);
+    j.col_bytes = (uint32_t)col_table_stride(*dom, P.split);
+    j.n_cols = (uint32_t)dom->cols(P.split);
+    div_magic(j.n_cols, &j.col_m, &j.col_s);
+}
+
+void fill_table_job(JobDesc &j, const Plan &P, tgp_domain dom, const uint2 *code, float *tables, int which) {
+    memset(&j, 0, sizeof j);
+    j.code = code;
+    // the axes of this side of the split (none: one entry that no program uses)
+    const int k0 = which ? std::min<int>(P.split, dom->ndim) : 0;
+    const int k1 = which ? dom->ndim : std::min<int>(P.split, dom->ndim);
+    int64_t st = 1;
+    j.ndim = std::max(1, k1 - k0);
+    for (int k = 0; k < 3; ++k) {
+        j.shape[k] = j.stride[k] = 1;
+        j.coord[k] = dom->coord[0];
+    }
+    for (int k = k1 - 1; k >= k0; --k) {
+        j.shape[k - k0] = (int32_t)dom->shape[k];
+        j.stride[k - k0] = (int32_t)st;
+        j.coord[k - k0] = dom->coord[k];
+        st *= dom->shape[k];
+    }
+    j.n_cases = (int32_t)st;
+    for (int k = 0; k < 2; ++k) div_magic((uint32_t)j.stride[k], &j.div_m[k], &j.div_s[k]);
+    float *tab = which ? tables + P.row_bytes(*dom) / sizeof(float) : tables;
+    j.cache = tab;  // lower levels' entries
+    j.out = tab;
+    j.cache_stride = j.out_stride =
+        (int64_t)((which ? col_table_stride(*dom, P.split) : row_table_stride(*dom, P.split)) / sizeof(float));
+}
+
 static void fill_args(InterpArgs &a, tgp_domain dom, const uint2 *code, const float *cache) {
     memset(&a, 0, sizeof a);
     fill_job(a.job, dom, code, cache);
 }
 
 // The cache-fill launches of d's plan, writing its cache rows to `cache`.
-static tgp_status fill_into(tgp_ctx ctx, tgp_dag d, tgp_domain dom, int K, float *cache) {
+static tgp_status fill_into(tgp_ctx ctx, tgp_dag d, tgp_domain dom, int K, float *cache, float *tables) {
     const Plan &P = d->plan;
     record(ctx, 0);
     ctx->fill_recorded = ctx->timing;
-    for (size_t l = 0; l + 1 < P.level_first.size(); ++l) {
+    for (size_t l = 0; l < (size_t)P.levels(); ++l) {
+        if (l < P.tab_level.size()) {
+            const Plan::TabLevel &t = P.tab_level[l];
+            TableArgs ta;
+            int64_t entries = 0;
+            for (int which = 0; which < 2; ++which) {
+                JobDesc &j = ta.job[which];
+                fill_table_job(j, P, dom, P.code_dev, tables, which);
+                ta.n_progs[which] = which ? t.last - t.mid : t.mid - t.first;
+                entries = std::max<int64_t>(entries, j.n_cases);
+            }
+            const int tk = entries >= 64 * 4 ? 4 : 2;
+            for (int which = 0; which < 2; ++which) {
+                JobDesc &j = ta.job[which];
+                choose_split(ctx, ta.n_progs[which], j.n_cases, tk, &j.n_stripes, &j.tiles_per_stripe);
+            }
+            ta.progs = P.tab_dev + t.first;
+            HCHK(ctx, launch_tables(tk, ta, ctx->stream));
+        }
+        if (l + 1 >= P.level_first.size()) continue;
         const int32_t b = P.level_first[l], e = P.level_first[l + 1];
         if (e == b) continue;
         InterpArgs a;
         fill_args(a, dom, P.code_dev, cache);
+        fill_table_fields(a.job, P, dom, tables);
         a.progs = P.fill_dev + b;
         a.n_progs = e - b;
         choose_split(ctx, a.n_progs, dom->cases, K, &a.job.n_stripes, &a.job.tiles_per_stripe);
         a.job.out = cache;
-        HCHK(ctx, launch_interp(K, P.D, true, a, ctx->stream, P.ext));
+        HCHK(ctx, launch_interp(K, P.D, true, a, ctx->stream, form_of(P, *dom)));
     }
     record(ctx, 1);
     return TGP_OK;
 }
 
 static tgp_status run_fill(tgp_ctx ctx, tgp_dag d, tgp_domain dom, int K, float **cache_out) {
-    const Plan &P = d->plan;
+    Plan &P = d->plan;
     *cache_out = nullptr;
     ctx->fill_recorded = false;
-    if (P.n_slots == 0) return TGP_OK;
+    if (P.n_slots == 0 && P.tab_host.empty()) return TGP_OK;
     const size_t bytes = sizeof(float) * (size_t)P.n_slots * (size_t)dom->cases;
-    HCHK(ctx, ensure(ctx->cache, bytes));
-    float *cache = (float *)ctx->cache.p;
+    if (P.n_slots) HCHK(ctx, ensure(ctx->cache, bytes));
+    // The tables belong to the plan: their addresses stay the same for its
+    // life (tgp_fitness_noalloc uses them too, perhaps inside a HIP graph).
+    const size_t tab = P.tables_bytes(*dom);
+    if (tab > P.tables_cap) {
+        if (P.tables) {
+            HCHK(ctx, hipStreamSynchronize(ctx->stream));
+            ctx->pool.release(P.tables);
+            P.tables = nullptr;
+            P.tables_cap = 0;
+        }
+        HCHK(ctx, ctx->pool.alloc(&P.tables, tab));
+        P.tables_cap = tab;
+    }
+    float *cache = P.n_slots ? (float *)ctx->cache.p : nullptr;
     *cache_out = cache;
-    return fill_into(ctx, d, dom, K, cache);
+    return fill_into(ctx, d, dom, K, cache, (float *)P.tables);
 }
 
 // The plan of d for dom with its cache filled (fill launches queued on the
@@ -1856,12 +2220,12 @@ static tgp_status run_fill(tgp_ctx ctx, tgp_dag d, tgp_domain dom, int K, float 
 // need the bitwise operators or warp when the root programs do).
 static tgp_status plan_and_fill(tgp_ctx ctx, tgp_dag d, tgp_domain dom, float **cache) {
     bool filled = false;
-    tgp_status st = build_plan(ctx, d, dom->cases, [&]() {
+    tgp_status st = build_plan(ctx, d, dom, [&]() {
         filled = true;
-        return run_fill(ctx, d, dom, choose_K(ctx, dom->cases, d->plan.ext), cache);
+        return run_fill(ctx, d, dom, choose_K(ctx, dom->cases, d->plan), cache);
     });
     if (st != TGP_OK || filled) return st;
-    return run_fill(ctx, d, dom, choose_K(ctx, dom->cases, d->plan.ext), cache);
+    return run_fill(ctx, d, dom, choose_K(ctx, dom->cases, d->plan), cache);
 }
 
 tgp_status check_eval_args(tgp_ctx ctx, tgp_dag d, tgp_domain dom) {
@@ -1878,16 +2242,18 @@ static void record_work(tgp_ctx ctx, tgp_dag d, tgp_domain dom, bool fitness) {
     tgp_work_stats &w = ctx->work;
     const double cases = (double)dom->cases;
     w.credited_node_evals = d->stats.dag_nodes * dom->cases;
-    w.executed_node_evals = (int64_t)(P.exec_per_case * cases);
-    w.cached_nodes = P.n_slots;
+    const double rows = P.split ? (double)dom->rows(P.split) : 0, cols = P.split ? (double)dom->cols(P.split) : 0;
+    const int64_t tab_cells = (int64_t)(P.n_tab[0] * rows + P.n_tab[1] * cols);
+    w.executed_node_evals = (int64_t)(P.exec_per_case * cases + P.exec_tab[0] * rows + P.exec_tab[1] * cols);
+    w.cached_nodes = P.n_slots + P.n_tab[0] + P.n_tab[1];
     w.stack_spills = P.n_spills;
-    w.cache_levels = (int64_t)P.level_first.size() - 1;
+    w.cache_levels = P.levels();
     w.programs = fitness ? P.n_reduce : P.n_store;
     w.instructions = P.instructions;
     w.algorithmic_valu = P.valu_dag_per_case * cases;
     w.executed_valu_fill = P.valu_fill_per_case * cases;
     w.executed_valu_roots = P.valu_roots_per_case * cases;
-    w.cache_bytes_written = (int64_t)P.n_slots * dom->cases * 4;
+    w.cache_bytes_written = ((int64_t)P.n_slots * dom->cases + tab_cells) * 4;
     w.cache_bytes_read = P.cache_reads_per_case * dom->cases * 4;
     w.folded_nodes = P.n_folded;
 }
@@ -1922,9 +2288,10 @@ tgp_status tgp_fitness(tgp_ctx ctx, tgp_dag d, tgp_domain dom, const float *targ
     st = plan_and_fill(ctx, d, dom, &cache);
     if (st != TGP_OK) return st;
     const Plan &P = d->plan;
-    const int K = choose_K(ctx, dom->cases, P.ext);
+    const int K = choose_K(ctx, dom->cases, P);
     InterpArgs a;
     fill_args(a, dom, P.code_roots_dev, cache);
+    fill_table_fields(a.job, P, dom, (float *)P.tables);
     a.progs = P.reduce_dev;
     a.n_progs = P.n_reduce;
     choose_split(ctx, a.n_progs, dom->cases, K, &a.job.n_stripes, &a.job.tiles_per_stripe);
@@ -1932,7 +2299,7 @@ tgp_status tgp_fitness(tgp_ctx ctx, tgp_dag d, tgp_domain dom, const float *targ
     HCHK(ctx, ensure(ctx->partial, sizeof(float2) * (size_t)a.n_progs * (size_t)a.job.n_stripes));
     a.job.partial = (float2 *)ctx->partial.p;
     record(ctx, 2);
-    HCHK(ctx, launch_interp(K, P.D, false, a, ctx->stream, P.ext));
+    HCHK(ctx, launch_interp(K, P.D, false, a, ctx->stream, form_of(P, *dom)));
     record(ctx, 3);
     record(ctx, 4);
     HCHK(ctx, launch_finalize(a.job.partial, P.ind_rows_dev, d->n_ind, d->n_ch, a.job.n_stripes,
@@ -1968,7 +2335,7 @@ tgp_status tgp_fitness_noalloc(tgp_ctx ctx, tgp_dag d, tgp_domain dom, const flo
         return fail(ctx, TGP_EINVAL,
                     "the DAG has no plan for a domain of %lld cases under this context's settings "
                     "(evaluate it once with tgp_fitness or tgp_evaluate)", (long long)dom->cases);
-    const int K = choose_K(ctx, dom->cases, P.ext);
+    const int K = choose_K(ctx, dom->cases, P);
     InterpArgs a;
     fill_args(a, dom, P.code_roots_dev, nullptr);
     a.progs = P.reduce_dev;
@@ -1977,6 +2344,17 @@ tgp_status tgp_fitness_noalloc(tgp_ctx ctx, tgp_dag d, tgp_domain dom, const flo
     const size_t partial_bytes =
         (sizeof(float2) * (size_t)a.n_progs * (size_t)a.job.n_stripes + 255) & ~(size_t)255;
     const size_t cache_bytes = sizeof(float) * (size_t)P.n_slots * (size_t)dom->cases;
+    // The plan's tables were allocated with it; a domain of the same size but
+    // another shape may need larger ones, which then go into the scratch.
+    const size_t table_bytes = P.tables_bytes(*dom);
+    const bool own_tables = table_bytes <= P.tables_cap;
+    const size_t tables_at = (partial_bytes + cache_bytes + 255) & ~(size_t)255;
+    if (P.split && std::max(P.row_bytes(*dom), table_bytes - P.row_bytes(*dom)) >= 0xffffff00u)
+        return fail(ctx, TGP_ENOMEM, "the tables of this domain's shape exceed 4 GiB");
+    if (!own_tables && tables_at + table_bytes > kNoAllocScratchBytes)
+        return fail(ctx, TGP_ENOMEM,
+                    "needs %zu bytes of scratch (%zu of tables for this domain's shape); "
+                    "tgp_fitness_noalloc has %zu", tables_at + table_bytes, table_bytes, kNoAllocScratchBytes);
     if (partial_bytes + cache_bytes > kNoAllocScratchBytes)
         return fail(ctx, TGP_ENOMEM,
                     "needs %zu bytes of scratch (%zu of partial sums, %zu of cache rows); "
@@ -1986,16 +2364,18 @@ tgp_status tgp_fitness_noalloc(tgp_ctx ctx, tgp_dag d, tgp_domain dom, const flo
     // is read, so nothing in the scratch needs clearing between calls.
     char *base = static_cast<char *>(g_scratch_ptr[ctx->device]);
     float *cache = P.n_slots ? reinterpret_cast<float *>(base + partial_bytes) : nullptr;
+    float *tables = own_tables ? (float *)P.tables : reinterpret_cast<float *>(base + tables_at);
     ctx->fill_recorded = false;
-    if (P.n_slots) {
-        st = fill_into(ctx, d, dom, K, cache);
+    if (P.n_slots || !P.tab_host.empty()) {
+        st = fill_into(ctx, d, dom, K, cache, tables);
         if (st != TGP_OK) return st;
     }
+    fill_table_fields(a.job, P, dom, tables);
     a.job.cache = cache;
     a.job.target = target_dev;
     a.job.partial = reinterpret_cast<float2 *>(base);
     record(ctx, 2);
-    HCHK(ctx, launch_interp(K, P.D, false, a, ctx->stream, P.ext));
+    HCHK(ctx, launch_interp(K, P.D, false, a, ctx->stream, form_of(P, *dom)));
     record(ctx, 3);
     record(ctx, 4);
     HCHK(ctx, launch_finalize(a.job.partial, P.ind_rows_dev, d->n_ind, d->n_ch, a.job.n_stripes,
@@ -2018,15 +2398,16 @@ tgp_status tgp_evaluate(tgp_ctx ctx, tgp_dag d, tgp_domain dom, float *out_dev) 
     st = plan_and_fill(ctx, d, dom, &cache);
     if (st != TGP_OK) return st;
     const Plan &P = d->plan;
-    const int K = choose_K(ctx, dom->cases, P.ext);
+    const int K = choose_K(ctx, dom->cases, P);
     InterpArgs a;
     fill_args(a, dom, P.code_roots_dev, cache);
+    fill_table_fields(a.job, P, dom, (float *)P.tables);
     a.progs = P.store_dev;
     a.n_progs = P.n_store;
     choose_split(ctx, a.n_progs, dom->cases, K, &a.job.n_stripes, &a.job.tiles_per_stripe);
     a.job.out = out_dev;
     record(ctx, 2);
-    HCHK(ctx, launch_interp(K, P.D, true, a, ctx->stream, P.ext));
+    HCHK(ctx, launch_interp(K, P.D, true, a, ctx->stream, form_of(P, *dom)));
     record(ctx, 3);
     record(ctx, 4);
     record(ctx, 5);

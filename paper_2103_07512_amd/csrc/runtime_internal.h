@@ -4,9 +4,15 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <atomic>
 #include <chrono>
+#include <condition_variable>
 #include <functional>
+#include <memory>
+#include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "tgp_internal.h"
@@ -19,7 +25,55 @@ struct DevBuf {
     size_t cap = 0;
 };
 
+// Host threads that a context keeps for planning (creating them for every
+// phase of every plan costs more than most phases): at most kMaxWorkers, made
+// on first use and joined when the context is destroyed.  Used by the
+// context's one host thread at a time.
+class HostTeam {
+public:
+    ~HostTeam();
+    // Runs fn(t) for t = 0 .. T-1, t = 0 on the calling thread, and returns
+    // when all have returned.
+    void run(int T, const std::function<void(int)> &fn);
+
+private:
+    static constexpr int kMaxWorkers = 15;
+    void work(int id, uint64_t seen);
+    std::vector<std::thread> workers_;
+    std::mutex m_;
+    std::condition_variable cv_;
+    std::atomic<uint64_t> round_{0};
+    std::atomic<int> left_{0};
+    int want_ = 0;
+    const std::function<void(int)> *fn_ = nullptr;
+    bool stop_ = false;
+};
+
+// Host arrays that a context keeps from one DAG and plan to the next (their
+// pages would otherwise be mapped and cleared anew every generation): one
+// set, of the largest DAG seen, given back with the context.
+struct DagArrays {
+    std::vector<int32_t> op;  // op | var << 8
+    std::vector<float> value;
+    std::vector<int32_t> kid;  // [U][3]
+    std::vector<int32_t> roots, mult, indeg, height;
+    void swap(DagArrays &o) {
+        op.swap(o.op);
+        value.swap(o.value);
+        kid.swap(o.kid);
+        roots.swap(o.roots);
+        mult.swap(o.mult);
+        indeg.swap(o.indeg);
+        height.swap(o.height);
+    }
+};
+struct PlanScratch;  // the planner's arrays (runtime.cpp)
+
 struct tgp_ctx_s {
+    HostTeam team;
+    DagArrays spare_dag;
+    std::vector<uint2> spare_code;
+    std::shared_ptr<PlanScratch> plan_scratch;
     int device = 0;
     hipStream_t stream = nullptr;
     size_t cache_budget = 0;
@@ -73,7 +127,26 @@ struct tgp_domain_s {
     int64_t cases = 0;
     double lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};
     float *coord[3] = {nullptr, nullptr, nullptr};
+    // The split of the axes for table programs (0: the domain is evaluated
+    // flat): axes below it number the grid rows, the others the columns.
+    int32_t split = 0;
+    // Entries of the tables of a program split at axis s.  Any s of 1..2 has
+    // a meaning on any domain (without axes on one side it has one entry).
+    int64_t rows(int s) const {
+        int64_t n = 1;
+        for (int k = 0; k < s && k < ndim; ++k) n *= shape[k];
+        return n;
+    }
+    int64_t cols(int s) const { return cases / rows(s); }
 };
+
+// Byte strides of the tables' subtrees on a domain split at axis s.
+inline size_t row_table_stride(const tgp_domain_s &d, int s) {
+    return sizeof(float) * (size_t)((d.rows(s) + 15) / 16 * 16);
+}
+inline size_t col_table_stride(const tgp_domain_s &d, int s) {
+    return sizeof(float) * (size_t)((d.cols(s) + 15) / 16 * 16);
+}
 
 // A compiled evaluation plan of one DAG for one case count.
 struct Plan {
@@ -83,6 +156,30 @@ struct Plan {
     double access_cost = 0;
     int fold = -1;
     int64_t n_folded = 0;               // constant subtrees folded
+    // Table programs (split > 0): subtrees of the leading axes alone live in the
+    // row table, of the trailing axes alone in the column table, the cache
+    // slots hold the others.  asked: the split the plan was made for (a plan
+    // whose tables did not fit falls back to flat programs, split = 0).
+    int32_t split = 0, asked = 0;
+    int32_t n_tab[2] = {0, 0};          // subtrees in the row and column tables
+    struct TabLevel {
+        int32_t first, mid, last;       // row programs [first, mid), column programs [mid, last)
+    };
+    std::vector<TabLevel> tab_level;    // table programs of each level
+    std::vector<ProgDesc> tab_host;
+    ProgDesc *tab_dev = nullptr;
+    int64_t tab_code_end = 0;           // the table programs' code comes first in code_host
+    double exec_tab[2] = {0, 0};        // instructions run per table entry
+    void *tables = nullptr;             // the plain path's tables (pool block of tables_cap bytes)
+    size_t tables_cap = 0;
+    int levels() const { return (int)std::max(level_first.empty() ? 0 : level_first.size() - 1, tab_level.size()); }
+    size_t tables_bytes(const tgp_domain_s &d) const {
+        if (!split) return 0;
+        return row_bytes(d) + (size_t)n_tab[1] * col_table_stride(d, split);
+    }
+    size_t row_bytes(const tgp_domain_s &d) const {
+        return ((size_t)n_tab[0] * row_table_stride(d, split) + 255) & ~(size_t)255;
+    }
     int32_t n_slots = 0;
     int64_t n_spills = 0;               // cached only to bound the register stack
     std::vector<int32_t> level_first;   // fill programs of level l: [level_first[l], level_first[l+1])
@@ -120,7 +217,10 @@ struct Plan {
     void release(DevicePool &pool) {
         pool.release(blob);
         pool.release(blob_roots);
-        blob = blob_roots = nullptr;
+        pool.release(tables);
+        blob = blob_roots = tables = nullptr;
+        tables_cap = 0;
+        tab_dev = nullptr;
         code_dev = code_roots_dev = nullptr;
         fill_dev = reduce_dev = store_dev = nullptr;
         ind_rows_dev = nullptr;
@@ -128,16 +228,12 @@ struct Plan {
     }
 };
 
-struct tgp_dag_s {
+struct tgp_dag_s : DagArrays {  // host copies
     tgp_ctx ctx = nullptr;
     int32_t n_ind = 0, n_ch = 0;
     tgp_dag_stats stats{};
     DagDevice dev;
-    // host copies
-    std::vector<int32_t> op;   // op | var << 8
-    std::vector<float> value;
-    std::vector<int32_t> kid;  // [U][3]
-    std::vector<int32_t> roots, mult, indeg, height;
+    bool image_ops = false;          // a bitwise operator or warp occurs
     std::vector<uint8_t> precached;  // nodes whose values are resident (empty: none)
     Plan plan;
 };
@@ -195,25 +291,38 @@ struct StepJob {
     // uploads the plan's host copies).
     const uint2 *code_dev = nullptr;
     const int32_t *rows_dev = nullptr;
+    // Table programs: the request's tables (nullptr: the step allocates them) and
+    // whether this step fills them.
+    float *tables = nullptr;
+    bool fill_tables = true;
 };
 tgp_status batch_step(tgp_batch b, int32_t n_jobs, const StepJob *jobs, int64_t credited);
 
 // --------------------------------------------------------------- shared helpers
 extern const double kOpCost[TGP_NUM_OPS];
-// Plans d for domains of `cases` cases (a no-op when its plan is current) and
+// Plans d for domains like dom (a no-op when its plan is current) and
 // uploads the programs when the context keeps plans on the device.  When a
 // new plan is uploaded, after_fill (if given) is called once the fill
 // programs are on the device and before the root programs are emitted, so
 // that the caller can queue the cache fill while the host emits the rest.
-tgp_status build_plan(tgp_ctx ctx, tgp_dag d, int64_t cases,
+tgp_status build_plan(tgp_ctx ctx, tgp_dag d, tgp_domain dom,
                       const std::function<tgp_status()> &after_fill = nullptr);
 // Plans many DAGs at once (host threads, one device round trip for constant
 // folding); programs stay on the host.  A DAG listed more than once is
 // planned once, for its largest domain.
-tgp_status build_plans(tgp_ctx ctx, int32_t n, const tgp_dag *dags, const int64_t *cases);
-int choose_K(tgp_ctx ctx, int64_t cases, bool ext);
+tgp_status build_plans(tgp_ctx ctx, int32_t n, const tgp_dag *dags, const tgp_domain *doms);
+// Cases per lane of a plan's launches over `cases` cases, and their form.
+int choose_K(tgp_ctx ctx, int64_t cases, const Plan &P);
+inline int form_of(const Plan &P, const tgp_domain_s &d) {
+    if (P.split) return d.cols(P.split) % kWideCols == 0 ? kWide : kRagged;
+    return P.ext ? kExt : kFlat;
+}
 int ctx_stack_slots(tgp_ctx ctx);
 void choose_split(tgp_ctx ctx, int64_t n_progs, int64_t cases, int K, int32_t *stripes,
                   int32_t *tiles_per);
 void fill_job(JobDesc &j, tgp_domain dom, const uint2 *code, const float *cache);
+// The table fields of j for P's split, the tables at `tables`.
+void fill_table_fields(JobDesc &j, const Plan &P, tgp_domain dom, float *tables);
+// The flat job that fills the row (which = 0) or column (1) table of P.
+void fill_table_job(JobDesc &j, const Plan &P, tgp_domain dom, const uint2 *code, float *tables, int which);
 tgp_status check_eval_args(tgp_ctx ctx, tgp_dag d, tgp_domain dom);

@@ -108,6 +108,7 @@ struct Req {
     uint2 *code_dev = nullptr;
     int32_t *rows_dev = nullptr;
     double *acc = nullptr, *out_dev = nullptr;
+    float *tables = nullptr;  // table programs: filled by the first slab's step
     // outcome
     int status = TGP_EBUSY;
     bool finished = false;
@@ -241,7 +242,7 @@ void prepare(tgp_server s, tgp_ctx pc, const ReqP &rp) {
         for (CacheEntry *e : hit)
             if (e) s->cache->unpin(e, false);
     };
-    st = build_plan(pc, d, r.dom->cases);
+    st = build_plan(pc, d, r.dom);
     if (st != TGP_OK) {
         unpin_hits();
         end_request(s, r, st, std::string("plan: ") + tgp_last_error(pc));
@@ -314,8 +315,11 @@ void prepare(tgp_server s, tgp_ctx pc, const ReqP &rp) {
     }
     // Programs with slots mapped to arena rows (in arena units).
     r.plan = P;
-    for (uint2 &ins : r.plan.code_host)
+    // (the tables' programs, first in the code, name table entries instead)
+    for (size_t i = (size_t)P.tab_code_end; i < r.plan.code_host.size(); ++i) {
+        uint2 &ins = r.plan.code_host[i];
         if (reads_cache_row(ins.x)) ins.y = (uint32_t)r.entry[ins.y]->off;
+    }
     for (ProgDesc &pd : r.plan.fill_host) pd.dest = (int32_t)r.entry[pd.dest]->off;
     // Slabs and work split, from this request alone.
     const int64_t cases = r.dom->cases;
@@ -375,6 +379,8 @@ void release_exec(tgp_server s, Req &r) {
     p.release(r.rows_dev);
     p.release(r.acc);
     p.release(r.out_dev);
+    p.release(r.tables);
+    r.tables = nullptr;
     r.code_dev = nullptr;
     r.rows_dev = nullptr;
     r.acc = r.out_dev = nullptr;
@@ -437,6 +443,8 @@ void exec_loop(tgp_server s) {
             hipError_t e = pool_upload(s, &r->code_dev, r->plan.code_host);
             if (e == hipSuccess) e = pool_upload(s, &r->rows_dev, r->plan.ind_rows_host);
             if (e == hipSuccess) e = s->exec->pool.alloc((void **)&r->out_dev, sizeof(double) * r->n_ind);
+            const size_t tab = r->plan.tables_bytes(*r->dom);
+            if (e == hipSuccess && tab) e = s->exec->pool.alloc((void **)&r->tables, tab);
             if (e == hipSuccess && r->n_slabs > 1)
                 e = s->exec->pool.alloc((void **)&r->acc, sizeof(double) * r->n_ind);
             if (e != hipSuccess) {
@@ -477,6 +485,8 @@ void exec_loop(tgp_server s) {
                 j.tiles_per_item = r->tps;
                 j.code_dev = r->code_dev;
                 j.rows_dev = r->rows_dev;
+                j.tables = r->tables;
+                j.fill_tables = k == 0;
                 jobs.push_back(j);
                 f.items.push_back({r, k == r->n_slabs - 1});
                 credited += r->dag_nodes * (int64_t)j.n_cases;
@@ -606,7 +616,8 @@ tgp_status tgp_server_create(tgp_ctx ctx, size_t cache_budget_bytes, int32_t max
     // per lane (the split, and so the summation order, of a request must not
     // depend on its neighbours).
     s->K = 4;
-    s->exec->force_K = 4;
+    static_assert(kTableK == 4 && kSlabQuantum % kWideCols == 0, "one case split for every form; slabs of whole tiles");
+    for (tgp_ctx c : all) c->force_K = 4;
     s->stats.bytes_capacity = (int64_t)budget;
     tgp_server raw = s.release();
     for (int i = 0; i < kPrepThreads; ++i) raw->prep_thr[i] = std::thread(prep_loop, raw, i);

@@ -64,6 +64,8 @@ __host__ __device__ constexpr int arity_of(uint32_t op) { return (int)((kArityPa
 // v the index of (operator, reversed) in kFuseOps / kFuseRev; reversed
 // means the terminal is the operator's first operand.  A fused form at depth
 // S reads slot S - 1 and writes it.
+// In a wide or ragged program (JobDesc, below) I_X / kFuseX read row .y of the grid-row
+// table and I_Y / kFuseY row .y of the column table instead of a coordinate.
 enum : uint32_t {
     I_X = 0, I_Y = 1, I_Z = 2, I_CONST = 3, I_CACHE = 4, I_END = 5,
     I_WARP = 6,  // pops t0, t1; pushes cache row .y at the point they name
@@ -80,12 +82,17 @@ constexpr bool kFuseRev[kNumFused] = {false, false, false, false, false, false, 
                                       false, false, false, true,  true,  true,  true};
 
 // Index v of (op, reversed) in kFuseOps / kFuseRev, or -1 if it has no
-// fused form.
-inline int fused_index(int op, bool rev) {
-    for (int v = 0; v < kNumFused; ++v)
-        if (kFuseOps[v] == op && kFuseRev[v] == rev) return v;
-    return -1;
-}
+// fused form (a table: the planner asks for every binary node).
+struct FusedTable {
+    int8_t v[2][TGP_NUM_OPS];
+    constexpr FusedTable() : v() {
+        for (int r = 0; r < 2; ++r)
+            for (int o = 0; o < TGP_NUM_OPS; ++o) v[r][o] = -1;
+        for (int i = 0; i < kNumFused; ++i) v[kFuseRev[i] ? 1 : 0][kFuseOps[i]] = (int8_t)i;
+    }
+};
+constexpr FusedTable kFusedTable;
+inline int fused_index(int op, bool rev) { return kFusedTable.v[rev ? 1 : 0][op]; }
 // The code of an instruction word.
 __host__ __device__ constexpr uint32_t ins_code(uint32_t x) { return x & 0xffu; }
 // Whether the instruction's .y names a cache row.
@@ -94,12 +101,28 @@ inline bool reads_cache_row(uint32_t x) {
     return c == I_CACHE || c == I_WARP || (c >= kFuseBase + 16 * kFuseCache && c < kFuseBase + 16 * (kFuseCache + 1));
 }
 
-constexpr uint8_t kPerms[6][3] = {{0, 1, 2}, {0, 2, 1}, {1, 0, 2}, {1, 2, 0}, {2, 0, 1}, {2, 1, 0}};
-
-inline bool is_commutative(int op) {
+// Per opcode: the index of the fused form whose terminal is the last of the
+// children in order (forward) or the first (backward), or -1.
+constexpr bool op_commutes(int op) {
     return op == TGP_ADD || op == TGP_MULT || op == TGP_MIN || op == TGP_MAX || op == TGP_MDIST ||
            op == TGP_LEN || op == TGP_OR || op == TGP_XOR || op == TGP_AND;
 }
+struct OpForms {
+    int8_t forward[TGP_NUM_OPS], backward[TGP_NUM_OPS];
+    bool commutes[TGP_NUM_OPS];
+    constexpr OpForms() : forward(), backward(), commutes() {
+        for (int o = 0; o < TGP_NUM_OPS; ++o) {
+            commutes[o] = op_commutes(o);
+            forward[o] = kFusedTable.v[0][o];
+            backward[o] = kFusedTable.v[commutes[o] ? 0 : 1][o];
+        }
+    }
+};
+constexpr OpForms kOpForms;
+
+constexpr uint8_t kPerms[6][3] = {{0, 1, 2}, {0, 2, 1}, {1, 0, 2}, {1, 2, 0}, {2, 0, 1}, {2, 1, 0}};
+
+inline bool is_commutative(int op) { return kOpForms.commutes[op]; }
 inline int ternary_index(int op) {
     return op == TGP_CLIP ? 0 : (op == TGP_IF ? 1 : (op == TGP_LERP ? 2 : -1));
 }
@@ -116,6 +139,18 @@ struct ProgDesc {
 
 // Everything a work item needs to know about the domain and the buffers of
 // the evaluation it belongs to.
+//
+// Wide and ragged jobs.  The leading axes of the grid number its rows, the
+// trailing axes its columns (one row = n_cols consecutive cases).  A subtree
+// that depends only on the leading axes has one value per grid row, one that
+// depends only on the trailing axes one value per column, and neither is
+// computed per case: their values are filled once per evaluation into two
+// tables (subtree s at row_tab + s * row_bytes, one float per grid row; at
+// col_tab + s * col_bytes, one per column), by flat jobs over the leading and
+// the trailing axes alone.  Tiles are the flat form's 64*K consecutive cases,
+// so every case is summed in the same order in every form.  Wide jobs have
+// tiles that lie inside one grid row (n_cols, and so n_cases and case_base,
+// multiples of kWideCols).
 // A job covers the n_cases consecutive cases of the domain that start at
 // case case_base (all of it, or one slab of it); every per-case array below
 // is indexed by the global case index case_base + i.
@@ -136,7 +171,17 @@ struct JobDesc {
     float2 *partial;             // REDUCE: [dest][n_stripes] (sum, compensation)
     int64_t cache_stride, out_stride, target_stride;
     float warp_lo[2], warp_scale[2]; // warp: axis k position of t is (t - lo) * scale
+    // wide and ragged jobs only
+    const float *row_tab, *col_tab;
+    uint32_t row_bytes, col_bytes;   // byte strides of the tables' subtrees (each table < 4 GiB)
+    uint32_t n_cols, col_m, col_s;   // columns, and multiply-shift division by them
 };
+
+// Interpreter forms: flat (coordinates in registers), flat with the bitwise
+// operators, warp and the third axis, and the two that read tables.
+enum { kFlat = 0, kExt = 1, kWide = 2, kRagged = 3 };
+constexpr int kTableK = 4;           // cases per lane of the wide and ragged forms
+constexpr int kWideCols = 64 * kTableK;
 
 // Launch arguments of the plain (one program set, one domain) interpreter:
 // work item i is program i / n_stripes, stripe i % n_stripes.
@@ -144,6 +189,14 @@ struct InterpArgs {
     JobDesc job;
     const ProgDesc *progs;
     int32_t n_progs;
+};
+
+// Launch arguments of one level of table fills: the programs of the row
+// table (job[0]) first, then those of the column table (job[1]).
+struct TableArgs {
+    JobDesc job[2];
+    const ProgDesc *progs;
+    int32_t n_progs[2];
 };
 
 // Batched evaluation: a pair is one program of one job; its work items are
@@ -185,14 +238,15 @@ struct Variant {
     int D;
 };
 
-// ext: the interpreter that also knows the bitwise operators and warp (only
-// K = 4).
-hipError_t launch_interp(int K, int D, bool store, const InterpArgs &a, hipStream_t s, bool bit);
+// form: kFlat, or (only with K = 4 and the register stack) another one; the
+// LDS stack form knows every operator.
+hipError_t launch_interp(int K, int D, bool store, const InterpArgs &a, hipStream_t s, int form);
+hipError_t launch_tables(int K, const TableArgs &a, hipStream_t s);
 // Batched interpreter kernels (for graph nodes): the persistent form takes
 // (jobs, pairs, item_first, groups, g, counters[groups x batch_parts()]),
 // the direct form (jobs, pairs, item_first, groups, g) with one wave per item.
-const void *batch_kernel(int K, int D, bool store, bool persistent, bool bit);
-int batch_grid(int K, int D, bool store, bool bit);  // resident waves of the persistent form
+const void *batch_kernel(int K, int D, bool store, bool persistent, int form);
+int batch_grid(int K, int D, bool store, int form);  // resident waves of the persistent form
 uint32_t batch_parts();
 const void *reset_kernel();           // (uint32_t *counters, int32_t n)
 const void *finalize_batch_kernel();  // (const FinJob *, const int32_t *n_jobs, const uint32_t *n_ind)
@@ -286,7 +340,7 @@ hipError_t launch_breed(const BreedArgs &A, const int32_t *bad, int64_t *out_off
                         hipStream_t s);
 int64_t breed_scan_blocks(int64_t n);
 hipError_t launch_breed_write(const BreedArgs &A, const int64_t *out_off, uint2 *out_tok, hipStream_t s);
-bool interp_variant_exists(int K, int D, bool bit = false);
+bool interp_variant_exists(int K, int D, int form = kFlat);
 int interp_max_stack();   // register stack slots
 int interp_lds_stack();   // LDS stack slots (the other stack form, K = 2)
 
