@@ -4,7 +4,7 @@
 // evaluations, Sec. 4.2; their textbook form, Koza 1992).
 //
 // Four launches: the shape of every parent token (subtree size, height,
-// depth from the root), the decisions of every offspring (one thread each,
+// depth from the root; one wave per tree), the decisions of every offspring (one thread each,
 // drawing from its own counter-based stream, writing one record and the
 // length of each child tree), an exclusive scan of the lengths into the
 // offspring offsets, and the copy of the child trees (one wave per child:
@@ -14,6 +14,7 @@
 #include <hip/hip_runtime.h>
 
 #include "tgp_internal.h"
+#include "tree_scan.h"
 
 namespace tgp {
 
@@ -123,7 +124,7 @@ __device__ inline uint32_t tournament(Draws &dr, const BreedArgs &A) {
 }
 
 // Shape of one tree in global memory (the fallback for trees whose operand
-// stack outgrows the LDS stack): subtree size and height from the operands
+// stack outgrows the wave's LDS table): subtree size and height from the operands
 // (the last operand ends just before its parent, each earlier one just
 // before the next), then the depth from the root, parents before children.
 // Returns 0, 1 (malformed) or 2 (unknown operator).
@@ -156,82 +157,36 @@ __device__ int shape_global(const uint2 *tok, int64_t o0, int64_t o1, int32_t *s
     return 0;
 }
 
-constexpr int kShapeStack = 32;  // LDS operand-stack entries per thread
+// Shape of every token, one wave per tree (tree_scan.h): subtree size and
+// height forward, depth from the root backward.  A tree whose operand stack
+// outgrows the LDS table is redone with shape_global.  A tree that is not
+// exactly one postfix tree, or holds an unknown operator, raises *bad (1 =
+// malformed, 2 = operator).  1000 x 3 trees to depth 12: 1.31 ms with one
+// thread per tree, 0.18 ms with one wave.
+constexpr int64_t kShapeBlocks = 1 << 20;
 
-// Shape of every token, one thread per tree.  Forward, an operand stack of
-// (size, height) pairs in LDS gives each token's subtree size and height
-// from its operands' entries; backward from the root, a stack of (depth of
-// the children, children still to come) frames gives each token's depth.
-// Both stacks hold at most the tree's postfix stack depth; a tree that needs
-// more than kShapeStack entries is redone with shape_global.  A tree that is
-// not exactly one postfix tree, or holds an unknown operator, raises *bad
-// (1 = malformed, 2 = operator).
 __global__ __launch_bounds__(64) void k_shape(const uint2 *tok, const int64_t *off, int64_t R, int64_t T,
                                               int32_t *size, int32_t *height, int32_t *depth, int32_t *bad) {
-    __shared__ int2 stk[kShapeStack][64];
+    __shared__ int2 table[kScanSlots + 1];
     const int lane = threadIdx.x;
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + lane;
-    if (r >= R) return;
-    const int64_t o0 = off[r], o1 = off[r + 1];
-    if (o0 < 0 || o1 <= o0 || o1 > T) {
-        atomicMax(bad, 1);
-        return;
+    for (int64_t r = blockIdx.x; r < R; r += gridDim.x) {
+        const int64_t o0 = off[r], o1 = off[r + 1];
+        int verdict = kTreeParse;
+        if (o0 >= 0 && o1 > o0 && o1 <= T) {
+            TreeInfo info;
+            verdict = tree_scan<false>(tok, o0, o1, lane, table, nullptr, nullptr, info,
+                                       [&](int64_t t, const TreeToken &x) {
+                                           size[t] = (int32_t)(t + 1 - x.first);
+                                           height[t] = x.height;
+                                       });
+            if (verdict == kTreeDeep)
+                verdict = lane == 0 ? shape_global(tok, o0, o1, size, height, depth) : kTreeOk;
+            else if (verdict == kTreeOk)
+                tree_depths(tok, o0, o1, lane, table, [&](int64_t t, int32_t d) { depth[t] = d; });
+        }
+        if (lane == 0 && verdict) atomicMax(bad, verdict);
+        __syncthreads();
     }
-    int sp = 0, verdict = 0;
-    bool overflow = false;
-    for_tokens<8, false>(tok, o0, o1, [&](int64_t i, uint2 w) {
-        const int op = tok_op(w);
-        if (op >= TGP_NUM_OPS) {
-            verdict = 2;
-            return false;
-        }
-        const int a = arity_of(op);
-        if (sp < a) {
-            verdict = 1;
-            return false;
-        }
-        int32_t s = 1, h = 0;
-        for (int j = 0; j < a; ++j) {
-            const int2 e = stk[--sp][lane];
-            s += e.x;
-            h = max(h, e.y + 1);
-        }
-        size[i] = s;
-        height[i] = h;
-        if (sp == kShapeStack) {
-            overflow = true;
-            return false;
-        }
-        stk[sp++][lane] = int2{s, h};
-        return true;
-    });
-    if (verdict) {
-        atomicMax(bad, verdict);
-        return;
-    }
-    if (overflow) {
-        const int v = shape_global(tok, o0, o1, size, height, depth);
-        if (v) atomicMax(bad, v);
-        return;
-    }
-    if (sp != 1) {
-        atomicMax(bad, 1);
-        return;
-    }
-    // backward: frames (depth of the children, children still to come)
-    sp = 0;
-    for_tokens<8, true>(tok, o0, o1, [&](int64_t i, uint2 w) {
-        const int a = arity_of(tok_op(w));
-        int32_t d = 0;
-        if (sp > 0) {
-            int2 &f = stk[sp - 1][lane];
-            d = f.x;
-            if (--f.y == 0) --sp;
-        }
-        depth[i] = d;
-        if (a > 0) stk[sp++][lane] = int2{d + 1, a};
-        return true;
-    });
 }
 
 // The decisions of one offspring (one thread each): operator, parents, and
@@ -390,7 +345,7 @@ inline dim3 grid_of(int64_t n, int b) { return dim3((unsigned)((n + b - 1) / b))
 hipError_t launch_shape(const uint2 *tok, const int64_t *off, int64_t R, int64_t T, int32_t *size,
                         int32_t *height, int32_t *depth, int32_t *bad, hipStream_t s) {
     if (R <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_shape, grid_of(R, 64), dim3(64), 0, s, tok, off, R, T, size, height, depth, bad);
+    hipLaunchKernelGGL(k_shape, dim3((unsigned)(R < kShapeBlocks ? R : kShapeBlocks)), dim3(64), 0, s, tok, off, R, T, size, height, depth, bad);
     return hipGetLastError();
 }
 

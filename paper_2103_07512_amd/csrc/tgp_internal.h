@@ -262,50 +262,6 @@ struct FoldDesc {
 hipError_t launch_fold_level(const FoldDesc *jobs, const int2 *list, int32_t n, hipStream_t s);
 hipError_t launch_finalize_batch(const FinJob *jobs, const int32_t *n_jobs, const uint32_t *n_ind,
                                  int32_t grid, hipStream_t s);
-#ifdef __HIPCC__
-// Calls f(i, token i) for the tokens of [lo, hi) in order (REV: from hi - 1
-// down to lo), reading them N at a time with the next N in flight, until f
-// returns false; returns whether every token was visited.  Per-tree scans
-// (one thread per tree) use it so that each token's load does not stall the
-// scan's dependent steps.  Two buffers alternate (a copy from the in-flight
-// buffer would wait for it), and every load is unconditional, at an index
-// clamped into [lo, hi) (a branch around each load hides from the compiler
-// which loads are outstanding, and it then waits for all of them).
-template <int N, bool REV, typename F>
-__device__ __forceinline__ bool for_tokens(const uint2 *tok, int64_t lo, int64_t hi, F &&f) {
-    if (hi <= lo) return true;
-    uint2 a[N], b[N];
-    auto at = [&](int64_t base, int j) { return REV ? base - j : base + j; };
-    auto ok = [&](int64_t i) { return i >= lo && i < hi; };
-    auto load = [&](uint2 (&buf)[N], int64_t base) {
-#pragma unroll
-        for (int j = 0; j < N; ++j) {
-            const int64_t i = at(base, j);
-            buf[j] = tok[i < lo ? lo : (i >= hi ? hi - 1 : i)];
-        }
-    };
-    auto run = [&](const uint2 (&buf)[N], int64_t base) {
-#pragma unroll
-        for (int j = 0; j < N; ++j)
-            if (ok(at(base, j)) && !f(at(base, j), buf[j])) return false;
-        return true;
-    };
-    int64_t base = REV ? hi - 1 : lo;
-    load(a, base);
-    for (;;) {
-        const int64_t nb = at(base, N);
-        load(b, nb);
-        if (!run(a, base)) return false;
-        if (!ok(nb)) return true;
-        const int64_t nb2 = at(nb, N);
-        load(a, nb2);
-        if (!run(b, nb)) return false;
-        if (!ok(nb2)) return true;
-        base = nb2;
-    }
-}
-#endif
-
 // Genetic operators (k_breed.hip).  A child tree is the first parent's
 // tokens [a0, cut_lo) + a middle part of `mid` tokens + [cut_hi, a1); the
 // middle is the second parent's tokens from b_lo (splice) or a new random
