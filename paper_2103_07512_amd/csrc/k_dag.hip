@@ -7,7 +7,7 @@
 //   1. structure: one wave per tree scans its postfix tokens 64 at a time,
 //      validates arities and opcodes, and records each token's children and
 //      height (a terminal has height 0);
-//   2. hash-consing, level by level in increasing height: a token's key is
+//   2. hash-consing, level by level in increasing height (one launch each): a token's key is
 //      (opcode, payload, classes of its children), whose children all lie on
 //      lower, already finished levels.  Keys go into an open-addressing table
 //      (linear probing, capacity >= 2 x tokens); equal keys are detected by
@@ -15,32 +15,44 @@
 //      token's class is the table slot of its key (a slot never moves, so the
 //      keys built from classes stay put); the representative of a key is its
 //      smallest token index (atomicMin over every level: with rewrites, one
-//      key can occur at several tree heights), and a last pass replaces each
+//      key can occur at several tree heights), and a later pass replaces each
 //      class by its representative, so the result does not depend on thread
 //      timing;
 //   3. compaction: representatives are numbered by an exclusive scan in token
 //      order, which is the order of first occurrence in a postfix walk of the
 //      trees in population order, so children get smaller ids than parents.
+// A small population takes steps 2 and 3 in one workgroup (k_build_small),
+// whose barriers cost a microsecond where a launch per pass costs several.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 
-#include <string.h>
+#include <stddef.h>
 #include <stdio.h>
+#include <string.h>
 #include <vector>
 
-#include "tgp_internal.h"
+#include "runtime_internal.h"
 #include "tree_scan.h"
 
 namespace tgp {
 
+constexpr int kLvlBins = 512;  // tree levels counted in LDS
+
+// What the host reads back.  A build ends with one copy of it and the DAG's
+// arrays (small populations), or of it, then of the arrays.
 struct BuildStatus {
     unsigned long long first_error;  // (tree << 4) | code, min over trees; ~0 = none
+    int64_t first_off, last_off;     // the population's first and last offset
     int32_t max_height;
     int32_t max_var;
     int32_t max_stack;
-    int32_t lost_key;  // nonzero when hash-consing found no slot for a key
+    int32_t nodes;                   // distinct subtrees
+    int32_t cnt[kLvlBins];           // tokens of each height
+    int32_t cursor[kLvlBins];        // and how many of them are listed
 };
+// The head of a DAG's device block, in front of its arrays.
+constexpr size_t kBlobHead = (sizeof(BuildStatus) + 255) / 256 * 256;
 
 enum { ERR_NONE = 0, ERR_OP = 1, ERR_PARSE = 2, ERR_RANGE = 3 };
 
@@ -86,10 +98,23 @@ __global__ __launch_bounds__(64) void k_structure(const uint2 *tok, const int64_
     }
 }
 
-// The tallest tree, deepest stack and highest axis over the trees' info.
-__global__ __launch_bounds__(1024) void k_tree_max(const int4 *info, int64_t R, BuildStatus *st) {
+// The status of a build that has not started, with the population's ends.
+__global__ __launch_bounds__(256) void k_build_init(BuildStatus *st, const int64_t *off, int64_t R) {
+    for (int i = threadIdx.x; i < kLvlBins; i += blockDim.x) st->cnt[i] = st->cursor[i] = 0;
+    if (threadIdx.x == 0) {
+        st->first_error = ~0ull;
+        st->first_off = off[0];
+        st->last_off = off[R];
+        st->max_height = st->max_stack = st->nodes = 0;
+        st->max_var = -1;
+    }
+}
+
+// The tallest tree, deepest stack and highest axis over the trees' info: the
+// maxima of trees first, first + step, ... into *st.
+__device__ __forceinline__ void tree_max(const int4 *info, int64_t R, int64_t first, int64_t step, BuildStatus *st) {
     int32_t h = 0, sp = 0, v = -1;
-    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < R; r += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t r = first; r < R; r += step) {
         const int4 x = info[r];
         h = max(h, x.x);
         sp = max(sp, x.y);
@@ -101,9 +126,9 @@ __global__ __launch_bounds__(1024) void k_tree_max(const int4 *info, int64_t R, 
         v = max(v, __shfl_xor(v, o));
     }
     if ((threadIdx.x & 63) == 0) {
-        atomicMax(&st->max_height, h);
-        atomicMax(&st->max_stack, sp);
-        atomicMax(&st->max_var, v);
+        if (h > 0) atomicMax(&st->max_height, h);
+        if (sp > 0) atomicMax(&st->max_stack, sp);
+        if (v >= 0) atomicMax(&st->max_var, v);
     }
 }
 
@@ -124,29 +149,51 @@ __global__ void k_level_scatter(const int32_t *height, int64_t T, int32_t *curso
 // leaves, so the global forms above serialise on one address).  A block
 // takes kLvlPer tokens per thread and touches each global counter once.
 // Used when the tallest tree has at most kLvlBins levels; the order of the
-// tokens inside a level is not significant.
-constexpr int kLvlBins = 512;
+// tokens inside a level is not significant.  The count runs before the trees
+// are known to be sound, so it leaves out heights outside the bins (a
+// malformed tree's are not written).
 constexpr int kLvlPer = 16;
+constexpr int kMaxBlocks = 4;  // of the count launch, reduce the trees' info as well
 
-__global__ void __launch_bounds__(256) k_level_hist_lds(const int32_t *height, int64_t T, int32_t H,
-                                                        int32_t *cnt) {
+__global__ void __launch_bounds__(256) k_level_hist_lds(const int32_t *height, int64_t T, const int4 *info, int64_t R,
+                                                        BuildStatus *st) {
     __shared__ int32_t c[kLvlBins];
-    for (int i = threadIdx.x; i < H; i += blockDim.x) c[i] = 0;
+    for (int i = threadIdx.x; i < kLvlBins; i += blockDim.x) c[i] = 0;
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * blockDim.x * kLvlPer + threadIdx.x;
     for (int j = 0; j < kLvlPer; ++j) {
         const int64_t t = base + (int64_t)j * blockDim.x;
-        if (t < T) atomicAdd(&c[height[t]], 1);
+        const uint32_t h = t < T ? (uint32_t)height[t] : ~0u;
+        if (h < kLvlBins) atomicAdd(&c[h], 1);
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < H; i += blockDim.x)
-        if (c[i]) atomicAdd(&cnt[i], c[i]);
+    for (int i = threadIdx.x; i < kLvlBins; i += blockDim.x)
+        if (c[i]) atomicAdd(&st->cnt[i], c[i]);
+    const int64_t nb = min((int64_t)gridDim.x, (int64_t)kMaxBlocks);
+    if (blockIdx.x < nb)
+        tree_max(info, R, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, nb * blockDim.x, st);
 }
 
-__global__ void __launch_bounds__(256) k_level_scatter_lds(const int32_t *height, int64_t T, int32_t H,
-                                                           int32_t *cursor, int32_t *list) {
-    __shared__ int32_t c[kLvlBins];
-    for (int i = threadIdx.x; i < H; i += blockDim.x) c[i] = 0;
+// First list entry of every level, into start[0 .. kLvlBins] (256 threads).
+__device__ __forceinline__ void level_starts(const int32_t *cnt, int32_t *start, int32_t *tmp) {
+    const int tid = threadIdx.x;
+    const int32_t a = cnt[2 * tid], b = cnt[2 * tid + 1];
+    int32_t s = wave_scan(a + b, tid & 63);
+    if ((tid & 63) == 63) tmp[tid >> 6] = s;
+    __syncthreads();
+    for (int w = 0; w < (tid >> 6); ++w) s += tmp[w];
+    start[2 * tid] = s - a - b;
+    start[2 * tid + 1] = s - b;
+    if (tid == 255) start[kLvlBins] = s;
+    __syncthreads();
+}
+
+__global__ void __launch_bounds__(256) k_level_scatter_lds(const int32_t *height, int64_t T, BuildStatus *st,
+                                                           int32_t *list) {
+    static_assert(kLvlBins == 512, "two levels per thread");
+    __shared__ int32_t c[kLvlBins], start[kLvlBins + 1], tmp[4];
+    level_starts(st->cnt, start, tmp);
+    for (int i = threadIdx.x; i < kLvlBins; i += blockDim.x) c[i] = 0;
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * blockDim.x * kLvlPer + threadIdx.x;
     int32_t h[kLvlPer], r[kLvlPer];
@@ -156,8 +203,8 @@ __global__ void __launch_bounds__(256) k_level_scatter_lds(const int32_t *height
         r[j] = h[j] >= 0 ? atomicAdd(&c[h[j]], 1) : 0;
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < H; i += blockDim.x)
-        c[i] = c[i] ? atomicAdd(&cursor[i], c[i]) : 0;
+    for (int i = threadIdx.x; i < kLvlBins; i += blockDim.x)
+        if (c[i]) c[i] = start[i] + atomicAdd(&st->cursor[i], c[i]);
     __syncthreads();
     for (int j = 0; j < kLvlPer; ++j)
         if (h[j] >= 0) list[c[h[j]] + r[j]] = (int32_t)(base + (int64_t)j * blockDim.x);
@@ -257,173 +304,167 @@ __device__ __forceinline__ int32_t rewrite_target(int32_t t, const uint2 *tok, c
     }
 }
 
-// 2a. Insert the tokens of one level; the slot of a key ends up holding the
-// smallest token index with that key.  A rewritten token is not inserted.
-__global__ void k_hash_insert(const int32_t *list, int32_t n, const uint2 *tok, const int32_t *kid,
-                              const int32_t *canon, int32_t *table, uint64_t mask,
-                              uint32_t hash_bits, bool commute, bool rewrite) {
-    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    const bool live = i < n;
-    int32_t t = live ? list[i] : -1;
+// 2a. Inserts token t (-1: none) into the table; the slot of a key ends up
+// holding the smallest token index with that key, and is the token's class.
+// A rewritten token is not inserted: its class is the one it stands for.
+// Every lane of the wave calls it (the leaves' ballots).
+__device__ __forceinline__ void hash_token(int32_t t, const uint2 *tok, const int32_t *kid, int32_t *canon,
+                                           int32_t *table, uint64_t mask, uint32_t hash_bits, bool commute,
+                                           bool rewrite) {
+    const bool live = t >= 0;
     const Key k = live ? key_of(t, tok, kid, canon, commute) : Key{0xffffffffu, 0, 0, 0};
-    const bool rewritten = live && rewrite && rewrite_target(t, tok, kid, canon, table) >= 0;
-    // Leaves (x, y, z and the constants) repeat many times within one wave:
-    // lanes holding the same leaf key (its first two words) insert once,
+    const int32_t target = live && rewrite ? rewrite_target(t, tok, kid, canon, table) : -1;
+    // Leaves (x, y, z and common constants) repeat many times within one
+    // wave: lanes holding the same leaf key (its first two words) insert once,
     // through the group's lowest lane, with the group's smallest token index.
-    // Every lane of the wave takes part in the ballots and shuffles.
+    // The axes first, then two constants (the distinct constants of a random
+    // population would each make a group); four groups a wave at most.
     const uint32_t op = k.k0 & 0xffu;
     const bool leaf = live && (op == TGP_VAR || op == TGP_CONST);
-    bool insert = live && !leaf && !rewritten;
-    const int lane = (int)(threadIdx.x & 63u);
-    uint64_t todo = __ballot(leaf);
-    while (todo) {
+    bool insert = live && target < 0;
+    int from = (int)(threadIdx.x & 63u);  // the lane that inserts this lane's key
+    const int lane = from;
+    int32_t smallest = t;
+    uint64_t todo = __ballot(leaf), axes = __ballot(live && op == TGP_VAR), consts = todo & ~axes;
+    for (int round = 0; round < 4 && todo; ++round) {
+        todo = axes ? axes : consts;
         const int leader = __ffsll((unsigned long long)todo) - 1;
         const uint32_t l0 = __shfl(k.k0, leader), l1 = __shfl(k.k1, leader);
         const uint64_t same = __ballot(leaf && k.k0 == l0 && k.k1 == l1) & todo;
-        int32_t m = ((same >> lane) & 1u) ? t : INT32_MAX;
-        for (int d = 32; d > 0; d >>= 1) m = min(m, __shfl_xor(m, d));
-        if (lane == leader) {
-            t = m;
-            insert = true;
+        if (__popcll(same) > 1) {
+            int32_t m = ((same >> lane) & 1u) ? t : INT32_MAX;
+            for (int d = 32; d > 0; d >>= 1) m = min(m, __shfl_xor(m, d));
+            if ((same >> lane) & 1u) {
+                from = leader;
+                insert = lane == leader;
+                smallest = m;
+            }
         }
-        todo &= ~same;
+        axes &= ~same;
+        consts &= ~same;
+        todo = axes | consts;
     }
-    if (!insert) return;
-    uint64_t s = key_hash(k, hash_bits) & mask;
-    for (;;) {
-        int32_t e = table[s];
-        if (e < 0) {
-            e = atomicCAS(&table[s], -1, t);
-            if (e < 0) return;  // claimed an empty slot
+    uint64_t s = 0;
+    if (insert) {
+        s = key_hash(k, hash_bits) & mask;
+        for (;;) {  // at most half the table is ever taken
+            int32_t e = table[s];
+            if (e < 0) {
+                e = atomicCAS(&table[s], -1, smallest);
+                if (e < 0) break;  // claimed an empty slot
+            }
+            if (key_eq(key_of(e, tok, kid, canon, commute), k)) {
+                // A slot's value only decreases and its key never changes, so a
+                // token that is not below the value it read (which may be stale,
+                // never lower than the current one) cannot lower it.  Skipping
+                // those leaves the atomics to the few tokens that can: without
+                // this, every leaf x or y of the level updated one address.
+                if (smallest < e) atomicMin(&table[s], smallest);
+                break;
+            }
+            s = (s + 1) & mask;
         }
-        if (key_eq(key_of(e, tok, kid, canon, commute), k)) {
-            // A slot's value only decreases and its key never changes, so a
-            // token that is not below the value it read (which may be stale,
-            // never lower than the current one) cannot lower it.  Skipping
-            // those leaves the atomics to the few tokens that can: without
-            // this, every leaf x or y of the level updated one address.
-            if (t < e) atomicMin(&table[s], t);
-            return;
-        }
-        s = (s + 1) & mask;
     }
+    const int32_t slot = __shfl((int32_t)s, from);
+    if (live) canon[t] = target >= 0 ? target : slot;
 }
 
-// 2b. Every token of the level looks its key up again and takes the
-// representative.
-__global__ void k_hash_resolve(const int32_t *list, int32_t n, const uint2 *tok, const int32_t *kid,
-                               int32_t *canon, const int32_t *table, uint64_t mask,
-                               uint32_t hash_bits, bool commute, bool rewrite, BuildStatus *st) {
+// One level of tokens.  (The class needs no second look-up: a key's slot
+// never moves once it is claimed, and the children's classes are final.)
+__global__ __launch_bounds__(256) void k_hash_level(const int32_t *list, int32_t n, const uint2 *tok,
+                                                    const int32_t *kid, int32_t *canon, int32_t *table, uint64_t mask,
+                                                    uint32_t hash_bits, bool commute, bool rewrite) {
     const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int32_t t = list[i];
-    if (rewrite) {
-        const int32_t target = rewrite_target(t, tok, kid, canon, table);
-        if (target >= 0) {
-            canon[t] = target;
-            return;
-        }
-    }
-    const Key k = key_of(t, tok, kid, canon, commute);
-    uint64_t s = key_hash(k, hash_bits) & mask;
-    for (;;) {
-        const int32_t e = table[s];
-        if (e < 0) {
-            // t itself was inserted before the first empty slot of its probe
-            // sequence, so reaching one means the table is corrupt: the build
-            // fails with an error instead of yielding a wrong DAG
-            atomicOr(&st->lost_key, 1);
-            canon[t] = (int32_t)s;  // an empty slot; the build fails with an error
-            return;
-        }
-        if (key_eq(key_of(e, tok, kid, canon, commute), k)) {
-            canon[t] = (int32_t)s;  // the class: the key's slot
-            return;
-        }
-        s = (s + 1) & mask;
-    }
+    hash_token(i < n ? list[i] : -1, tok, kid, canon, table, mask, hash_bits, commute, rewrite);
 }
 
-// 2c. After the last level: every class becomes its representative, the
-// smallest token index with that key.
-__global__ void k_class_to_token(int32_t *canon, int64_t T, const int32_t *table) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < T) canon[t] = table[canon[t]];
+__global__ void k_fill(int32_t *p, int64_t n, int32_t v) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        p[i] = v;
 }
 
-__global__ void k_flags(const int32_t *canon, int64_t T, int32_t *flag) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < T) flag[t] = canon[t] == (int32_t)t ? 1 : 0;
-}
+// 2b. After the last level: every class becomes its representative, the
+// smallest token index with that key; representatives get their rank within
+// the 1024 tokens of the block, and the block its count.
+constexpr int kRankTokens = 1024;
 
-// Exclusive scan, 1024 elements per block (256 threads x 4).
-__global__ __launch_bounds__(256) void k_scan_block(const int32_t *in, int32_t *out, int64_t n,
-                                                    int32_t *block_sums) {
-    __shared__ int32_t sh[256];
+__global__ __launch_bounds__(256) void k_rank(int32_t *canon, int64_t T, const int32_t *table, int32_t *pos,
+                                              int32_t *block_sum) {
+    __shared__ int32_t tmp[4];
     const int tid = threadIdx.x;
-    const int64_t base = (int64_t)blockIdx.x * 1024 + tid * 4;
-    int32_t v[4];
-    int32_t sum = 0;
+    const int64_t base = (int64_t)blockIdx.x * kRankTokens + tid * 4;
+    int32_t f[4], sum = 0;
     for (int j = 0; j < 4; ++j) {
-        v[j] = base + j < n ? in[base + j] : 0;
-        sum += v[j];
+        const int64_t t = base + j;
+        f[j] = 0;
+        if (t < T) {
+            const int32_t c = table[canon[t]];
+            canon[t] = c;
+            f[j] = c == (int32_t)t ? 1 : 0;
+        }
+        sum += f[j];
     }
-    sh[tid] = sum;
+    int32_t run = wave_scan(sum, tid & 63);
+    if ((tid & 63) == 63) tmp[tid >> 6] = run;
     __syncthreads();
-    for (int o = 1; o < 256; o <<= 1) {
-        const int32_t x = tid >= o ? sh[tid - o] : 0;
-        __syncthreads();
-        sh[tid] += x;
-        __syncthreads();
-    }
-    int32_t run = sh[tid] - sum;  // exclusive prefix of this thread
+    for (int w = 0; w < (tid >> 6); ++w) run += tmp[w];
+    if (tid == 255) block_sum[blockIdx.x] = run;
+    run -= sum;
     for (int j = 0; j < 4; ++j) {
-        if (base + j < n) out[base + j] = run;
-        run += v[j];
+        if (base + j < T) pos[base + j] = run;
+        run += f[j];
     }
-    if (tid == 255 && block_sums) block_sums[blockIdx.x] = sh[255];
 }
 
-__global__ void k_scan_add(int32_t *out, int64_t n, const int32_t *block_off) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] += block_off[i / 1024];
+// Exclusive scan of the blocks' counts by one block; the total is the number
+// of nodes.
+__global__ __launch_bounds__(1024) void k_rank_blocks(int32_t *block_sum, int64_t nb, BuildStatus *st) {
+    __shared__ int32_t tmp[16];
+    const int tid = threadIdx.x;
+    int32_t carry = 0;
+    for (int64_t c0 = 0; c0 < nb; c0 += 1024) {
+        const int32_t v = c0 + tid < nb ? block_sum[c0 + tid] : 0;
+        int32_t run = wave_scan(v, tid & 63);
+        if ((tid & 63) == 63) tmp[tid >> 6] = run;
+        __syncthreads();
+        int32_t total = 0;
+        for (int w = 0; w < 16; ++w) {
+            if (w < (tid >> 6)) run += tmp[w];
+            total += tmp[w];
+        }
+        if (c0 + tid < nb) block_sum[c0 + tid] = carry + run - v;
+        carry += total;
+        __syncthreads();
+    }
+    if (tid == 0) st->nodes = carry;
 }
 
-static hipError_t exclusive_scan(const int32_t *in, int32_t *out, int64_t n, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    const int64_t nb = (n + 1023) / 1024;
-    if (nb == 1) {
-        hipLaunchKernelGGL(k_scan_block, dim3(1), dim3(256), 0, s, in, out, n, (int32_t *)nullptr);
-        return hipGetLastError();
-    }
-    int32_t *sums = nullptr, *offs = nullptr;
-    hipError_t e = hipMallocAsync((void **)&sums, nb * sizeof(int32_t), s);
-    if (e != hipSuccess) return e;
-    e = hipMallocAsync((void **)&offs, nb * sizeof(int32_t), s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_scan_block, dim3(nb), dim3(256), 0, s, in, out, n, sums);
-    e = exclusive_scan(sums, offs, nb, s);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_scan_add, dim3((n + 255) / 256), dim3(256), 0, s, out, n, offs);
-        e = hipGetLastError();
-    }
-    hipFreeAsync(sums, s);
-    hipFreeAsync(offs, s);
-    return e;
-}
+// The arrays of a DAG's block (DagDevice), laid out for U nodes.
+struct NodeArrays {
+    int32_t *op, *value, *kid, *height, *mult, *indeg, *roots;
+    __device__ __forceinline__ NodeArrays(int32_t *b, int64_t U)
+        : op(b), value(b + U), kid(b + 2 * U), height(b + 5 * U), mult(b + 6 * U), indeg(b + 7 * U), roots(b + 8 * U) {}
+};
 
-// 3a. Node fields of every representative.
-__global__ void k_emit_nodes(const uint2 *tok, const int32_t *canon, const int32_t *pos,
-                             const int32_t *height, int64_t T, int32_t *node_op, float *node_value,
-                             int32_t *node_height) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= T || canon[t] != (int32_t)t) return;
-    const int32_t id = pos[t];
-    const uint2 w = tok[t];
+// Fields of the node that token w stands for.
+__device__ __forceinline__ void put_node(const NodeArrays &A, int32_t id, uint2 w, int32_t height) {
     const uint32_t op = w.x & 0xffu;
-    node_op[id] = (int32_t)(op == TGP_VAR ? (op | (w.x & 0xff00u)) : op);
-    node_value[id] = op == TGP_CONST ? __uint_as_float(w.y) : 0.0f;
-    node_height[id] = height[t];
+    A.op[id] = (int32_t)(op == TGP_VAR ? (op | (w.x & 0xff00u)) : op);
+    A.value[id] = op == TGP_CONST ? (int32_t)w.y : 0;
+    A.height[id] = height;
+}
+
+// 3a. Node fields of every representative, the roots, and zeroed counts.
+__global__ void k_emit_nodes(const uint2 *tok, const int32_t *canon, const int32_t *pos, const int32_t *block_off,
+                             const int32_t *height, int64_t T, const int32_t *root_tok, int64_t R, int32_t *blob,
+                             const BuildStatus *st) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // up to max(T, R)
+    const int64_t U = st->nodes;
+    const NodeArrays A(blob, U);
+    auto id_of = [&](int32_t c) { return pos[c] + block_off[c / kRankTokens]; };
+    if (t < T && canon[t] == (int32_t)t) put_node(A, id_of((int32_t)t), tok[t], height[t]);
+    if (t < U) A.mult[t] = A.indeg[t] = 0;
+    if (t < R) A.roots[t] = id_of(canon[root_tok[t]]);
 }
 
 // 3b. Children ids, in-degrees and multiplicities.
@@ -462,64 +503,164 @@ __device__ __forceinline__ void block_counts_flush(const BlockCounts &c, int32_t
         if (c.id[e] >= 0) atomicAdd(&counter[c.id[e]], c.n[e]);
 }
 
-// Adds 1 for every lane whose id >= 0: lanes of a wave with equal ids are
-// grouped by ballots (the loop runs once per distinct id, wave-uniform) and
-// add their count through the group's lowest lane into the block's table.
-// The shared leaves (x, y and common constants) are counted by many tokens
-// of every wave; one device atomic per lane serialised on their few
-// addresses.
-__device__ __forceinline__ void add_one_per_lane(BlockCounts &c, int32_t *counter, int32_t id) {
-    const int lane = (int)(threadIdx.x & 63u);
-    uint64_t todo = __ballot(id >= 0);
-    while (todo) {
-        const int leader = __ffsll((unsigned long long)todo) - 1;
-        const int32_t lid = __shfl(id, leader);
-        const uint64_t same = __ballot(id == lid) & todo;
-        if (lane == leader) block_counts_add(c, counter, lid, (int32_t)__popcll(same));
-        todo &= ~same;
-    }
-}
-
 // Blocks of four waves: a block of many waves waits for that many free wave
 // slots on one compute unit, which it rarely finds while a long evaluation
 // kernel runs beside it (DAGs are built on side streams when serving).
 constexpr int kEmitBlock = 256;
 
+// (Lanes add to the block's LDS table one by one: equal ids serialise there
+// for a cycle each.  Grouping them by ballots first took up to 64 rounds a
+// wave, 25 us for the smallest population.)
 __global__ __launch_bounds__(kEmitBlock) void k_emit_edges(const int32_t *canon, const int32_t *pos,
-                                                           const int32_t *kid, int64_t T, int32_t *node_kid,
-                                                           int32_t *indeg, int32_t *mult) {
+                                                           const int32_t *block_off, const int32_t *kid, int64_t T,
+                                                           int32_t *blob, const BuildStatus *st) {
     __shared__ BlockCounts cm, ci;
     block_counts_clear(cm);
     block_counts_clear(ci);
     __syncthreads();
+    const NodeArrays A(blob, st->nodes);
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    // every lane reaches the ballots and barriers; lanes past T take part
-    // with id -1 (nothing to count)
-    const int32_t c = t < T ? canon[t] : -1;
-    const int32_t id = c >= 0 ? pos[c] : -1;
-    add_one_per_lane(cm, mult, id);
-    const bool rep = c == (int32_t)t && t < T;  // the token that represents node id
-    for (int j = 0; j < 3; ++j) {
-        const int32_t k = rep ? kid[3 * t + j] : -1;
-        const int32_t kid_id = k < 0 ? -1 : pos[canon[k]];
-        if (rep) node_kid[3 * id + j] = kid_id;
-        add_one_per_lane(ci, indeg, kid_id);
+    auto id_of = [&](int32_t c) { return pos[c] + block_off[c / kRankTokens]; };
+    if (t < T) {
+        const int32_t c = canon[t];
+        const int32_t id = id_of(c);
+        block_counts_add(cm, A.mult, id, 1);
+        if (c == (int32_t)t) {  // the token that represents node id
+            for (int j = 0; j < 3; ++j) {
+                const int32_t k = kid[3 * t + j];
+                const int32_t kid_id = k < 0 ? -1 : id_of(canon[k]);
+                A.kid[3 * (int64_t)id + j] = kid_id;
+                if (k >= 0) block_counts_add(ci, A.indeg, kid_id, 1);
+            }
+        }
     }
     __syncthreads();
-    block_counts_flush(cm, mult);
-    block_counts_flush(ci, indeg);
+    block_counts_flush(cm, A.mult);
+    block_counts_flush(ci, A.indeg);
 }
 
-__global__ void k_emit_roots(const int32_t *root_tok, const int32_t *canon, const int32_t *pos,
-                             int64_t R, int32_t *roots) {
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r < R) roots[r] = pos[canon[root_tok[r]]];
+// Steps 2 and 3 for a small population, after k_structure, in one workgroup
+// of 16 waves: level lists, hash-consing level by level, ranks, emission, all
+// separated by workgroup barriers (one compute unit: its vector cache is
+// shared, so plain stores are seen after a barrier; table slots, which
+// atomics write behind it, are read back past it once every wave has waited
+// for its own).  LDS: the count of every node's tokens (low half) and edges
+// (high half, at most three per node).  The head of the blob gets the status;
+// nothing else is written when a tree is malformed or too tall for the bins.
+//
+// A population of 50 trees (690 tokens) took 42 launches, copies and fills and
+// five waits, 0.30 ms a build; now three launches, two copies and two waits,
+// 0.084 ms.  At 9.4k tokens one workgroup (0.21 ms a build) loses to a launch
+// per level (0.19 ms; 0.43 before, with two launches per level and a wait
+// for every count), so the line lies between.
+constexpr int64_t kSmallTokens = 6144;  // 24 KB of counts, below 2^16 each
+constexpr int kSmallThreads = 1024;
+
+__global__ __launch_bounds__(kSmallThreads) void k_build_small(const uint2 *tok, int32_t T, const int32_t *kid,
+                                                               const int32_t *height, const int32_t *root_tok,
+                                                               const int4 *info, int32_t R, int32_t *list,
+                                                               int32_t *canon, int32_t *pos, int32_t *table,
+                                                               uint32_t mask, uint32_t hash_bits, bool commute,
+                                                               bool rewrite, int32_t *blob, const BuildStatus *st) {
+    extern __shared__ uint32_t counts[];  // [T]
+    __shared__ int32_t c[kLvlBins], start[kLvlBins + 1], tmp[16];
+    __shared__ int32_t most[3];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    auto settle = [] { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
+    if (tid < 3) most[tid] = tid < 2 ? 0 : -1;
+    for (int i = tid; i < kLvlBins; i += kSmallThreads) c[i] = 0;
+    for (uint32_t i = tid; i <= mask; i += kSmallThreads) table[i] = -1;
+    for (int i = tid; i < T; i += kSmallThreads) counts[i] = 0;
+    settle();
+    __syncthreads();
+    for (int r = tid; r < R; r += kSmallThreads) {
+        const int4 x = info[r];
+        atomicMax(&most[0], x.x);
+        atomicMax(&most[1], x.y);
+        atomicMax(&most[2], x.z);
+    }
+    __syncthreads();
+    const int32_t H = most[0] + 1;
+    BuildStatus *const head = reinterpret_cast<BuildStatus *>(reinterpret_cast<char *>(blob) - kBlobHead);
+    if (tid == 0) {
+        head->first_error = st->first_error;
+        head->max_height = most[0];
+        head->max_stack = most[1];
+        head->max_var = most[2];
+        head->nodes = 0;
+    }
+    if (st->first_error != ~0ull || H > kLvlBins) return;  // (the host reports it, or takes the general way)
+    for (int t = tid; t < T; t += kSmallThreads) atomicAdd(&c[height[t]], 1);
+    __syncthreads();
+    if (tid == 0) {
+        int32_t run = 0;
+        for (int h = 0; h < H; ++h) {
+            start[h] = run;
+            run += c[h];
+        }
+        start[H] = run;
+        head->cnt[0] = c[0];
+    }
+    __syncthreads();
+    for (int i = tid; i < H; i += kSmallThreads) c[i] = start[i];
+    __syncthreads();
+    for (int t = tid; t < T; t += kSmallThreads) list[atomicAdd(&c[height[t]], 1)] = t;
+    __syncthreads();
+    for (int32_t h = 0; h < H; ++h) {
+        const int32_t end = start[h + 1];
+        for (int32_t i0 = start[h]; i0 < end; i0 += kSmallThreads)  // whole waves take part
+            if (i0 + wave * 64 < end)
+                hash_token(i0 + tid < end ? list[i0 + tid] : -1, tok, kid, canon, table, mask, hash_bits, commute,
+                           rewrite);
+        settle();
+        __syncthreads();
+    }
+    // representatives and their ids
+    int32_t U = 0;
+    for (int t0 = 0; t0 < T; t0 += kSmallThreads) {
+        const int t = t0 + tid;
+        int32_t rep = -1;
+        if (t < T) {
+            rep = __hip_atomic_load(&table[canon[t]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            canon[t] = rep;
+        }
+        const uint64_t m = __ballot(rep == t && t < T);
+        if (lane == 0) tmp[wave] = (int32_t)__popcll(m);
+        __syncthreads();
+        int32_t run = U;
+        for (int w = 0; w < 16; ++w) {
+            if (w < wave) run += tmp[w];
+            U += tmp[w];
+        }
+        if (t < T) pos[t] = run + (int32_t)__popcll(m & ((1ull << lane) - 1));
+        __syncthreads();
+    }
+    const NodeArrays A(blob, U);
+    for (int t = tid; t < T; t += kSmallThreads) {
+        const int32_t rep = canon[t], id = pos[rep];
+        atomicAdd(&counts[id], 1u);
+        if (rep != t) continue;
+        put_node(A, id, tok[t], height[t]);
+        for (int j = 0; j < 3; ++j) {
+            const int32_t k = kid[3 * t + j];
+            const int32_t kid_id = k < 0 ? -1 : pos[canon[k]];
+            A.kid[3 * id + j] = kid_id;
+            if (k >= 0) atomicAdd(&counts[kid_id], 1u << 16);
+        }
+    }
+    for (int r = tid; r < R; r += kSmallThreads) A.roots[r] = pos[canon[root_tok[r]]];
+    __syncthreads();
+    for (int i = tid; i < U; i += kSmallThreads) {
+        A.mult[i] = (int32_t)(counts[i] & 0xffffu);
+        A.indeg[i] = (int32_t)(counts[i] >> 16);
+    }
+    if (tid == 0) head->nodes = U;
 }
 
 static inline dim3 grid_for(int64_t n, int b = 256) { return dim3((unsigned)((n + b - 1) / b)); }
 
 void dag_device_free(DagDevice *d, DevicePool &pool) {
-    pool.release(d->blob);
+    pool.release(d->block);
     *d = DagDevice{};
 }
 
@@ -535,50 +676,103 @@ void dag_device_free(DagDevice *d, DevicePool &pool) {
 
 uint32_t g_debug_hash_bits = 0;  // set by tests to force hash collisions
 
-DagBuildResult build_dag_device(const tgp_token *tok_dev, const int64_t *off_dev, int64_t R,
-                                int64_t T, DagDevice *dev, DevicePool &pool, hipStream_t s,
-                                char *err, size_t errlen, bool commute, bool rewrite) {
+DagBuildResult build_dag_device(tgp_ctx ctx, const tgp_token *tok_dev, const int64_t *off_dev, int64_t R, int64_t T,
+                                DagDevice *dev, const int32_t **host, char *err, size_t errlen) {
     DagBuildResult res{};
     res.status = TGP_OK;
     res.bad_tree = -1;
-    res.T = T;
+    DevicePool &pool = ctx->pool;
+    const hipStream_t s = ctx->stream;
+    const bool commute = ctx->commute != 0, rewrite = ctx->rewrite != 0;
     const uint2 *tok = reinterpret_cast<const uint2 *>(tok_dev);
-    int32_t *kid = nullptr, *height = nullptr, *stk = nullptr, *root_tok = nullptr;
-    int32_t *canon = nullptr, *table = nullptr, *cnt = nullptr, *list = nullptr, *flag = nullptr,
-            *pos = nullptr;
-    BuildStatus *st = nullptr;
-    int4 *info = nullptr;
-    BuildStatus hs{};
-    std::vector<int32_t> hcnt;
+    // scratch, in one block: see the offsets below
+    char *scratch = nullptr;
+    BuildStatus *st = nullptr, *hs = nullptr;
+    int32_t *kid, *height, *stk, *root_tok, *list, *canon, *pos, *table, *sums, *blob, *cnt = nullptr;
+    int4 *info;
+    void *stage = nullptr;
     uint64_t cap = 1024;
-    int64_t U = 0;
+    size_t at = 0;
+    int64_t H = 0, nb = 0;
+    bool small = false;
     *dev = DagDevice{};
+    *host = nullptr;
+
+    // The status first: a device-resident population's size is not known yet.
+    DCHK(pool.alloc((void **)&st, sizeof(BuildStatus)));
+    hipLaunchKernelGGL(k_build_init, dim3(1), dim3(256), 0, s, st, off_dev, R);
+    DCHK(hipGetLastError());
+    if (T < 0) {
+        DCHK(ctx_pinned(ctx, kBlobHead, &stage));
+        hs = static_cast<BuildStatus *>(stage);
+        DCHK(hipMemcpyAsync(hs, st, offsetof(BuildStatus, cnt), hipMemcpyDeviceToHost, s));
+        DCHK(hipStreamSynchronize(s));
+        T = hs->last_off;
+        if (hs->first_off != 0 || T < 0 || T > 0x7fffffffLL) {
+            res.status = TGP_EINVAL;
+            snprintf(err, errlen, hs->first_off != 0 ? "offsets[0] must be 0" : "bad token count");
+            goto done;
+        }
+    }
+    res.T = T;
     dev->T = T;
     dev->R = R;
     while (cap < (uint64_t)(2 * T)) cap <<= 1;
-
-    DCHK(pool.alloc((void **)&kid, sizeof(int32_t) * 3 * T));
-    DCHK(pool.alloc((void **)&height, sizeof(int32_t) * T));
-    DCHK(pool.alloc((void **)&stk, sizeof(int32_t) * T));
-    DCHK(pool.alloc((void **)&root_tok, sizeof(int32_t) * R));
-    DCHK(pool.alloc((void **)&st, sizeof(BuildStatus)));
-    hs.first_error = ~0ull;
-    hs.max_height = 0;
-    hs.max_var = -1;
-    hs.max_stack = 0;
-    hs.lost_key = 0;
-    DCHK(pool.alloc((void **)&info, sizeof(int4) * R));
-    DCHK(hipMemcpyAsync(st, &hs, sizeof(hs), hipMemcpyHostToDevice, s));
+    nb = (T + kRankTokens - 1) / kRankTokens;
+    {
+        auto part = [&at](size_t bytes) {
+            const size_t o = at;
+            at += (bytes + 255) & ~(size_t)255;
+            return o;
+        };
+        const size_t okid = part(sizeof(int32_t) * 3 * T), oheight = part(sizeof(int32_t) * T),
+                     ostk = part(sizeof(int32_t) * T), oroot = part(sizeof(int32_t) * R), oinfo = part(sizeof(int4) * R),
+                     olist = part(sizeof(int32_t) * T), ocanon = part(sizeof(int32_t) * T),
+                     opos = part(sizeof(int32_t) * T), otable = part(sizeof(int32_t) * cap),
+                     osums = part(sizeof(int32_t) * nb);
+        DCHK(pool.alloc((void **)&scratch, at));
+        kid = (int32_t *)(scratch + okid);
+        height = (int32_t *)(scratch + oheight);
+        stk = (int32_t *)(scratch + ostk);
+        root_tok = (int32_t *)(scratch + oroot);
+        info = (int4 *)(scratch + oinfo);
+        list = (int32_t *)(scratch + olist);
+        canon = (int32_t *)(scratch + ocanon);
+        pos = (int32_t *)(scratch + opos);
+        table = (int32_t *)(scratch + otable);
+        sums = (int32_t *)(scratch + osums);
+    }
+    // The DAG's block, sized for T distinct nodes, with the status in front.
+    DCHK(pool.alloc((void **)&dev->block, kBlobHead + DagDevice::blob_bytes(T, R)));
+    blob = reinterpret_cast<int32_t *>(dev->block + kBlobHead);
+    small = T > 0 && T <= kSmallTokens && R <= kSmallTokens;
     hipLaunchKernelGGL(k_structure, dim3((unsigned)std::min<int64_t>(R, kStructBlocks)), dim3(64), 0, s, tok, off_dev,
                        R, T, kid, height, stk, root_tok, info, st);
-    hipLaunchKernelGGL(k_tree_max, dim3((unsigned)std::min<int64_t>(64, (R + 1023) / 1024)), dim3(1024), 0, s, info, R,
-                       st);
     DCHK(hipGetLastError());
-    DCHK(hipMemcpyAsync(&hs, st, sizeof(hs), hipMemcpyDeviceToHost, s));
+    if (small) {
+        // one workgroup, then one copy of the status and the largest blob
+        hipLaunchKernelGGL(k_build_small, dim3(1), dim3(kSmallThreads), sizeof(uint32_t) * T, s, tok, (int32_t)T, kid,
+                           height, root_tok, info, (int32_t)R, list, canon, pos, table, (uint32_t)(cap - 1),
+                           g_debug_hash_bits, commute, rewrite, blob, st);
+        DCHK(hipGetLastError());
+        const size_t bytes = kBlobHead + DagDevice::blob_bytes(T, R);
+        DCHK(ctx_pinned(ctx, bytes, &stage));
+        DCHK(hipMemcpyAsync(stage, dev->block, bytes, hipMemcpyDeviceToHost, s));
+    } else {
+        if (T > 0) {
+            hipLaunchKernelGGL(k_level_hist_lds, grid_for(T, 256 * kLvlPer), dim3(256), 0, s, height, T, info, R, st);
+            hipLaunchKernelGGL(k_fill, dim3((unsigned)std::min<uint64_t>(1024, cap / 1024)), dim3(256), 0, s, table,
+                               (int64_t)cap, -1);
+            DCHK(hipGetLastError());
+        }
+        DCHK(ctx_pinned(ctx, kBlobHead, &stage));
+        DCHK(hipMemcpyAsync(stage, st, offsetof(BuildStatus, cursor), hipMemcpyDeviceToHost, s));
+    }
     DCHK(hipStreamSynchronize(s));
-    if (hs.first_error != ~0ull) {
-        const int code = (int)(hs.first_error & 15ull);
-        res.bad_tree = (int64_t)(hs.first_error >> 4);
+    hs = static_cast<BuildStatus *>(stage);
+    if (hs->first_error != ~0ull) {
+        const int code = (int)(hs->first_error & 15ull);
+        res.bad_tree = (int64_t)(hs->first_error >> 4);
         res.status = code == ERR_OP ? TGP_EOP : (code == ERR_PARSE ? TGP_EPARSE : TGP_EINVAL);
         snprintf(err, errlen, "tree %lld: %s", (long long)res.bad_tree,
                  code == ERR_OP ? "unknown opcode"
@@ -586,100 +780,78 @@ DagBuildResult build_dag_device(const tgp_token *tok_dev, const int64_t *off_dev
                                                      : "offsets out of range or decreasing"));
         goto done;
     }
-    res.max_height = hs.max_height;
-    res.max_stack = hs.max_stack;
-    res.max_var = hs.max_var;
-    {
-        const int64_t H = hs.max_height + 1;
-        DCHK(pool.alloc((void **)&cnt, sizeof(int32_t) * H));
-        DCHK(hipMemsetAsync(cnt, 0, sizeof(int32_t) * H, s));
-        const bool lds = H <= kLvlBins;
-        if (lds)
-            hipLaunchKernelGGL(k_level_hist_lds, grid_for(T, 256 * kLvlPer), dim3(256), 0, s, height, T,
-                               (int32_t)H, cnt);
-        else
-            hipLaunchKernelGGL(k_level_hist, grid_for(T), dim3(256), 0, s, height, T, cnt);
-        DCHK(hipGetLastError());
-        hcnt.resize(H);
-        DCHK(hipMemcpyAsync(hcnt.data(), cnt, sizeof(int32_t) * H, hipMemcpyDeviceToHost, s));
-        DCHK(hipStreamSynchronize(s));
-        res.tree_internal = T - hcnt[0];  // a token of height 0 is a terminal
+    res.max_height = hs->max_height;
+    res.max_stack = hs->max_stack;
+    res.max_var = hs->max_var;
+    H = res.max_height + 1;
+    if (!small || H > kLvlBins) {
         std::vector<int32_t> start(H + 1, 0);
-        for (int64_t h = 0; h < H; ++h) start[h + 1] = start[h] + hcnt[h];
-        DCHK(hipMemcpyAsync(cnt, start.data(), sizeof(int32_t) * H, hipMemcpyHostToDevice, s));
-        DCHK(pool.alloc((void **)&list, sizeof(int32_t) * T));
-        if (lds)
-            hipLaunchKernelGGL(k_level_scatter_lds, grid_for(T, 256 * kLvlPer), dim3(256), 0, s, height,
-                               T, (int32_t)H, cnt, list);
-        else
+        if (H <= kLvlBins) {
+            for (int64_t h = 0; h < H; ++h) start[h + 1] = start[h] + hs->cnt[h];
+            hipLaunchKernelGGL(k_level_scatter_lds, grid_for(T, 256 * kLvlPer), dim3(256), 0, s, height, T, st, list);
+            DCHK(hipGetLastError());
+        } else {
+            // very tall trees: counters in global memory, one per level
+            std::vector<int32_t> hcnt(H);
+            DCHK(pool.alloc((void **)&cnt, sizeof(int32_t) * H));
+            hipLaunchKernelGGL(k_fill, grid_for(H), dim3(256), 0, s, cnt, H, 0);
+            if (small)
+                hipLaunchKernelGGL(k_fill, dim3((unsigned)std::min<uint64_t>(1024, cap / 1024)), dim3(256), 0, s, table,
+                                   (int64_t)cap, -1);
+            hipLaunchKernelGGL(k_level_hist, grid_for(T), dim3(256), 0, s, height, T, cnt);
+            DCHK(hipGetLastError());
+            DCHK(hipMemcpyAsync(hcnt.data(), cnt, sizeof(int32_t) * H, hipMemcpyDeviceToHost, s));
+            DCHK(hipStreamSynchronize(s));
+            for (int64_t h = 0; h < H; ++h) start[h + 1] = start[h] + hcnt[h];
+            DCHK(hipMemcpyAsync(cnt, start.data(), sizeof(int32_t) * H, hipMemcpyHostToDevice, s));
             hipLaunchKernelGGL(k_level_scatter, grid_for(T), dim3(256), 0, s, height, T, cnt, list);
-        DCHK(hipGetLastError());
-        DCHK(pool.alloc((void **)&canon, sizeof(int32_t) * T));
-        DCHK(pool.alloc((void **)&table, sizeof(int32_t) * cap));
-        DCHK(hipMemsetAsync(table, 0xff, sizeof(int32_t) * cap, s));
+            DCHK(hipGetLastError());
+        }
+        res.tree_internal = T - (start[1] - start[0]);  // a token of height 0 is a terminal
         for (int64_t h = 0; h < H; ++h) {
-            const int32_t n = hcnt[h];
-            if (!n) continue;
-            const int32_t *lst = list + start[h];
-            hipLaunchKernelGGL(k_hash_insert, grid_for(n), dim3(256), 0, s, lst, n, tok, kid, canon,
-                               table, (uint64_t)(cap - 1), g_debug_hash_bits, commute, rewrite);
-            hipLaunchKernelGGL(k_hash_resolve, grid_for(n), dim3(256), 0, s, lst, n, tok, kid,
-                               canon, table, (uint64_t)(cap - 1), g_debug_hash_bits, commute, rewrite, st);
+            const int32_t n = start[h + 1] - start[h];
+            if (n > 0)
+                hipLaunchKernelGGL(k_hash_level, grid_for(n), dim3(256), 0, s, list + start[h], n, tok, kid, canon,
+                                   table, (uint64_t)(cap - 1), g_debug_hash_bits, commute, rewrite);
         }
+        hipLaunchKernelGGL(k_rank, dim3((unsigned)nb), dim3(256), 0, s, canon, T, table, pos, sums);
+        hipLaunchKernelGGL(k_rank_blocks, dim3(1), dim3(1024), 0, s, sums, nb, st);
+        hipLaunchKernelGGL(k_emit_nodes, grid_for(std::max(T, R)), dim3(256), 0, s, tok, canon, pos, sums, height, T,
+                           root_tok, R, blob, st);
+        hipLaunchKernelGGL(k_emit_edges, grid_for(T, kEmitBlock), dim3(kEmitBlock), 0, s, canon, pos, sums, kid, T,
+                           blob, st);
         DCHK(hipGetLastError());
-        hipLaunchKernelGGL(k_class_to_token, grid_for(T), dim3(256), 0, s, canon, T, table);
-        DCHK(hipGetLastError());
-        DCHK(pool.alloc((void **)&flag, sizeof(int32_t) * T));
-        DCHK(pool.alloc((void **)&pos, sizeof(int32_t) * T));
-        hipLaunchKernelGGL(k_flags, grid_for(T), dim3(256), 0, s, canon, T, flag);
-        DCHK(exclusive_scan(flag, pos, T, s));
-        int32_t last[2] = {0, 0};
-        DCHK(hipMemcpyAsync(&last[0], pos + T - 1, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        DCHK(hipMemcpyAsync(&last[1], flag + T - 1, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        DCHK(hipMemcpyAsync(&hs, st, sizeof(hs), hipMemcpyDeviceToHost, s));
+        DCHK(ctx_pinned(ctx, kBlobHead, &stage));
+        hs = static_cast<BuildStatus *>(stage);
+        DCHK(hipMemcpyAsync(hs, st, offsetof(BuildStatus, cnt), hipMemcpyDeviceToHost, s));
         DCHK(hipStreamSynchronize(s));
-        if (hs.lost_key) {
-            res.status = TGP_EHIP;
-            snprintf(err, errlen, "hash-consing found no table slot for a subtree (internal error)");
-            goto done;
-        }
-        U = (int64_t)last[0] + last[1];
-        res.U = U;
-        dev->U = U;
-        // One block, in the order of DagDevice::blob_bytes: op, value, kid[3],
-        // height, mult, indeg (U each), roots (R).
-        DCHK(pool.alloc((void **)&dev->blob, DagDevice::blob_bytes(U, R)));
-        dev->node_op = dev->blob;
-        dev->node_value = reinterpret_cast<float *>(dev->blob + U);
-        dev->node_kid = dev->blob + 2 * U;
-        dev->node_height = dev->blob + 5 * U;
-        dev->mult = dev->blob + 6 * U;
-        dev->indeg = dev->blob + 7 * U;
-        dev->roots = dev->blob + 8 * U;
-        DCHK(hipMemsetAsync(dev->mult, 0, sizeof(int32_t) * 2 * U, s));
-        hipLaunchKernelGGL(k_emit_nodes, grid_for(T), dim3(256), 0, s, tok, canon, pos, height, T,
-                           dev->node_op, dev->node_value, dev->node_height);
-        hipLaunchKernelGGL(k_emit_edges, grid_for(T, kEmitBlock), dim3(kEmitBlock), 0, s, canon, pos, kid, T,
-                           dev->node_kid, dev->indeg, dev->mult);
-        hipLaunchKernelGGL(k_emit_roots, grid_for(R), dim3(256), 0, s, root_tok, canon, pos, R,
-                           dev->roots);
-        DCHK(hipGetLastError());
+        const size_t bytes = DagDevice::blob_bytes(hs->nodes, R);
+        res.U = hs->nodes;
+        DCHK(ctx_pinned(ctx, bytes, &stage));
+        DCHK(hipMemcpyAsync(stage, blob, bytes, hipMemcpyDeviceToHost, s));
+        DCHK(hipStreamSynchronize(s));
+        *host = static_cast<const int32_t *>(stage);
+    } else {
+        res.U = hs->nodes;
+        res.tree_internal = T - hs->cnt[0];
+        *host = reinterpret_cast<const int32_t *>(static_cast<char *>(stage) + kBlobHead);
     }
+    dev->U = res.U;
+    dev->node_op = blob;
+    dev->node_value = reinterpret_cast<float *>(blob + res.U);
+    dev->node_kid = blob + 2 * res.U;
+    dev->node_height = blob + 5 * res.U;
+    dev->mult = blob + 6 * res.U;
+    dev->indeg = blob + 7 * res.U;
+    dev->roots = blob + 8 * res.U;
 done:
-    hipStreamSynchronize(s);  // every kernel that used the scratch has finished
-    pool.release(kid);
-    pool.release(height);
-    pool.release(stk);
-    pool.release(root_tok);
+    if (res.status != TGP_OK) {
+        hipStreamSynchronize(s);  // every kernel that used the scratch has finished
+        dag_device_free(dev, pool);
+    }
     pool.release(st);
-    pool.release(info);
+    pool.release(scratch);
     pool.release(cnt);
-    pool.release(list);
-    pool.release(canon);
-    pool.release(table);
-    pool.release(flag);
-    pool.release(pos);
-    if (res.status != TGP_OK) dag_device_free(dev, pool);
     return res;
 }
 

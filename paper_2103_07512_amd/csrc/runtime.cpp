@@ -415,15 +415,7 @@ tgp_status tgp_build_dag(tgp_ctx ctx, const tgp_population *pop, tgp_dag *out) {
             off_dev = off_own;
             tok_dev = tok_own;
         } else {
-            int64_t ends[2];
-            HCHK(ctx, hipMemcpyAsync(&ends[0], pop->offsets, sizeof(int64_t), hipMemcpyDeviceToHost,
-                                     ctx->stream));
-            HCHK(ctx, hipMemcpyAsync(&ends[1], pop->offsets + R, sizeof(int64_t),
-                                     hipMemcpyDeviceToHost, ctx->stream));
-            HCHK(ctx, hipStreamSynchronize(ctx->stream));
-            if (ends[0] != 0) return fail(ctx, TGP_EINVAL, "offsets[0] must be 0");
-            T = ends[1];
-            if (T < 0 || T > 0x7fffffffLL) return fail(ctx, TGP_EINVAL, "bad token count");
+            T = -1;  // read from offsets[R] by the build
             off_dev = pop->offsets;
             tok_dev = pop->tokens;
         }
@@ -436,9 +428,8 @@ tgp_status tgp_build_dag(tgp_ctx ctx, const tgp_population *pop, tgp_dag *out) {
     d->stats.max_var = -1;
     if (R > 0) {
         char msg[256] = "";
-        DagBuildResult br =
-            build_dag_device(tok_dev, off_dev, R, T, &d->dev, ctx->pool, ctx->stream, msg, sizeof msg,
-                             ctx->commute != 0, ctx->rewrite != 0);
+        const int32_t *h = nullptr;
+        DagBuildResult br = build_dag_device(ctx, tok_dev, off_dev, R, T, &d->dev, &h, msg, sizeof msg);
         ctx->pool.release(off_own);  // build_dag_device has synchronised the stream
         if (br.status != TGP_OK) {
             delete d;
@@ -453,28 +444,14 @@ tgp_status tgp_build_dag(tgp_ctx ctx, const tgp_population *pop, tgp_dag *out) {
         d->roots.resize(R);
         d->mult.resize(U);
         d->indeg.resize(U);
-        // one readback of the whole DAG block through the pinned staging
-        const size_t bytes = DagDevice::blob_bytes(U, R);
-        void *stage = nullptr;
-        hipError_t e = ctx_pinned(ctx, bytes, &stage);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(stage, d->dev.blob, bytes, hipMemcpyDeviceToHost, ctx->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-        if (e == hipSuccess) {
-            const int32_t *h = static_cast<const int32_t *>(stage);
-            memcpy(d->op.data(), h, sizeof(int32_t) * U);
-            memcpy(d->value.data(), h + U, sizeof(float) * U);
-            memcpy(d->kid.data(), h + 2 * U, sizeof(int32_t) * 3 * U);
-            memcpy(d->height.data(), h + 5 * U, sizeof(int32_t) * U);
-            memcpy(d->mult.data(), h + 6 * U, sizeof(int32_t) * U);
-            memcpy(d->indeg.data(), h + 7 * U, sizeof(int32_t) * U);
-            memcpy(d->roots.data(), h + 8 * U, sizeof(int32_t) * R);
-        }
-        if (e != hipSuccess) {
-            tgp_dag_destroy(d);
-            return fail(ctx, TGP_EHIP, "DAG readback: %s", hipGetErrorString(e));
-        }
-        d->stats.tree_nodes = T;
+        memcpy(d->op.data(), h, sizeof(int32_t) * U);
+        memcpy(d->value.data(), h + U, sizeof(float) * U);
+        memcpy(d->kid.data(), h + 2 * U, sizeof(int32_t) * 3 * U);
+        memcpy(d->height.data(), h + 5 * U, sizeof(int32_t) * U);
+        memcpy(d->mult.data(), h + 6 * U, sizeof(int32_t) * U);
+        memcpy(d->indeg.data(), h + 7 * U, sizeof(int32_t) * U);
+        memcpy(d->roots.data(), h + 8 * U, sizeof(int32_t) * R);
+        d->stats.tree_nodes = br.T;
         d->stats.tree_internal = br.tree_internal;
         d->stats.dag_nodes = U;
         int64_t di = 0, sh = 0;

@@ -238,6 +238,16 @@ struct tgp_dag_s : DagArrays {  // host copies
     Plan plan;
 };
 
+namespace tgp {
+// Builds the DAG of R trees given device tokens and offsets under the
+// context's hashing settings (T < 0: the token count is offsets[R], read from
+// the device and checked).  The device arrays come from the context's pool
+// (given back with dag_device_free once the stream has passed every use);
+// *host is a copy of them in the context's pinned staging.  Blocks.
+DagBuildResult build_dag_device(tgp_ctx ctx, const tgp_token *tok_dev, const int64_t *off_dev, int64_t R, int64_t T,
+                                DagDevice *dev, const int32_t **host, char *err, size_t errlen);
+}  // namespace tgp
+
 // ------------------------------------------------------------------ errors
 tgp_status fail(tgp_ctx ctx, tgp_status st, const char *fmt, ...);
 

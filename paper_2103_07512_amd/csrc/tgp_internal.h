@@ -348,7 +348,7 @@ struct DevicePool {
 // DAG construction kernels (k_dag.hip).
 struct DagDevice {
     int64_t T = 0, R = 0, U = 0;
-    int32_t *blob = nullptr;         // one pool block holding every array below
+    char *block = nullptr;           // one pool block holding every array below
     int32_t *node_op = nullptr;      // packed per node: op | var << 8
     float *node_value = nullptr;
     int32_t *node_kid = nullptr;     // [U][3]
@@ -356,6 +356,7 @@ struct DagDevice {
     int32_t *roots = nullptr;        // [R]
     int32_t *mult = nullptr;         // [U]
     int32_t *indeg = nullptr;        // [U]
+    // the arrays in the order op, value, kid, height, mult, indeg, roots
     static size_t blob_bytes(int64_t U, int64_t R) { return sizeof(int32_t) * (8 * U + R); }
 };
 
@@ -365,15 +366,6 @@ struct DagBuildResult {
     int64_t T, U, max_height, max_stack, max_var, tree_internal;
 };
 
-// Builds the DAG of R trees given device tokens/offsets; allocates the dev
-// arrays from the pool (returned with dag_device_free once the stream has
-// passed every use).
-// commute: identify nodes of operators whose operands commute by the
-// unordered pair of their children; rewrite: apply the identity rewrites
-// (tgp_ctx_set_rewrite).
-DagBuildResult build_dag_device(const tgp_token *tok_dev, const int64_t *off_dev, int64_t R,
-                                int64_t T, DagDevice *dev, DevicePool &pool, hipStream_t s,
-                                char *err, size_t errlen, bool commute, bool rewrite);
 void dag_device_free(DagDevice *dev, DevicePool &pool);
 
 }  // namespace tgp
