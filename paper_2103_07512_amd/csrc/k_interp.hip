@@ -79,6 +79,12 @@ __device__ __forceinline__ float row_load(const Row &row, uint32_t off, uint32_t
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(row.r, off, soff, 0));
 }
 
+// v in a vector register (a value the compiler would keep in a scalar one).
+__device__ __forceinline__ float to_vector(float v) {
+    asm("" : "+v"(v));
+    return v;
+}
+
 // Where a tile of the wide form reads: its one grid row's entry of the row
 // table (subtree 0), its first column's offset, its cases.
 template <int K>

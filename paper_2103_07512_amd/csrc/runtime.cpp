@@ -1227,6 +1227,19 @@ struct Planner {
                     const int fv = order[1] ? kOpForms.forward[o] : kOpForms.backward[o];
                     uint32_t y = 0;
                     const int kind = fv >= 0 ? fuse_operand(f.kid[1], y, uc) : -1;
+                    // two table values: a pair form
+                    const int32_t c0 = f.kid[0];
+                    if (kind >= 0 && uc == 3 && value(c0) && in_table(c0) && in_table(f.kid[1]) &&
+                        cls[c0] != cls[f.kid[1]] && std::max(slot[c0], slot[f.kid[1]]) < 65536) {
+                        // the row-table value is the first operand, unless it
+                        // is child 1
+                        const int32_t rc = cls[c0] == 1 ? c0 : f.kid[1], cc = cls[c0] == 1 ? f.kid[1] : c0;
+                        const bool rev = k[0] != rc && !is_commutative(o);
+                        put(kPairBase + (uint32_t)fused_index(o, rev), (uint32_t)slot[cc] << 16 | (uint32_t)slot[rc]);
+                        slots += 2.0;
+                        ++S;
+                        return;
+                    }
                     if (kind >= 0) {
                         f.fv = (int8_t)fv;
                         f.kind = (uint8_t)kind;

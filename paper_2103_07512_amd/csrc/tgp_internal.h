@@ -66,6 +66,11 @@ __host__ __device__ constexpr int arity_of(uint32_t op) { return (int)((kArityPa
 // S reads slot S - 1 and writes it.
 // In a wide or ragged program (JobDesc, below) I_X / kFuseX read row .y of the grid-row
 // table and I_Y / kFuseY row .y of the column table instead of a coordinate.
+// Pair forms, only there: a binary operator of one value of either table, code
+// kPairBase + v, .y = column-table row << 16 | row-table row (an operator whose
+// rows do not fit 16 bits takes the fused form); not reversed means the
+// row-table value is the operator's first operand.  A pair form at depth S
+// writes slot S.
 enum : uint32_t {
     I_X = 0, I_Y = 1, I_Z = 2, I_CONST = 3, I_CACHE = 4, I_END = 5,
     I_WARP = 6,  // pops t0, t1; pushes cache row .y at the point they name
@@ -74,6 +79,7 @@ enum : uint32_t {
     kPermBase = 72,
     kFuseBase = 96,
     kFuseX = 0, kFuseY = 1, kFuseConst = 2, kFuseCache = 3,
+    kPairBase = 160,
 };
 constexpr int kNumFused = 14;
 constexpr int kFuseOps[kNumFused] = {TGP_ADD, TGP_SUB, TGP_MULT, TGP_DIV, TGP_POW, TGP_MIN,  TGP_MAX,

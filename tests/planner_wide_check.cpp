@@ -17,14 +17,43 @@
 
 namespace {
 
-// A program with its table operands turned into cache reads: the cache rows
-// are followed by the row table's entries, then the column table's.
+int64_t g_pairs = 0;
+
+// The plan with its table operands turned into cache reads: the cache rows
+// are followed by the row table's entries, then the column table's.  A pair
+// form becomes two instructions, so the programs move: their descriptors are
+// translated too.
 Plan with_tables_as_rows(const Plan &P) {
     Plan Q;
-    Q.code_host = P.code_host;
-    for (size_t i = (size_t)P.tab_code_end; i < Q.code_host.size(); ++i) {
+    Q.fill_host = P.fill_host;
+    Q.reduce_host = P.reduce_host;
+    Q.store_host = P.store_host;
+    const uint32_t at[2] = {(uint32_t)P.n_slots, (uint32_t)(P.n_slots + P.n_tab[0])};
+    std::vector<uint32_t> moved(P.code_host.size() + 1);
+    for (size_t i = 0; i < P.code_host.size(); ++i) {
+        moved[i] = (uint32_t)Q.code_host.size();
+        const uint2 w = P.code_host[i];
+        const uint32_t c = w.x & 0xffu, S = w.x >> 8;
+        if (i >= (size_t)P.tab_code_end && c >= kPairBase) {
+            const uint32_t v = c - kPairBase, row = at[0] + (w.y & 0xffffu), col = at[1] + (w.y >> 16);
+            ++g_pairs;
+            // push one operand, the fused form reads the other as the last child
+            Q.code_host.push_back(uint2{(S << 8) | I_CACHE, row});
+            Q.code_host.push_back(uint2{((S + 1) << 8) | (kFuseBase + 16 * kFuseCache + v), col});
+            continue;
+        }
+        Q.code_host.push_back(w);
+    }
+    moved[P.code_host.size()] = (uint32_t)Q.code_host.size();
+    for (auto *list : {&Q.fill_host, &Q.reduce_host, &Q.store_host})
+        for (ProgDesc &pd : *list) {
+            const uint32_t end = moved[pd.code_off + pd.len];
+            pd.code_off = moved[pd.code_off];
+            pd.len = end - pd.code_off;
+        }
+    for (size_t i = moved[P.tab_code_end]; i < Q.code_host.size(); ++i) {
         uint2 &ins = Q.code_host[i];
-        const uint32_t c = ins.x & 0xffu, at[2] = {(uint32_t)P.n_slots, (uint32_t)(P.n_slots + P.n_tab[0])};
+        const uint32_t c = ins.x & 0xffu;
         if (c == I_X || c == I_Y) {
             ins.y += at[c == I_X ? 0 : 1];
             ins.x = (ins.x & ~0xffu) | I_CACHE;
@@ -89,7 +118,7 @@ void check_wide(const char *what, tgp_dag_s &d, PlanJob &w, int D, int split, in
                 }
             if (l + 1 >= (int)P.level_first.size()) continue;
             for (int32_t i = P.level_first[l]; i < P.level_first[l + 1]; ++i) {
-                const ProgDesc &pd = P.fill_host[i];
+                const ProgDesc &pd = Q.fill_host[i];
                 float v;
                 const bool ok = run(Q, pd, D, NAN, NAN, all(), &v, nullptr);
                 const int32_t node = P.slot_node[pd.dest];
@@ -99,7 +128,7 @@ void check_wide(const char *what, tgp_dag_s &d, PlanJob &w, int D, int split, in
         }
         const std::vector<float> c = all();
         for (int pass = 0; pass < 2; ++pass)
-            for (const ProgDesc &pd : pass ? P.store_host : P.reduce_host) {
+            for (const ProgDesc &pd : pass ? Q.store_host : Q.reduce_host) {
                 float v;
                 const bool ok = run(Q, pd, D, NAN, NAN, c, &v, nullptr);
                 const int32_t node = pass ? d.roots[pd.dest] : w.reduce_list[pd.dest].first;
@@ -174,6 +203,8 @@ int main() {
         if (spills[0] == spills[1])
             CHECK(cached[0] == cached[1] && level[0] == level[1], "U=%lld: passes differ\n", (long long)U);
     }
+    printf("%lld pair forms\n", (long long)g_pairs);
+    CHECK(g_pairs > 0, "no pair form emitted\n");
     if (g_bad) {
         printf("%d failures\n", g_bad);
         return 1;
