@@ -55,16 +55,24 @@ constexpr float kC0 = -4.934802055358887f, kC1 = 4.0587077140808105f, kC2 = -1.3
 // exact in FP32: r = a - 2 rint(a/2) is exact (a and 2 rint(a/2) are
 // multiples of ulp(a) at most 1 apart; every FP32 value of magnitude
 // >= 2^24 is even, so r = 0 there), and t = r - n/2 likewise.  Returns
-// sin(pi t) and cos(pi t) and the quadrant q = n mod 4.  A non-finite a
-// gives NaN polynomials (and q = 2, unused).
+// sin(pi t) and cos(pi t) and q, whose two low bits are the quadrant n mod 4.
+// n comes from adding 3 2^22 to 2r, which rounds it to an integer (to even,
+// as rint does) in the sum's low bits, so q needs no conversion.  A
+// non-finite a gives NaN polynomials (and an unused q).
 TGP_HD inline void sincospi_core(float a, float &sp, float &cp, uint32_t &q) {
     const float r = fmaf(-2.0f, rintf(0.5f * a), a);
-    const float n = rintf(2.0f * r);
+    const float shifted = 2.0f * r + 12582912.0f;
+    const float n = shifted - 12582912.0f;
     const float t = fmaf(-0.5f, n, r);
     const float z = t * t;
     sp = t * fmaf(fmaf(fmaf(kS3, z, kS2), z, kS1), z, kS0);
     cp = fmaf(z, fmaf(fmaf(fmaf(kC3, z, kC2), z, kC1), z, kC0), 1.0f);
-    q = (uint32_t)(int32_t)fmaxf(n, -2.0f) & 3u;  // fmaxf: NaN gives -2, a defined conversion
+    q = float_to_bits(shifted);  // 3 2^22 + n: its low bits are n's
+}
+
+// v's bits where the mask is set, else w's.
+TGP_HD inline float pick(uint32_t mask, float v, float w) {
+    return bits_to_float((float_to_bits(v) & mask) | (float_to_bits(w) & ~mask));
 }
 
 // sin(pi a); zeros are +0 (at a = k exactly; +0 is added last).
@@ -72,7 +80,7 @@ TGP_HD inline float sinpi_f32(float a) {
     float sp, cp;
     uint32_t q;
     sincospi_core(a, sp, cp, q);
-    const float v = (q & 1u) ? cp : sp;
+    const float v = pick(0u - (q & 1u), cp, sp);
     return flip_sign(v, (q & 2u) << 30) + 0.0f;
 }
 
@@ -81,7 +89,7 @@ TGP_HD inline float cospi_f32(float a) {
     float sp, cp;
     uint32_t q;
     sincospi_core(a, sp, cp, q);
-    const float v = (q & 1u) ? sp : cp;
+    const float v = pick(0u - (q & 1u), sp, cp);
     return flip_sign(v, ((q + 1u) & 2u) << 30) + 0.0f;
 }
 
