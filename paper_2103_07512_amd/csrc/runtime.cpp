@@ -1543,8 +1543,35 @@ static void plan_prepare(PlanJob &w, bool fold, int threads = 1) {
     w.pl.folded.swap(use);
 }
 
-// Folds the marked subtrees of every job: one upload of the node lists, one
-// launch per height over all jobs, one read-back of the values.
+// Folds one job's marked subtrees in one launch that reads the node list from,
+// and writes the values to, the pinned staging.
+static hipError_t fold_one(tgp_ctx ctx, PlanJob &w) {
+    const int32_t n = (int32_t)w.fold_list.size(), heights = (int32_t)w.fold_first.size() - 1;
+    const int64_t U = w.d->stats.dag_nodes;
+    void *pos = nullptr, *stage = nullptr;
+    hipError_t e = ctx->pool.alloc(&pos, sizeof(int32_t) * U);
+    if (e == hipSuccess) e = ctx_pinned(ctx, sizeof(int32_t) * (2 * (size_t)n + heights + 1), &stage);
+    if (e == hipSuccess) {
+        int32_t *list = static_cast<int32_t *>(stage), *first = list + n;
+        float *out = reinterpret_cast<float *>(first + heights + 1);
+        memcpy(list, w.fold_list.data(), sizeof(int32_t) * n);
+        memcpy(first, w.fold_first.data(), sizeof(int32_t) * (heights + 1));
+        e = launch_fold_all(FoldDesc{w.d->dev.node_op, w.d->dev.node_value, w.d->dev.node_kid, static_cast<float *>(pos)},
+                            list, n, first, heights, out, ctx->stream);
+        const hipError_t es = hipStreamSynchronize(ctx->stream);
+        if (e == hipSuccess) e = es;
+        if (e == hipSuccess) {
+            w.pl.fold_val.resize(U);
+            for (int32_t i = 0; i < n; ++i) w.pl.fold_val[w.fold_list[i]] = out[i];
+        }
+    }
+    ctx->pool.release(pos);
+    return e;
+}
+
+// Folds the marked subtrees of every job.  A single DAG's few nodes: one
+// launch (fold_one).  Otherwise one upload of the node lists, one launch per
+// height over all jobs, one read-back of the values.
 static tgp_status fold_run(tgp_ctx ctx, const std::vector<PlanJob *> &jobs) {
     std::vector<PlanJob *> fj;
     size_t n_list = 0, n_val = 0;
@@ -1559,6 +1586,11 @@ static tgp_status fold_run(tgp_ctx ctx, const std::vector<PlanJob *> &jobs) {
             fj.push_back(w);
         }
     if (fj.empty()) return TGP_OK;
+    if (fj.size() == 1 && n_list <= (size_t)kFoldNodes && max_h < kFoldHeights) {
+        const hipError_t e1 = fold_one(ctx, *fj[0]);
+        if (e1 != hipSuccess) return fail(ctx, TGP_EHIP, "constant folding: %s", hipGetErrorString(e1));
+        return TGP_OK;
+    }
     // the (job, node) lists of all jobs ordered by height, then job
     std::vector<int32_t> hfirst(max_h + 2, 0);
     for (PlanJob *w : fj)

@@ -266,6 +266,13 @@ struct FoldDesc {
     float *val;
 };
 hipError_t launch_fold_level(const FoldDesc *jobs, const int2 *list, int32_t n, hipStream_t s);
+// The same for one DAG in one launch: n nodes, those of height h from first[h];
+// list, first and out (a value per list entry) may be in pinned host memory.
+// d.val is overwritten.  At most kFoldNodes (their operands and values fill the
+// 64 KB of LDS that need no attribute) and kFoldHeights.
+constexpr int32_t kFoldNodes = 2048, kFoldHeights = 1024;
+hipError_t launch_fold_all(const FoldDesc &d, const int32_t *list, int32_t n, const int32_t *first, int32_t heights,
+                           float *out, hipStream_t s);
 hipError_t launch_finalize_batch(const FinJob *jobs, const int32_t *n_jobs, const uint32_t *n_ind,
                                  int32_t grid, hipStream_t s);
 // Genetic operators (k_breed.hip).  A child tree is the first parent's
