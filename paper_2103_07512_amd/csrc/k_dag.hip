@@ -384,6 +384,38 @@ __global__ __launch_bounds__(256) void k_hash_level(const int32_t *list, int32_t
     hash_token(i < n ? list[i] : -1, tok, kid, canon, table, mask, hash_bits, commute, rewrite);
 }
 
+// Levels h0 .. H - 1, listed from `first` on, by one workgroup with a barrier
+// after each (the vector cache is its compute unit's; classes are plain
+// stores, and what an atomic did to the table is waited for).  The upper
+// levels of a population's trees hold few tokens: a launch each is some 6 us
+// for work below 3.  Levels of up to 1024 tokens, one a thread: the build of 500
+// bred trees (9.7 k tokens) took 175 us with a launch per level and 156 us with
+// this, 300 trees of three axes 190 and 178 us, 200 trees to depth 10 253 and
+// 244 us (268 with levels of up to 2048; up to 512 is as 1024).
+constexpr int32_t kRestTokens = 1024;
+constexpr int kRestThreads = 1024;
+
+__global__ __launch_bounds__(kRestThreads) void k_hash_rest(const int32_t *list, int32_t first, int32_t h0, int32_t H,
+                                                            const BuildStatus *st, const uint2 *tok,
+                                                            const int32_t *kid, int32_t *canon, int32_t *table,
+                                                            uint64_t mask, uint32_t hash_bits, bool commute,
+                                                            bool rewrite) {
+    __shared__ int32_t cnt[kLvlBins];
+    const int tid = threadIdx.x, wave = tid >> 6;
+    for (int h = h0 + tid; h < H; h += kRestThreads) cnt[h] = st->cnt[h];
+    __syncthreads();
+    for (int32_t h = h0; h < H; ++h) {
+        const int32_t n = cnt[h];
+        for (int32_t i0 = 0; i0 < n; i0 += kRestThreads)  // whole waves take part
+            if (i0 + wave * 64 < n)
+                hash_token(i0 + tid < n ? list[first + i0 + tid] : -1, tok, kid, canon, table, mask, hash_bits,
+                           commute, rewrite);
+        first += n;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+    }
+}
+
 __global__ void k_fill(int32_t *p, int64_t n, int32_t v) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         p[i] = v;
@@ -849,12 +881,19 @@ DagBuildResult build_dag_device(tgp_ctx ctx, const tgp_token *tok_dev, const int
             DCHK(hipGetLastError());
         }
         res.tree_internal = T - (start[1] - start[0]);  // a token of height 0 is a terminal
-        for (int64_t h = 0; h < H; ++h) {
+        // a launch for each of the large levels, one for the rest
+        int64_t h0 = H;
+        if (H <= kLvlBins)
+            while (h0 > 0 && start[h0] - start[h0 - 1] <= kRestTokens) --h0;
+        for (int64_t h = 0; h < h0; ++h) {
             const int32_t n = start[h + 1] - start[h];
             if (n > 0)
                 hipLaunchKernelGGL(k_hash_level, grid_for(n), dim3(256), 0, s, list + start[h], n, tok, kid, canon,
                                    table, (uint64_t)(cap - 1), g_debug_hash_bits, commute, rewrite);
         }
+        if (h0 < H)
+            hipLaunchKernelGGL(k_hash_rest, dim3(1), dim3(kRestThreads), 0, s, list, start[h0], (int32_t)h0, (int32_t)H,
+                               st, tok, kid, canon, table, (uint64_t)(cap - 1), g_debug_hash_bits, commute, rewrite);
         hipLaunchKernelGGL(k_rank, dim3((unsigned)nb), dim3(256), 0, s, canon, T, table, pos, sums);
         hipLaunchKernelGGL(k_rank_blocks, dim3(1), dim3(1024), 0, s, sums, nb, st);
         hipLaunchKernelGGL(k_emit_nodes, grid_for(std::max(T, R)), dim3(256), 0, s, tok, canon, pos, sums, height, T,
