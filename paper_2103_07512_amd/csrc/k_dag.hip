@@ -230,8 +230,9 @@ __device__ __forceinline__ bool commutes(uint32_t op) {
            op == TGP_LEN || op == TGP_OR || op == TGP_XOR || op == TGP_AND;
 }
 
-__device__ __forceinline__ Key key_of(int32_t t, const uint2 *tok, const int32_t *kid,
-                                      const int32_t *canon, bool commute) {
+// (I: the width the children and classes are held at, 16 bits in LDS.)
+template <class I>
+__device__ __forceinline__ Key key_of(int32_t t, const uint2 *tok, const I *kid, const I *canon, bool commute) {
     const uint2 w = tok[t];
     const uint32_t op = w.x & 0xffu;
     Key k{op, 0xffffffffu, 0xffffffffu, 0xffffffffu};
@@ -282,8 +283,9 @@ __device__ __forceinline__ uint64_t key_hash(const Key &k, uint32_t hash_mask_bi
 //   mult(x, 1), mult(1, x) -> x; div(x, 1) -> x.
 // The children are already canonical (lower levels), so a rule sees through
 // earlier rewrites.
-__device__ __forceinline__ int32_t rewrite_target(int32_t t, const uint2 *tok, const int32_t *kid,
-                                                  const int32_t *canon, const int32_t *table) {
+template <class I>
+__device__ __forceinline__ int32_t rewrite_target(int32_t t, const uint2 *tok, const I *kid, const I *canon,
+                                                  const int32_t *table) {
     const uint32_t op = tok[t].x & 0xffu;
     const int a = arity_of(op);
     if (a == 0) return -1;
@@ -314,9 +316,9 @@ __device__ __forceinline__ int32_t rewrite_target(int32_t t, const uint2 *tok, c
 // holding the smallest token index with that key, and is the token's class.
 // A rewritten token is not inserted: its class is the one it stands for.
 // Every lane of the wave calls it (the leaves' ballots).
-__device__ __forceinline__ void hash_token(int32_t t, const uint2 *tok, const int32_t *kid, int32_t *canon,
-                                           int32_t *table, uint64_t mask, uint32_t hash_bits, bool commute,
-                                           bool rewrite) {
+template <class I>
+__device__ __forceinline__ void hash_token(int32_t t, const uint2 *tok, const I *kid, I *canon, int32_t *table,
+                                           uint64_t mask, uint32_t hash_bits, bool commute, bool rewrite) {
     const bool live = t >= 0;
     const Key k = live ? key_of(t, tok, kid, canon, commute) : Key{0xffffffffu, 0, 0, 0};
     const int32_t target = live && rewrite ? rewrite_target(t, tok, kid, canon, table) : -1;
@@ -372,7 +374,7 @@ __device__ __forceinline__ void hash_token(int32_t t, const uint2 *tok, const in
         }
     }
     const int32_t slot = __shfl((int32_t)s, from);
-    if (live) canon[t] = target >= 0 ? target : slot;
+    if (live) canon[t] = (I)(target >= 0 ? target : slot);
 }
 
 // One level of tokens.  (The class needs no second look-up: a key's slot
@@ -579,37 +581,42 @@ __global__ __launch_bounds__(kEmitBlock) void k_emit_edges(const int32_t *canon,
 
 // Steps 2 and 3 for a small population, after k_structure, in one workgroup
 // of 16 waves: level lists, hash-consing level by level, ranks, emission, all
-// separated by workgroup barriers (one compute unit: its vector cache is
-// shared, so plain stores are seen after a barrier; table slots, which
-// atomics write behind it, are read back past it once every wave has waited
-// for its own).  LDS: the count of every node's tokens (low half) and edges
-// (high half, at most three per node).  The head of the blob gets the status;
-// nothing else is written when a tree is malformed or too tall for the bins.
+// separated by workgroup barriers.  What bounds it is the chain of dependent
+// reads of each level (list, children, their classes, the table slot, the
+// slot's token and its children's classes), so all of these but the tokens
+// themselves are in LDS, indexes in 16 bits: 14 bytes a token and 4 a table
+// slot, 148 KB of the 160 at the most.  The counts hold every node's tokens
+// (low half) and edges (high half, at most three per node).  The head of the
+// blob gets the status; nothing else is written when a tree is malformed or
+// too tall for the bins.
 //
 // A population of 50 trees (690 tokens) took 42 launches, copies and fills and
-// five waits, 0.30 ms a build; now three launches, two copies and two waits,
-// 0.084 ms.  At 9.4k tokens one workgroup (0.21 ms a build) loses to a launch
-// per level (0.19 ms; 0.43 before, with two launches per level and a wait
-// for every count), so the line lies between.
-constexpr int64_t kSmallTokens = 6144;  // 24 KB of counts, below 2^16 each
+// five waits, 0.30 ms a build; with one workgroup and two waits 0.078 ms, and
+// 0.065 ms since the indexes are in LDS (5.0 k tokens: 0.164 and 0.122 ms, 5.2 k
+// with image operators 0.136 and 0.092 ms).  The line is the LDS: past 6144
+// tokens the table would have to be denser or stay in memory, where at 9.4 k
+// tokens one workgroup lost to a launch per level (0.21 and 0.19 ms).
+constexpr int64_t kSmallTokens = 6144;
 constexpr int kSmallThreads = 1024;
 
 __global__ __launch_bounds__(kSmallThreads) void k_build_small(const uint2 *tok, int32_t T, const int32_t *kid,
                                                                const int32_t *height, const int32_t *root_tok,
-                                                               const int4 *info, int32_t R, int32_t *list,
-                                                               int32_t *canon, int32_t *pos, int32_t *table,
-                                                               uint32_t mask, uint32_t hash_bits, bool commute,
-                                                               bool rewrite, int32_t *blob, const BuildStatus *st) {
+                                                               const int4 *info, int32_t R, uint32_t mask,
+                                                               uint32_t hash_bits, bool commute, bool rewrite,
+                                                               int32_t *blob, const BuildStatus *st) {
     extern __shared__ uint32_t counts[];  // [T]
+    int32_t *const table = reinterpret_cast<int32_t *>(counts + T);       // [mask + 1]
+    uint16_t *const kids = reinterpret_cast<uint16_t *>(table + mask + 1);  // [3 T], 0xffff for none
+    uint16_t *const canon = kids + 3 * T, *const list = canon + T;        // [T] each
+    uint16_t *const pos = list;  // once the levels are done
     __shared__ int32_t c[kLvlBins], start[kLvlBins + 1], tmp[16];
     __shared__ int32_t most[3];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    auto settle = [] { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
     if (tid < 3) most[tid] = tid < 2 ? 0 : -1;
     for (int i = tid; i < kLvlBins; i += kSmallThreads) c[i] = 0;
     for (uint32_t i = tid; i <= mask; i += kSmallThreads) table[i] = -1;
     for (int i = tid; i < T; i += kSmallThreads) counts[i] = 0;
-    settle();
+    for (int i = tid; i < 3 * T; i += kSmallThreads) kids[i] = (uint16_t)kid[i];
     __syncthreads();
     for (int r = tid; r < R; r += kSmallThreads) {
         const int4 x = info[r];
@@ -642,15 +649,14 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(const uint2 *tok,
     __syncthreads();
     for (int i = tid; i < H; i += kSmallThreads) c[i] = start[i];
     __syncthreads();
-    for (int t = tid; t < T; t += kSmallThreads) list[atomicAdd(&c[height[t]], 1)] = t;
+    for (int t = tid; t < T; t += kSmallThreads) list[atomicAdd(&c[height[t]], 1)] = (uint16_t)t;
     __syncthreads();
     for (int32_t h = 0; h < H; ++h) {
         const int32_t end = start[h + 1];
         for (int32_t i0 = start[h]; i0 < end; i0 += kSmallThreads)  // whole waves take part
             if (i0 + wave * 64 < end)
-                hash_token(i0 + tid < end ? list[i0 + tid] : -1, tok, kid, canon, table, mask, hash_bits, commute,
-                           rewrite);
-        settle();
+                hash_token(i0 + tid < end ? (int32_t)list[i0 + tid] : -1, tok, kids, canon, table, mask, hash_bits,
+                           commute, rewrite);
         __syncthreads();
     }
     // representatives and their ids
@@ -659,8 +665,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(const uint2 *tok,
         const int t = t0 + tid;
         int32_t rep = -1;
         if (t < T) {
-            rep = __hip_atomic_load(&table[canon[t]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            canon[t] = rep;
+            rep = table[canon[t]];
+            canon[t] = (uint16_t)rep;
         }
         const uint64_t m = __ballot(rep == t && t < T);
         if (lane == 0) tmp[wave] = (int32_t)__popcll(m);
@@ -670,7 +676,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(const uint2 *tok,
             if (w < wave) run += tmp[w];
             U += tmp[w];
         }
-        if (t < T) pos[t] = run + (int32_t)__popcll(m & ((1ull << lane) - 1));
+        if (t < T) pos[t] = (uint16_t)(run + (int32_t)__popcll(m & ((1ull << lane) - 1)));
         __syncthreads();
     }
     const NodeArrays A(blob, U);
@@ -680,10 +686,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(const uint2 *tok,
         if (rep != t) continue;
         put_node(A, id, tok[t], height[t]);
         for (int j = 0; j < 3; ++j) {
-            const int32_t k = kid[3 * t + j];
-            const int32_t kid_id = k < 0 ? -1 : pos[canon[k]];
+            const uint32_t k = kids[3 * t + j];
+            const int32_t kid_id = k == 0xffffu ? -1 : pos[canon[k]];
             A.kid[3 * id + j] = kid_id;
-            if (k >= 0) atomicAdd(&counts[kid_id], 1u << 16);
+            if (kid_id >= 0) atomicAdd(&counts[kid_id], 1u << 16);
         }
     }
     for (int r = tid; r < R; r += kSmallThreads) A.roots[r] = pos[canon[root_tok[r]]];
@@ -694,6 +700,9 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(const uint2 *tok,
     }
     if (tid == 0) head->nodes = U;
 }
+
+// Its LDS for T tokens and a table of cap slots.
+static size_t small_lds(int64_t T, uint64_t cap) { return (size_t)(14 * T) + 4 * (size_t)cap; }
 
 // The status and, with a blob, its 8 U + R words (U the nodes found) to pinned
 // memory at out, laid out as a DAG's block.  What a copy would take is the
@@ -819,9 +828,9 @@ DagBuildResult build_dag_device(tgp_ctx ctx, const tgp_token *tok_dev, const int
     DCHK(hipGetLastError());
     if (small) {
         // one workgroup, whose status and arrays are published together
-        hipLaunchKernelGGL(k_build_small, dim3(1), dim3(kSmallThreads), sizeof(uint32_t) * T, s, tok, (int32_t)T, kid,
-                           height, root_tok, info, (int32_t)R, list, canon, pos, table, (uint32_t)(cap - 1),
-                           g_debug_hash_bits, commute, rewrite, blob, st);
+        hipLaunchKernelGGL(k_build_small, dim3(1), dim3(kSmallThreads), small_lds(T, cap), s, tok, (int32_t)T, kid,
+                           height, root_tok, info, (int32_t)R, (uint32_t)(cap - 1), g_debug_hash_bits, commute, rewrite,
+                           blob, st);
         DCHK(hipGetLastError());
         DCHK(ctx_pinned(ctx, kBlobHead + DagDevice::blob_bytes(T, R), &stage));
         hipLaunchKernelGGL(k_publish, publish_grid(T, R), dim3(256), 0, s, reinterpret_cast<BuildStatus *>(dev->block),
