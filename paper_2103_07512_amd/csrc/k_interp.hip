@@ -19,8 +19,8 @@
 // case.  The values are those of the same operators on the same operands and
 // the cases are summed in the flat form's order, so every result keeps its
 // bits.  That population's fitness launch on 1024 x 1024 cases: 55.5 ms flat,
-// 31.6 ms wide, its cache fill 2.9 ms flat, 0.7 ms with the tables (37k
-// subtrees, 0.08 ms); executed instructions 358 G flat, 190 G.  The launch
+// 30.8 ms wide, its cache fill 2.9 ms flat, 0.6 ms with the tables (37k
+// subtrees, 0.08 ms); executed node evaluations 358 G flat, 172 G.  The launch
 // is bound by vector issue in both forms.
 //
 // Fitness form (Sec. 4.1, RMSE against a target): each lane accumulates
@@ -344,15 +344,16 @@ __device__ __forceinline__ void run_item(const Job &a, const uint2 *code, int32_
     if constexpr (MODE == MODE_REDUCE) write_partial(a, ks, kc, dest, stripe, lane);
 }
 
-// Waves per SIMD the plain interpreter asks for.  The fitness form (flat) runs at
-// seven (72 VGPRs): its dispatch chain waits on scalar loads and its cache
-// rows on vector loads, and a seventh resident wave hides more of that than
-// the few values that then live in scratch cost (only the z vector of 3-D
-// domains is reloaded inside the dispatch loop; 1000 x 3 population on
-// 1024^2: 66 ms against 69 ms at six).  The store form (cache fill) keeps
-// six, where it spills less.  The batched kernels hold more descriptor state
-// and spill far more at these counts (measured slower), so they keep the
-// compiler's choice.
+// Waves per SIMD the interpreter asks for.  The fitness form runs at seven (72
+// VGPRs): its dispatch chain waits on scalar loads and its cache rows on
+// vector loads, and a seventh resident wave hides more of that than the few
+// values that then live in scratch cost (1000 x 3 population on 1024^2, flat
+// programs: 66 ms against 69 ms at six).  Table programs hold no coordinates
+// and need 66 (wide) and 70 (ragged) VGPRs, so nothing of theirs is spilled.
+// The store form (cache fill) keeps six, where it spills less.  The batched
+// kernels hold more descriptor state and spill a few values at seven; at six
+// they spill none, one wave per item, but a serving mix took 3.20 ms against
+// 3.09, and a batch of twelve 10.9 against 11.0.
 template <int MODE, int FORM>
 constexpr int min_waves() { return MODE == MODE_REDUCE ? 7 : 6; }
 
