@@ -504,9 +504,11 @@ void tgp_dag_destroy(tgp_dag dag) {
     hipSetDevice(ctx->device);
     hipStreamSynchronize(ctx->stream);  // no queued kernel reads the blocks any more
     dag->plan.release(ctx->pool);
+    dag->other.release(ctx->pool);
     dag_device_free(&dag->dev, ctx->pool);
     if (dag->op.capacity() > ctx->spare_dag.op.capacity()) dag->swap(ctx->spare_dag);
-    if (dag->plan.code_host.capacity() > ctx->spare_code.capacity()) dag->plan.code_host.swap(ctx->spare_code);
+    for (Plan *P : {&dag->plan, &dag->other})
+        if (P->code_host.capacity() > ctx->spare_code.capacity()) P->code_host.swap(ctx->spare_code);
     delete dag;
 }
 
@@ -670,6 +672,18 @@ void height_order(HostTeam *team, const int32_t *hgt, int64_t U, int T, std::vec
     });
 }
 
+// Whether tables of so many entries, each of slots_per cache slots of
+// slot_bytes, may be used: at most half the cache budget, and a 32-bit byte
+// offset into either.  *slots: their size.
+bool tables_fit(const int64_t (&entries)[2], const double (&slots_per)[2], double slot_bytes, size_t budget_slots,
+                size_t *slots) {
+    *slots = (size_t)std::ceil(entries[0] * slots_per[0] + entries[1] * slots_per[1]);
+    if (*slots > budget_slots / 2) return false;
+    for (int q = 0; q < 2; ++q)
+        if (entries[q] * slots_per[q] * slot_bytes >= 0xffffff00u) return false;
+    return true;
+}
+
 struct Planner {
     const tgp_dag_s &d;
     int D;
@@ -703,16 +717,14 @@ struct Planner {
 
     bool in_table(int64_t n) const { return split > 0 && (cls[n] == 1 || cls[n] == 2); }
     int axis(int64_t n) const { return (d.op[n] >> 8) & 0xff; }
-    // the tables' size once every entry is marked; false: over the budget
+    // the tables' size once every entry is marked; false: they do not fit
     bool set_table_slots(const int64_t (&entries)[2]) {
-        const double slots = entries[0] * table_slots_per[0] + entries[1] * table_slots_per[1];
-        table_slots = (size_t)std::ceil(slots);
-        const double row = table_slots_per[0] * slot_bytes, col = table_slots_per[1] * slot_bytes;
-        // 32-bit byte offsets into either table
-        tables_over = table_slots > budget_slots / 2 || entries[0] * row >= 0xffffff00u || entries[1] * col >= 0xffffff00u;
+        for (int q = 0; q < 2; ++q) table_entries[q] = entries[q];
+        tables_over = !tables_fit(entries, table_slots_per, slot_bytes, budget_slots, &table_slots);
         return !tables_over;
     }
     double slot_bytes = 0;               // bytes of a cache slot
+    int64_t table_entries[2] = {0, 0};
 
     // nodes by height (filled by the parallel preparation or decisions)
     std::vector<int32_t> lorder;
@@ -1408,6 +1420,7 @@ struct PlanJob {
     // variable-free nodes by height (folding), this job's place in the batch
     std::vector<int32_t> fold_first, fold_list;
     size_t fold_list_at = 0, fold_val_at = 0;
+    int64_t tab_rows = 0;  // grid rows of the domain at its split
     double t_decide = 0, t_emit = 0;
     std::vector<uint2> code;  // becomes the plan's code
     // fill-program figures carried from the fill emission to the root one
@@ -1665,6 +1678,11 @@ static tgp_status plan_decide_emit_fill(PlanJob &w, int D, bool reorder, double 
     P.asked = pl.split;
     tgp_status st = decide();
     if (st != TGP_OK && pl.tables_over) {  // no room for the tables: flat programs
+        size_t unused;
+        const bool fit = tables_fit(pl.table_entries, pl.table_slots_per, pl.slot_bytes, pl.budget_slots, &unused);
+        // (tables that fit, but not beside the rows that bound the stack: no shape has room for both)
+        for (int q = 0; q < 2; ++q) P.refused[q] = fit ? INT32_MAX : pl.table_entries[q];
+        if (d->other.cases >= 0) return TGP_ENOMEM;  // the flat plan is there already
         pl.split = 0;
         pl.tables_over = false;
         w.err.clear();
@@ -1672,6 +1690,7 @@ static tgp_status plan_decide_emit_fill(PlanJob &w, int D, bool reorder, double 
     }
     if (st != TGP_OK) return st;
     P.split = pl.split;
+    P.tab_rows = w.tab_rows;
     const double t1 = now_ms();
     w.t_decide = t1 - t0;
 
@@ -1926,17 +1945,25 @@ static int32_t wanted_split(tgp_ctx ctx, tgp_dag d, tgp_domain dom) {
     return dom->split;
 }
 
+// Cache slots of an entry of either table on dom split at `split`.
+static void table_slots_on(tgp_domain dom, int32_t split, double (&per)[2]) {
+    const double slot_bytes = sizeof(float) * (double)dom->cases;
+    per[0] = (double)row_table_stride(*dom, split) / slot_bytes;
+    per[1] = (double)col_table_stride(*dom, split) / slot_bytes;
+}
+
 // Gives the planner of w the split `split` of dom.
 static void set_split(PlanJob &w, tgp_domain dom, int32_t split) {
     w.pl.split = split;
     if (!split) return;
+    w.tab_rows = dom->rows(split);
     w.pl.slot_bytes = sizeof(float) * (double)dom->cases;
-    w.pl.table_slots_per[0] = (double)row_table_stride(*dom, split) / w.pl.slot_bytes;
-    w.pl.table_slots_per[1] = (double)col_table_stride(*dom, split) / w.pl.slot_bytes;
+    table_slots_on(dom, split, w.pl.table_slots_per);
 }
 
-// Whether P holds programs for any domain of `cases` cases (a plan with tables
-// runs on any shape).
+// Whether P was made for this number of cases and the context's settings.  A
+// flat plan's programs run on any such domain, a plan's with tables where the
+// tables fit (best_plan).
 static bool plan_current(tgp_ctx ctx, const Plan &P, int64_t cases) {
     return P.cases == cases && P.D == ctx_stack_slots(ctx) && P.reorder == (ctx->reorder != 0) &&
            P.access_cost == ctx->cache_access_cost && P.fold == ctx->fold;
@@ -1946,21 +1973,79 @@ static size_t budget_slots(tgp_ctx ctx, int64_t cases) {
     return (size_t)(ctx->cache_budget / (sizeof(float) * (size_t)std::max<int64_t>(cases, 1)));
 }
 
+static bool tables_fit_on(tgp_ctx ctx, const int64_t (&entries)[2], tgp_domain dom, int32_t split) {
+    double per[2];
+    size_t slots;
+    table_slots_on(dom, split, per);
+    return tables_fit(entries, per, sizeof(float) * (double)dom->cases, budget_slots(ctx, dom->cases), &slots);
+}
+
+// Of d's plans for domains of dom's size, the one to evaluate dom with, or
+// nullptr if that one is not made yet: the one with tables where dom wants
+// them (want, its split) and they fit, else the flat one.  The tables' size
+// follows the grid's shape: a plan made on 1024 x 1024 cases may need hundreds
+// of times as much on 8 x 131072, more than the budget and more than their
+// 32-bit byte offsets reach.  On the shape that they were admitted for they
+// stay as they were planned, like the cache rows.  *tables: which one it is.
+static Plan *best_plan(tgp_ctx ctx, tgp_dag d, tgp_domain dom, int32_t want, bool *tables) {
+    Plan *with = nullptr, *flat = nullptr;
+    for (Plan *P : {&d->plan, &d->other})
+        if (plan_current(ctx, *P, dom->cases)) (P->split ? with : flat) = P;
+    *tables = want > 0;
+    if (want > 0 && with) {
+        const int64_t entries[2] = {with->n_tab[0], with->n_tab[1]};
+        *tables = dom->rows(with->split) == with->tab_rows || tables_fit_on(ctx, entries, dom, with->split);
+    } else if (want > 0 && flat && flat->asked) {
+        *tables = tables_fit_on(ctx, flat->refused, dom, flat->asked);
+    }
+    return *tables ? with : flat;
+}
+
+// Makes the plan to evaluate dom with d's plan in use.  *made: whether it is
+// there; if not, d->plan is empty and *split says what to make (0: a flat plan).
+// The other plan for the same size and settings is kept, so a DAG that is
+// evaluated on several shapes of one size in turn is planned twice at most.
+static tgp_status choose_plan(tgp_ctx ctx, tgp_dag d, tgp_domain dom, int32_t want, bool *made, int32_t *split) {
+    bool tables;
+    Plan *P = best_plan(ctx, d, dom, want, &tables);
+    *made = P != nullptr;
+    *split = tables ? want : 0;
+    if (P) {
+        if (P != &d->plan) std::swap(d->plan, d->other);
+        return TGP_OK;
+    }
+    if (plan_current(ctx, d->plan, dom->cases)) std::swap(d->plan, d->other);
+    for (Plan *Q : {&d->plan, &d->other})
+        if (!plan_current(ctx, *Q, dom->cases)) {
+            if (Q->blob) HCHK(ctx, hipStreamSynchronize(ctx->stream));  // no queued kernel reads it any more
+            Q->release(ctx->pool);
+            *Q = Plan();
+        }
+    return TGP_OK;
+}
+
+// After tables could not be planned beside a flat plan: goes on with the flat
+// plan, for every shape (so that no call plans in vain again).
+static void keep_flat(tgp_dag d) {
+    std::swap(d->plan, d->other);
+    d->plan.asked = d->other.asked;
+    for (int64_t &n : d->plan.refused) n = INT32_MAX;
+    d->other = Plan();
+}
+
 tgp_status build_plan(tgp_ctx ctx, tgp_dag d, tgp_domain dom, const std::function<tgp_status()> &after_fill) {
     const double t0 = now_ms();
     Plan &P = d->plan;
     const int64_t cases = dom->cases;
-    const int32_t split = wanted_split(ctx, d, dom);
-    if (plan_current(ctx, P, cases) && P.asked == split) {
-        tgp_status st = ctx->plan_upload && !P.blob ? plan_upload(ctx, P) : TGP_OK;
+    int32_t split = 0;
+    bool made = false;
+    tgp_status st = choose_plan(ctx, d, dom, wanted_split(ctx, d, dom), &made, &split);
+    if (st != TGP_OK) return st;
+    if (made) {
+        st = ctx->plan_upload && !P.blob ? plan_upload(ctx, P) : TGP_OK;
         ctx->times.plan_ms = now_ms() - t0;
         return st;
     }
-    if (P.blob) {
-        HCHK(ctx, hipStreamSynchronize(ctx->stream));
-        P.release(ctx->pool);
-    }
-    P.cases = -1;
     const int D = ctx_stack_slots(ctx);
     PlanJob w(d, cases, D, budget_slots(ctx, cases));
     set_split(w, dom, split);
@@ -1970,10 +2055,16 @@ tgp_status build_plan(tgp_ctx ctx, tgp_dag d, tgp_domain dom, const std::functio
     w.code.clear();
     plan_prepare(w, ctx->fold != 0, kPlanThreads);
     const double tf0 = now_ms();
-    tgp_status st = fold_run(ctx, {&w});
+    st = fold_run(ctx, {&w});
     if (st != TGP_OK) return st;
     ctx->times.plan_fold_ms = now_ms() - tf0;
     st = plan_decide_emit_fill(w, D, ctx->reorder != 0, ctx->cache_access_cost, ctx->fold, kPlanThreads);
+    if (st != TGP_OK && w.pl.tables_over && d->other.cases >= 0) {
+        keep_flat(d);
+        st = ctx->plan_upload && !P.blob ? plan_upload(ctx, P) : TGP_OK;
+        ctx->times.plan_ms = now_ms() - t0;
+        return st;
+    }
     if (st != TGP_OK) return fail(ctx, st, "%s", w.err.c_str());
     if (ctx->plan_upload) {
         // the fill goes to the device (and, through after_fill, to work)
@@ -2019,19 +2110,16 @@ tgp_status build_plans(tgp_ctx ctx, int32_t n, const tgp_dag *dags, const tgp_do
     }
     const int D = ctx_stack_slots(ctx);
     std::vector<std::unique_ptr<PlanJob>> jobs;
-    bool synced = false;
     for (tgp_dag d : order) {
         const Want &wd = want[d];
         const int64_t c = wd.dom->cases;
-        if (plan_current(ctx, d->plan, c) && d->plan.asked == wd.split) continue;
-        if (d->plan.blob) {
-            if (!synced) HCHK(ctx, hipStreamSynchronize(ctx->stream));
-            synced = true;
-            d->plan.release(ctx->pool);
-        }
-        d->plan.cases = -1;
+        int32_t split = 0;
+        bool made = false;
+        const tgp_status cs = choose_plan(ctx, d, wd.dom, wd.split, &made, &split);
+        if (cs != TGP_OK) return cs;
+        if (made) continue;
         jobs.emplace_back(new PlanJob(d, c, D, budget_slots(ctx, c)));
-        set_split(*jobs.back(), wd.dom, wd.split);
+        set_split(*jobs.back(), wd.dom, split);
     }
     if (jobs.empty()) {
         ctx->times.plan_ms = now_ms() - t0;
@@ -2066,6 +2154,10 @@ tgp_status build_plans(tgp_ctx ctx, int32_t n, const tgp_dag *dags, const tgp_do
         for (auto &w : jobs) w->pl.team = &ctx->team;
     parallel([&](PlanJob &w) {
         w.st = plan_decide_emit(w, D, reorder, access, fold_flag, emit_threads);
+        if (w.st != TGP_OK && w.pl.tables_over && w.d->other.cases >= 0) {
+            keep_flat(w.d);
+            w.st = TGP_OK;
+        }
         if (w.st != TGP_OK) w.d->plan.cases = -1;
     });
     for (auto &w : jobs)
@@ -2352,8 +2444,15 @@ tgp_status tgp_fitness_noalloc(tgp_ctx ctx, tgp_dag d, tgp_domain dom, const flo
     if (ctx->device >= kMaxDevices || !g_scratch_ptr[ctx->device])
         return fail(ctx, TGP_EHIP, "no scratch address for device %d: %s", ctx->device,
                     ctx->device < kMaxDevices ? hipGetErrorString(g_scratch_err[ctx->device]) : "device index");
+    // The best plan if it is on the device, else the other one (the tables of
+    // one that does not fit dom are checked below).
+    bool with_tables;
+    auto ready = [&](const Plan &Q) { return plan_current(ctx, Q, dom->cases) && Q.blob && Q.code_roots_dev; };
+    const Plan *best = best_plan(ctx, d, dom, wanted_split(ctx, d, dom), &with_tables);
+    if (!(best == &d->plan && ready(d->plan)) && ready(d->other) && (best == &d->other || !ready(d->plan)))
+        std::swap(d->plan, d->other);
     const Plan &P = d->plan;
-    if (!plan_current(ctx, P, dom->cases) || !P.blob || !P.code_roots_dev)
+    if (!ready(P))
         return fail(ctx, TGP_EINVAL,
                     "the DAG has no plan for a domain of %lld cases under this context's settings "
                     "(evaluate it once with tgp_fitness or tgp_evaluate)", (long long)dom->cases);

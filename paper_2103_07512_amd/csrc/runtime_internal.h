@@ -159,8 +159,13 @@ struct Plan {
     // Table programs (split > 0): subtrees of the leading axes alone live in the
     // row table, of the trailing axes alone in the column table, the cache
     // slots hold the others.  asked: the split the plan was made for (a plan
-    // whose tables did not fit falls back to flat programs, split = 0).
+    // whose tables did not fit falls back to flat programs, split = 0, and
+    // keeps their entries in refused).  tab_rows: the grid rows of the domain
+    // that the tables were admitted for; their size follows the shape, so on
+    // another shape of the same size they are checked again (best_plan).
     int32_t split = 0, asked = 0;
+    int64_t tab_rows = 0;
+    int64_t refused[2] = {0, 0};
     int32_t n_tab[2] = {0, 0};          // subtrees in the row and column tables
     struct TabLevel {
         int32_t first, mid, last;       // row programs [first, mid), column programs [mid, last)
@@ -235,7 +240,11 @@ struct tgp_dag_s : DagArrays {  // host copies
     DagDevice dev;
     bool image_ops = false;          // a bitwise operator or warp occurs
     std::vector<uint8_t> precached;  // nodes whose values are resident (empty: none)
-    Plan plan;
+    // The plan in use.  other: the flat plan where that one has tables, or the
+    // one with tables where it is flat; both are for one number of cases and
+    // one set of the context's settings, and either stays as it is (a captured
+    // call may read it) until a plan for others is made.
+    Plan plan, other;
 };
 
 namespace tgp {
