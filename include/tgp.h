@@ -298,6 +298,11 @@ tgp_status tgp_fitness(tgp_ctx ctx, tgp_dag dag, tgp_domain dom, const float *ta
  *     64 MiB device array per GPU, held until the process ends; a call that
  *     needs more returns TGP_ENOMEM without launching anything (lower the
  *     cache budget, tgp_ctx_set_cache_budget, before planning to fit).
+ * The tables of subtrees that vary along a part of the axes only (4 bytes per
+ * subtree per grid row or column) may lie there too; where they do not fit,
+ * as on a grid much longer and thinner than the one the DAG was planned for,
+ * the DAG is evaluated without them.  The first such call plans that on the
+ * host, and its programs go to memory that the DAG already holds.
  * Every call on a GPU shares that array, so calls that overlap on one GPU
  * (two streams, or two contexts on the same device) race: order them.
  * Queued on the context's stream; returns without waiting. */

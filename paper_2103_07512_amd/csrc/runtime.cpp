@@ -1421,6 +1421,7 @@ struct PlanJob {
     std::vector<int32_t> fold_first, fold_list;
     size_t fold_list_at = 0, fold_val_at = 0;
     int64_t tab_rows = 0;  // grid rows of the domain at its split
+    size_t budget = 0;     // cache budget in bytes
     double t_decide = 0, t_emit = 0;
     std::vector<uint2> code;  // becomes the plan's code
     // fill-program figures carried from the fill emission to the root one
@@ -1676,6 +1677,7 @@ static tgp_status plan_decide_emit_fill(PlanJob &w, int D, bool reorder, double 
                                                    : pl.decide(w.rootrefs, w.err);
     };
     P.asked = pl.split;
+    P.budget = w.budget;
     tgp_status st = decide();
     if (st != TGP_OK && pl.tables_over) {  // no room for the tables: flat programs
         size_t unused;
@@ -1841,6 +1843,7 @@ static void plan_emit_roots(PlanJob &w, int emit_threads) {
     P.store_host = std::move(store);
     P.ind_rows_host = std::move(w.ind_rows);
     P.cases = w.cases;
+    if (P.split && w.d->ctx && w.d->ctx->plan_upload) P.fold_val.swap(w.pl.fold_val);
     w.t_emit += now_ms() - t0;
 }
 
@@ -1849,6 +1852,26 @@ static tgp_status plan_decide_emit(PlanJob &w, int D, bool reorder, double acces
     tgp_status st = plan_decide_emit_fill(w, D, reorder, access_cost, fold, emit_threads);
     if (st == TGP_OK) plan_emit_roots(w, emit_threads);
     return st;
+}
+
+// Bytes of a flat plan's programs in one block, 256-byte aligned parts.
+static size_t flat_bytes(const Plan &P) {
+    auto up = [](size_t n) { return (n + 255) & ~(size_t)255; };
+    return up(sizeof(uint2) * P.code_host.size()) + up(sizeof(ProgDesc) * P.fill_host.size()) +
+           up(sizeof(ProgDesc) * P.reduce_host.size()) + up(sizeof(ProgDesc) * P.store_host.size()) +
+           up(sizeof(int32_t) * P.ind_rows_host.size());
+}
+
+// What a flat plan of d that tgp_fitness_noalloc can run needs at the most: a
+// cached subtree's program stands where one occurrence of it was in the trees,
+// which is a read now, so the code is no longer than the population's tokens
+// with a read and an end for every row, and an end for every root; and only
+// rows that fit the scratch count.
+static size_t flat_bytes_bound(const tgp_dag_s &d, int64_t cases) {
+    const size_t R = (size_t)d.stats.n_roots,
+                 rows = (size_t)std::min<int64_t>(d.stats.dag_internal, kNoAllocScratchBytes / (4 * std::max<int64_t>(cases, 1)));
+    return sizeof(uint2) * ((size_t)d.stats.tree_nodes + 2 * rows + R + 2) + sizeof(ProgDesc) * (rows + 2 * R) +
+           sizeof(int32_t) * R + 5 * 256;
 }
 
 // Copies n parts into one new pool block (256-byte aligned parts) by one copy
@@ -1908,7 +1931,7 @@ static tgp_status plan_upload_fill(tgp_ctx ctx, Plan &P) {
 
 // The root programs: the rest of code_host, the reduce and store descriptors
 // (offsets rebased to the start of that code) and the individual rows.
-static tgp_status plan_upload_roots(tgp_ctx ctx, Plan &P) {
+static tgp_status plan_upload_roots(tgp_ctx ctx, tgp_dag d, Plan &P) {
     const uint32_t at = (uint32_t)P.root_code_at;
     const UploadPart part[4] = {
         {P.code_host.data() + at, sizeof(uint2) * (P.code_host.size() - at), 0},
@@ -1927,12 +1950,58 @@ static tgp_status plan_upload_roots(tgp_ctx ctx, Plan &P) {
     P.reduce_dev = reinterpret_cast<ProgDesc *>(b + off[1]);
     P.store_dev = reinterpret_cast<ProgDesc *>(b + off[2]);
     P.ind_rows_dev = reinterpret_cast<int32_t *>(b + off[3]);
+    if (P.split && !P.reserve && !d->other.blob) {  // (without it, only flat_in_reserve fails)
+        P.reserve_bytes = flat_bytes_bound(*d, P.cases);
+        if (ctx->pool.alloc(&P.reserve, P.reserve_bytes) != hipSuccess) {
+            P.reserve = nullptr;
+            (void)hipGetLastError();
+        }
+    }
     return TGP_OK;
 }
 
-static tgp_status plan_upload(tgp_ctx ctx, Plan &P) {
+static tgp_status plan_upload(tgp_ctx ctx, tgp_dag d, Plan &P) {
     tgp_status st = plan_upload_fill(ctx, P);
-    return st == TGP_OK ? plan_upload_roots(ctx, P) : st;
+    return st == TGP_OK ? plan_upload_roots(ctx, d, P) : st;
+}
+
+// Some words passed as a kernel argument.
+struct PutWords {
+    uint32_t w[960];
+};
+__global__ void k_put(const PutWords a, uint32_t *dst, int32_t n) {
+    typedef const __attribute__((address_space(4))) uint32_t cword;
+    const cword *src = (const cword *)__builtin_amdgcn_kernarg_segment_ptr();
+    for (int i = threadIdx.x; i < n; i += blockDim.x) dst[i] = src[i];
+}
+
+// Writes the blob of a flat plan made by flat_in_reserve: its words travel as
+// kernel arguments, which needs no staging that would have to outlive a
+// capture.  A captured call writes it where it is replayed, so the next call
+// writes it again.
+static tgp_status put_flat(tgp_ctx ctx, Plan &P) {
+    if (!P.put) return TGP_OK;
+    std::vector<char> image(flat_bytes(P));
+    auto part = [&](const void *to, const void *src, size_t bytes) {
+        if (bytes) memcpy(image.data() + ((const char *)to - (const char *)P.blob), src, bytes);
+    };
+    part(P.code_dev, P.code_host.data(), sizeof(uint2) * P.code_host.size());
+    part(P.fill_dev, P.fill_host.data(), sizeof(ProgDesc) * P.fill_host.size());
+    part(P.reduce_dev, P.reduce_host.data(), sizeof(ProgDesc) * P.reduce_host.size());
+    part(P.store_dev, P.store_host.data(), sizeof(ProgDesc) * P.store_host.size());
+    part(P.ind_rows_dev, P.ind_rows_host.data(), sizeof(int32_t) * P.ind_rows_host.size());
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
+    if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess) (void)hipGetLastError();
+    for (size_t at = 0; at < image.size(); at += sizeof(PutWords)) {
+        PutWords a;
+        const size_t n = std::min(sizeof a, image.size() - at);
+        memcpy(a.w, image.data() + at, n);
+        hipLaunchKernelGGL(k_put, dim3(1), dim3(256), 0, ctx->stream, a, (uint32_t *)((char *)P.blob + at),
+                           (int32_t)(n / 4));
+    }
+    HCHK(ctx, hipGetLastError());
+    P.put = cap != hipStreamCaptureStatusNone;
+    return TGP_OK;
 }
 
 int ctx_stack_slots(tgp_ctx ctx) { return ctx->stack_lds ? interp_lds_stack() : interp_max_stack(); }
@@ -1969,15 +2038,16 @@ static bool plan_current(tgp_ctx ctx, const Plan &P, int64_t cases) {
            P.access_cost == ctx->cache_access_cost && P.fold == ctx->fold;
 }
 
-static size_t budget_slots(tgp_ctx ctx, int64_t cases) {
-    return (size_t)(ctx->cache_budget / (sizeof(float) * (size_t)std::max<int64_t>(cases, 1)));
+// Cache rows of `cases` cases in a budget of so many bytes.
+static size_t rows_in(size_t budget, int64_t cases) {
+    return (size_t)(budget / (sizeof(float) * (size_t)std::max<int64_t>(cases, 1)));
 }
 
-static bool tables_fit_on(tgp_ctx ctx, const int64_t (&entries)[2], tgp_domain dom, int32_t split) {
+static bool tables_fit_on(size_t budget, const int64_t (&entries)[2], tgp_domain dom, int32_t split) {
     double per[2];
     size_t slots;
     table_slots_on(dom, split, per);
-    return tables_fit(entries, per, sizeof(float) * (double)dom->cases, budget_slots(ctx, dom->cases), &slots);
+    return tables_fit(entries, per, sizeof(float) * (double)dom->cases, rows_in(budget, dom->cases), &slots);
 }
 
 // Of d's plans for domains of dom's size, the one to evaluate dom with, or
@@ -1994,9 +2064,9 @@ static Plan *best_plan(tgp_ctx ctx, tgp_dag d, tgp_domain dom, int32_t want, boo
     *tables = want > 0;
     if (want > 0 && with) {
         const int64_t entries[2] = {with->n_tab[0], with->n_tab[1]};
-        *tables = dom->rows(with->split) == with->tab_rows || tables_fit_on(ctx, entries, dom, with->split);
+        *tables = dom->rows(with->split) == with->tab_rows || tables_fit_on(with->budget, entries, dom, with->split);
     } else if (want > 0 && flat && flat->asked) {
-        *tables = tables_fit_on(ctx, flat->refused, dom, flat->asked);
+        *tables = tables_fit_on(flat->budget, flat->refused, dom, flat->asked);
     }
     return *tables ? with : flat;
 }
@@ -2024,6 +2094,10 @@ static tgp_status choose_plan(tgp_ctx ctx, tgp_dag d, tgp_domain dom, int32_t wa
     return TGP_OK;
 }
 
+// The cache budget of a plan made now: its neighbour's, so that a budget that was
+// set for the DAG's first plan holds for every shape of its size.
+static size_t plan_budget(tgp_ctx ctx, tgp_dag d) { return d->other.cases >= 0 ? d->other.budget : ctx->cache_budget; }
+
 // After tables could not be planned beside a flat plan: goes on with the flat
 // plan, for every shape (so that no call plans in vain again).
 static void keep_flat(tgp_dag d) {
@@ -2042,12 +2116,18 @@ tgp_status build_plan(tgp_ctx ctx, tgp_dag d, tgp_domain dom, const std::functio
     tgp_status st = choose_plan(ctx, d, dom, wanted_split(ctx, d, dom), &made, &split);
     if (st != TGP_OK) return st;
     if (made) {
-        st = ctx->plan_upload && !P.blob ? plan_upload(ctx, P) : TGP_OK;
+        st = !ctx->plan_upload ? TGP_OK : (!P.blob ? plan_upload(ctx, d, P) : put_flat(ctx, P));
         ctx->times.plan_ms = now_ms() - t0;
         return st;
     }
     const int D = ctx_stack_slots(ctx);
-    PlanJob w(d, cases, D, budget_slots(ctx, cases));
+    if (!split) {  // a flat plan of its own: the room kept for one is not needed
+        ctx->pool.release(d->other.reserve);
+        d->other.reserve = nullptr;
+    }
+    const size_t budget = plan_budget(ctx, d);
+    PlanJob w(d, cases, D, rows_in(budget, cases));
+    w.budget = budget;
     set_split(w, dom, split);
     w.pl.team = &ctx->team;
     ScratchLoan loan(ctx, w.pl);
@@ -2061,7 +2141,7 @@ tgp_status build_plan(tgp_ctx ctx, tgp_dag d, tgp_domain dom, const std::functio
     st = plan_decide_emit_fill(w, D, ctx->reorder != 0, ctx->cache_access_cost, ctx->fold, kPlanThreads);
     if (st != TGP_OK && w.pl.tables_over && d->other.cases >= 0) {
         keep_flat(d);
-        st = ctx->plan_upload && !P.blob ? plan_upload(ctx, P) : TGP_OK;
+        st = !ctx->plan_upload ? TGP_OK : (!P.blob ? plan_upload(ctx, d, P) : put_flat(ctx, P));
         ctx->times.plan_ms = now_ms() - t0;
         return st;
     }
@@ -2077,11 +2157,49 @@ tgp_status build_plan(tgp_ctx ctx, tgp_dag d, tgp_domain dom, const std::functio
     ctx->times.plan_decide_ms = w.t_decide;
     ctx->times.plan_emit_ms = w.t_emit;
     if (ctx->plan_upload) {
-        st = plan_upload_roots(ctx, P);
+        st = plan_upload_roots(ctx, d, P);
         if (st != TGP_OK) return st;
     }
     ctx->times.plan_ms = now_ms() - t0;
     return TGP_OK;
+}
+
+// The flat plan beside d's plan with tables, made from what that one keeps: no
+// allocation, and no device work but put_flat's.  Returns it, or nullptr.
+static Plan *flat_in_reserve(tgp_ctx ctx, tgp_dag d) {
+    if (d->plan.split) std::swap(d->plan, d->other);
+    Plan &P = d->plan, &with = d->other;
+    if (!with.split || !with.reserve || P.blob) return nullptr;
+    if (P.cases != with.cases) {
+        const int D = ctx_stack_slots(ctx);
+        PlanJob w(d, with.cases, D, rows_in(with.budget, with.cases));
+        w.budget = with.budget;
+        w.pl.team = &ctx->team;
+        ScratchLoan loan(ctx, w.pl);
+        plan_prepare(w, ctx->fold != 0, kPlanThreads);
+        w.pl.fold_val = with.fold_val;
+        if (plan_decide_emit(w, D, ctx->reorder != 0, ctx->cache_access_cost, ctx->fold, kPlanThreads) != TGP_OK) {
+            P = Plan();
+            return nullptr;
+        }
+    }
+    if (flat_bytes(P) > with.reserve_bytes) return nullptr;
+    char *b = static_cast<char *>(with.reserve);
+    auto part = [&](size_t bytes) {
+        char *p = b;
+        b += (bytes + 255) & ~(size_t)255;
+        return p;
+    };
+    P.blob = with.reserve;
+    with.reserve = nullptr;
+    // (the descriptors count from the first word of all the code)
+    P.code_dev = P.code_roots_dev = reinterpret_cast<uint2 *>(part(sizeof(uint2) * P.code_host.size()));
+    P.fill_dev = reinterpret_cast<ProgDesc *>(part(sizeof(ProgDesc) * P.fill_host.size()));
+    P.reduce_dev = reinterpret_cast<ProgDesc *>(part(sizeof(ProgDesc) * P.reduce_host.size()));
+    P.store_dev = reinterpret_cast<ProgDesc *>(part(sizeof(ProgDesc) * P.store_host.size()));
+    P.ind_rows_dev = reinterpret_cast<int32_t *>(part(sizeof(int32_t) * P.ind_rows_host.size()));
+    P.put = true;
+    return &P;
 }
 
 tgp_status build_plans(tgp_ctx ctx, int32_t n, const tgp_dag *dags, const tgp_domain *doms) {
@@ -2118,7 +2236,9 @@ tgp_status build_plans(tgp_ctx ctx, int32_t n, const tgp_dag *dags, const tgp_do
         const tgp_status cs = choose_plan(ctx, d, wd.dom, wd.split, &made, &split);
         if (cs != TGP_OK) return cs;
         if (made) continue;
-        jobs.emplace_back(new PlanJob(d, c, D, budget_slots(ctx, c)));
+        const size_t budget = plan_budget(ctx, d);
+        jobs.emplace_back(new PlanJob(d, c, D, rows_in(budget, c)));
+        jobs.back()->budget = budget;
         set_split(*jobs.back(), wd.dom, split);
     }
     if (jobs.empty()) {
@@ -2444,48 +2564,69 @@ tgp_status tgp_fitness_noalloc(tgp_ctx ctx, tgp_dag d, tgp_domain dom, const flo
     if (ctx->device >= kMaxDevices || !g_scratch_ptr[ctx->device])
         return fail(ctx, TGP_EHIP, "no scratch address for device %d: %s", ctx->device,
                     ctx->device < kMaxDevices ? hipGetErrorString(g_scratch_err[ctx->device]) : "device index");
-    // The best plan if it is on the device, else the other one (the tables of
-    // one that does not fit dom are checked below).
-    bool with_tables;
-    auto ready = [&](const Plan &Q) { return plan_current(ctx, Q, dom->cases) && Q.blob && Q.code_roots_dev; };
-    const Plan *best = best_plan(ctx, d, dom, wanted_split(ctx, d, dom), &with_tables);
-    if (!(best == &d->plan && ready(d->plan)) && ready(d->other) && (best == &d->other || !ready(d->plan)))
-        std::swap(d->plan, d->other);
-    const Plan &P = d->plan;
-    if (!ready(P))
+    // What a call with plan Q puts into the scratch: the partial sums, the cache
+    // rows and, where the plan's own block does not hold them, the tables.
+    struct Layout {
+        int32_t stripes, tiles;
+        size_t partial, rows, tables, total;
+        bool own_tables;
+    };
+    auto layout = [&](const Plan &Q) {
+        auto up = [](size_t n) { return (n + 255) & ~(size_t)255; };
+        Layout l;
+        choose_split(ctx, Q.n_reduce, dom->cases, choose_K(ctx, dom->cases, Q), &l.stripes, &l.tiles);
+        l.partial = up(sizeof(float2) * (size_t)Q.n_reduce * (size_t)l.stripes);
+        l.rows = sizeof(float) * (size_t)Q.n_slots * (size_t)dom->cases;
+        l.tables = Q.tables_bytes(*dom);
+        l.own_tables = l.tables <= Q.tables_cap;
+        l.total = l.own_tables ? l.partial + l.rows : up(l.partial + l.rows) + l.tables;
+        return l;
+    };
+    // The best plan for dom's shape if it is on the device and fits; else any
+    // that does, the flat one made for it where only one with tables is there.
+    auto ready = [&](const Plan *Q) {
+        return Q && plan_current(ctx, *Q, dom->cases) && Q->blob && Q->code_roots_dev;
+    };
+    auto fits = [&](const Plan *Q) { return ready(Q) && layout(*Q).total <= kNoAllocScratchBytes; };
+    if (!ready(&d->plan) && !ready(&d->other))
         return fail(ctx, TGP_EINVAL,
                     "the DAG has no plan for a domain of %lld cases under this context's settings "
                     "(evaluate it once with tgp_fitness or tgp_evaluate)", (long long)dom->cases);
+    const int32_t want = wanted_split(ctx, d, dom);
+    auto first_fit = [&](bool with_tables) -> Plan * {
+        for (Plan *Q : {&d->plan, &d->other})
+            if ((Q->split > 0) == with_tables && fits(Q)) return Q;
+        return nullptr;
+    };
+    Plan *chosen = first_fit(want > 0);
+    if (!chosen && want > 0) chosen = first_fit(false);
+    if (!chosen && flat_in_reserve(ctx, d)) chosen = first_fit(false);
+    if (!chosen) chosen = first_fit(true);
+    if (!chosen) {
+        const Plan &Q = ready(&d->plan) ? d->plan : d->other;
+        const Layout l = layout(Q);
+        return fail(ctx, TGP_ENOMEM,
+                    "needs %zu bytes of scratch (%zu of partial sums, %zu of cache rows, %zu of tables); "
+                    "tgp_fitness_noalloc has %zu", l.total, l.partial, l.rows, l.own_tables ? 0 : l.tables,
+                    kNoAllocScratchBytes);
+    }
+    if (chosen != &d->plan) std::swap(d->plan, d->other);
+    st = put_flat(ctx, d->plan);
+    if (st != TGP_OK) return st;
+    const Plan &P = d->plan;
     const int K = choose_K(ctx, dom->cases, P);
+    const Layout l = layout(P);
     InterpArgs a;
     fill_args(a, dom, P.code_roots_dev, nullptr);
     a.progs = P.reduce_dev;
     a.n_progs = P.n_reduce;
-    choose_split(ctx, a.n_progs, dom->cases, K, &a.job.n_stripes, &a.job.tiles_per_stripe);
-    const size_t partial_bytes =
-        (sizeof(float2) * (size_t)a.n_progs * (size_t)a.job.n_stripes + 255) & ~(size_t)255;
-    const size_t cache_bytes = sizeof(float) * (size_t)P.n_slots * (size_t)dom->cases;
-    // The plan's tables were allocated with it; a domain of the same size but
-    // another shape may need larger ones, which then go into the scratch.
-    const size_t table_bytes = P.tables_bytes(*dom);
-    const bool own_tables = table_bytes <= P.tables_cap;
-    const size_t tables_at = (partial_bytes + cache_bytes + 255) & ~(size_t)255;
-    if (P.split && std::max(P.row_bytes(*dom), table_bytes - P.row_bytes(*dom)) >= 0xffffff00u)
-        return fail(ctx, TGP_ENOMEM, "the tables of this domain's shape exceed 4 GiB");
-    if (!own_tables && tables_at + table_bytes > kNoAllocScratchBytes)
-        return fail(ctx, TGP_ENOMEM,
-                    "needs %zu bytes of scratch (%zu of tables for this domain's shape); "
-                    "tgp_fitness_noalloc has %zu", tables_at + table_bytes, table_bytes, kNoAllocScratchBytes);
-    if (partial_bytes + cache_bytes > kNoAllocScratchBytes)
-        return fail(ctx, TGP_ENOMEM,
-                    "needs %zu bytes of scratch (%zu of partial sums, %zu of cache rows); "
-                    "tgp_fitness_noalloc has %zu", partial_bytes + cache_bytes, partial_bytes, cache_bytes,
-                    kNoAllocScratchBytes);
+    a.job.n_stripes = l.stripes;
+    a.job.tiles_per_stripe = l.tiles;
     // Every (program, stripe) pair and every cache row is written before it
     // is read, so nothing in the scratch needs clearing between calls.
     char *base = static_cast<char *>(g_scratch_ptr[ctx->device]);
-    float *cache = P.n_slots ? reinterpret_cast<float *>(base + partial_bytes) : nullptr;
-    float *tables = own_tables ? (float *)P.tables : reinterpret_cast<float *>(base + tables_at);
+    float *cache = P.n_slots ? reinterpret_cast<float *>(base + l.partial) : nullptr;
+    float *tables = l.own_tables ? (float *)P.tables : reinterpret_cast<float *>(base + l.total - l.tables);
     ctx->fill_recorded = false;
     if (P.n_slots || !P.tab_host.empty()) {
         st = fill_into(ctx, d, dom, K, cache, tables);

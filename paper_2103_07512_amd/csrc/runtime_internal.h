@@ -166,6 +166,14 @@ struct Plan {
     int32_t split = 0, asked = 0;
     int64_t tab_rows = 0;
     int64_t refused[2] = {0, 0};
+    size_t budget = 0;                  // the cache budget that the plan was made for
+    // Beside tables: what the flat plan is made from where nothing may be
+    // allocated (flat_in_reserve): the folded constants, and a pool block that
+    // then holds its programs and is its blob.
+    std::vector<float> fold_val;
+    void *reserve = nullptr;
+    size_t reserve_bytes = 0;
+    bool put = false;                   // the blob is still to be written (put_flat)
     int32_t n_tab[2] = {0, 0};          // subtrees in the row and column tables
     struct TabLevel {
         int32_t first, mid, last;       // row programs [first, mid), column programs [mid, last)
@@ -223,7 +231,9 @@ struct Plan {
         pool.release(blob);
         pool.release(blob_roots);
         pool.release(tables);
-        blob = blob_roots = tables = nullptr;
+        pool.release(reserve);
+        blob = blob_roots = tables = reserve = nullptr;
+        put = false;
         tables_cap = 0;
         tab_dev = nullptr;
         code_dev = code_roots_dev = nullptr;

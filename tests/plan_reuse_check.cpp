@@ -4,7 +4,9 @@
 //   - the plan with tables is used only where the tables are within half the
 //     cache budget and a 32-bit byte offset of each, else a flat one;
 //   - a DAG evaluated on several shapes in turn is planned twice at most, and
-//     the plan that is not in use stays where it is.
+//     the plan that is not in use stays where it is;
+//   - the flat plan that tgp_fitness_noalloc makes beside one with tables is the
+//     one that planning flat gives, and fits the block kept for it.
 #define main planner_check_main
 #include "planner_check.cpp"
 #undef main
@@ -43,7 +45,9 @@ void use(tgp_ctx ctx, tgp_dag_s &d, tgp_domain_s dom) {
     CHECK(choose_plan(ctx, &d, &dom, wanted_split(ctx, &d, &dom), &made, &split) == TGP_OK, "choose_plan failed\n");
     if (!made) {
         ++g_planned;
-        PlanJob w(&d, dom.cases, 8, budget_slots(ctx, dom.cases));
+        const size_t budget = plan_budget(ctx, &d);
+        PlanJob w(&d, dom.cases, 8, rows_in(budget, dom.cases));
+        w.budget = budget;
         set_split(w, &dom, split);
         plan_prepare(w, true);
         const tgp_status st = plan_decide_emit(w, 8, true, ctx->cache_access_cost, 1, 1);
@@ -58,6 +62,67 @@ void use(tgp_ctx ctx, tgp_dag_s &d, tgp_domain_s dom) {
     CHECK(row < 4294967296.0 && col < 4294967296.0, "%lld x %lld: tables of %.0f and %.0f bytes\n",
           (long long)dom.rows(P.split), (long long)dom.cols(P.split), row, col);
     CHECK(row + col <= ctx->cache_budget / 2.0, "tables of %.0f bytes, budget %zu\n", row + col, ctx->cache_budget);
+}
+
+// The folded subtrees' values (no variable: any case).
+void fold(tgp_dag_s &d, PlanJob &w) {
+    if (w.pl.folded.empty()) return;
+    const int64_t U = d.stats.dag_nodes;
+    w.pl.fold_val.assign(U, 0.0f);
+    for (int64_t n = 0; n < U; ++n) {
+        const int op = d.op[n] & 0xff;
+        const int32_t *k = &d.kid[3 * n];
+        float *v = w.pl.fold_val.data();
+        v[n] = kArity[op] == 0 ? d.value[n] : apply(op, v[k[0]], k[1] >= 0 ? v[k[1]] : 0, k[2] >= 0 ? v[k[2]] : 0);
+    }
+}
+
+template <class T>
+bool same(const std::vector<T> &a, const std::vector<T> &b) {
+    return a.size() == b.size() && memcmp(a.data(), b.data(), sizeof(T) * a.size()) == 0;
+}
+
+void check_reserve(tgp_ctx ctx, Gen &g, int n_ind, int n_ch, int d_max, tgp_domain_s dom) {
+    tgp_dag_s d;
+    d.ctx = ctx;
+    make_dag(d, g, n_ind, n_ch, d_max);
+    std::vector<int64_t> size(d.op.size(), 1);
+    for (size_t n = 0; n < d.op.size(); ++n)
+        for (int j = 0; j < 3; ++j)
+            if (d.kid[3 * n + j] >= 0) size[n] += size[d.kid[3 * n + j]];
+    for (int32_t r : d.roots) d.stats.tree_nodes += size[r];
+    for (int32_t o : d.op) d.stats.dag_internal += kArity[o & 0xff] > 0;
+    Plan flat;
+    for (int32_t split : {0, dom.split}) {
+        d.plan = Plan();
+        PlanJob w(&d, dom.cases, 8, rows_in(ctx->cache_budget, dom.cases));
+        w.budget = ctx->cache_budget;
+        set_split(w, &dom, split);
+        plan_prepare(w, true);
+        fold(d, w);
+        const tgp_status st = plan_decide_emit(w, 8, true, ctx->cache_access_cost, 1, 1);
+        CHECK(st == TGP_OK && d.plan.split == split, "U=%lld: status %d\n", (long long)d.stats.dag_nodes, st);
+        if (!split) flat = d.plan;
+    }
+    const size_t bound = flat_bytes_bound(d, dom.cases), need = flat_bytes(flat);
+    const bool fits = sizeof(float) * (size_t)flat.n_slots * (size_t)dom.cases <= kNoAllocScratchBytes;
+    CHECK(!fits || need <= bound, "U=%lld: %zu bytes of flat programs, bound %zu\n", (long long)d.stats.dag_nodes, need, bound);
+    std::vector<char> block(bound);
+    d.plan.reserve = block.data();
+    d.plan.reserve_bytes = bound;
+    const size_t budget = ctx->cache_budget;
+    ctx->cache_budget = 0;  // the plan's own budget holds
+    Plan *made = flat_in_reserve(ctx, &d);
+    ctx->cache_budget = budget;
+    CHECK((made != nullptr) == (need <= bound), "U=%lld: no flat plan\n", (long long)d.stats.dag_nodes);
+    if (!made) return;
+    CHECK(made == &d.plan && d.other.split == dom.split, "the plans changed places\n");
+    CHECK(same(made->code_host, flat.code_host) && same(made->fill_host, flat.fill_host) &&
+              same(made->reduce_host, flat.reduce_host) && same(made->store_host, flat.store_host) &&
+              same(made->ind_rows_host, flat.ind_rows_host),
+          "U=%lld: another flat plan\n", (long long)d.stats.dag_nodes);
+    CHECK((char *)(made->ind_rows_dev + made->ind_rows_host.size()) <= block.data() + bound, "past the block\n");
+    CHECK(flat_in_reserve(ctx, &d) == nullptr, "made twice\n");
 }
 
 }  // namespace
@@ -123,6 +188,15 @@ int main() {
             }
         CHECK(g_planned == 2, "planned %d times\n", g_planned);
     }
+    c.plan_upload = true;
+    c.cache_budget = (size_t)72 << 30;
+    Gen g(20261206);
+    for (int i = 0; i < 12; ++i) {
+        check_reserve(&c, g, 20 + 5 * i, 1, 5 + i % 4, domain(&c, {64, 64}));
+        check_reserve(&c, g, 200, 1 + i % 3, 4 + i % 6, domain(&c, {33, 127}));
+        check_reserve(&c, g, 1, 1, 1 + i, domain(&c, {8, 128}));
+    }
+    check_reserve(&c, g, 2500, 3, 11, domain(&c, {32, 32}));  // planned by several threads
     if (g_bad) {
         printf("%d failures\n", g_bad);
         return 1;

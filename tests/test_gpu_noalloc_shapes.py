@@ -1,0 +1,77 @@
+"""tgp_fitness_noalloc on long thin grids: the tables of a plan made on a square
+grid of the same size need more than the fixed array there, so their entries'
+programs are run in place; the bits are those of tgp_fitness on a fresh DAG."""
+
+import numpy as np
+import pytest
+
+from paper_2103_07512_amd import popgen as pg
+
+pytestmark = pytest.mark.gpu
+
+FUNCS = tuple(n for n, a in pg.OPS if a > 0 and n not in ("or", "xor", "and", "warp"))
+
+
+def say(*a):
+    print(*a, flush=True)
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    from paper_2103_07512_amd import tgp
+    assert torch.cuda.is_available()
+    return tgp, tgp.Context(0), torch
+
+
+def _plane():
+    """One-sided subtrees with constants of their own under operators of every
+    operand order, with nested entries and one shared subtree of both sides."""
+    def full(d, v):
+        return v if d == 0 else f"sub({full(d - 1, v)}, mult({full(d - 1, v)}, 0.5))"
+    shared = "pow(sin(exp(x)), cos(exp(y)))"
+    forms = ["add({a}, {b})", "sub({b}, {a})", "div({a}, {b})", "mod({b}, {a})", "pow({a}, {b})", "max({b}, {a})",
+             "clip({b}, {a}, mult(x, y))", "if({a}, sub(x, y), {b})", "lerp({a}, {b}, add(x, y))",
+             "mdist(mult({a}, y), len({b}, x))", "sqrt(abs(sub({a}, {b})))"]
+    texts = []
+    for i in range(176):
+        c = round(0.0125 * i - 1.0, 4)
+        a, b = f"sin(mult(x, {c}))", f"add(cos(y), {c})"
+        texts.append(forms[i % len(forms)].format(a=a, b=b))
+    texts += [f"mult({full(9, 'x')}, {full(10, 'y')})", "sin(x)", "exp(y)", "0.25", "x"]
+    texts += [f"add({shared}, {0.1 * i:.1f})" for i in range(12)]
+    return pg.population_from_texts(texts)
+
+
+CASES = [("plane", (1024, 1024), [(8, 131072), (131072, 8), (4, 2, 131072), (1, 1 << 20)]),
+         ("volume", (64, 128, 128), [(2, 2, 262144), (262144, 2, 2)]),
+         # sides of nothing, the last tile not full
+         ("plane", (1001, 1031), [(7, 147433), (147433, 7)])]
+
+
+@pytest.mark.parametrize("which,planned,shapes", CASES, ids=["plane", "volume", "ragged"])
+def test_long_thin_grids(env, which, planned, shapes):
+    tgp, ctx, torch = env
+    pop = _plane() if which == "plane" else pg.ramped_half_and_half(150, 2, 6, 1301, FUNCS, 3, 1)
+    n, cases = pop.n_individuals, int(np.prod(planned))
+    rng = np.random.RandomState(11)
+    t = torch.from_numpy(rng.uniform(-1, 1, (1, cases)).astype(np.float32)).to("cuda:0")
+    out, ref = (torch.full((n,), -1.0, dtype=torch.float64, device="cuda:0") for _ in range(2))
+    ctx.set_cache_budget(56 << 20)   # rows and tables within the fixed array where the DAG is planned
+    try:
+        dag, dom = tgp.build_dag(ctx, pop), tgp.Domain(ctx, planned)
+        tgp.fitness(ctx, dag, dom, t, tgp.RMSE, ref)
+        work = ctx.last_work()
+        tgp.fitness_noalloc(ctx, dag, dom, t, tgp.RMSE, out)
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy().view(np.uint64), ref.cpu().numpy().view(np.uint64))
+    finally:
+        ctx.set_cache_budget(1 << 36)
+    for s in shapes:
+        say("planned", planned, "called on", s, "cached nodes", work["cached_nodes"])
+        thin = tgp.Domain(ctx, s)
+        out.fill_(-1.0)
+        tgp.fitness_noalloc(ctx, dag, thin, t, tgp.RMSE, out)
+        tgp.fitness(ctx, tgp.build_dag(ctx, pop), thin, t, tgp.RMSE, ref)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(out.cpu().numpy().view(np.uint64), ref.cpu().numpy().view(np.uint64))
