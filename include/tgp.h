@@ -303,6 +303,9 @@ tgp_status tgp_fitness(tgp_ctx ctx, tgp_dag dag, tgp_domain dom, const float *ta
  * as on a grid much longer and thinner than the one the DAG was planned for,
  * the DAG is evaluated without them.  The first such call plans that on the
  * host, and its programs go to memory that the DAG already holds.
+ * A captured call stays valid until dag is planned for another number of cases
+ * or under other settings, or destroyed; its calls on other shapes of the same
+ * size leave it alone.
  * Every call on a GPU shares that array, so calls that overlap on one GPU
  * (two streams, or two contexts on the same device) race: order them.
  * Queued on the context's stream; returns without waiting. */

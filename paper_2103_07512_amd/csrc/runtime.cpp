@@ -1950,12 +1950,22 @@ static tgp_status plan_upload_roots(tgp_ctx ctx, tgp_dag d, Plan &P) {
     P.reduce_dev = reinterpret_cast<ProgDesc *>(b + off[1]);
     P.store_dev = reinterpret_cast<ProgDesc *>(b + off[2]);
     P.ind_rows_dev = reinterpret_cast<int32_t *>(b + off[3]);
-    if (P.split && !P.reserve && !d->other.blob) {  // (without it, only flat_in_reserve fails)
-        P.reserve_bytes = flat_bytes_bound(*d, P.cases);
-        if (ctx->pool.alloc(&P.reserve, P.reserve_bytes) != hipSuccess) {
-            P.reserve = nullptr;
+    // Memory for tgp_fitness_noalloc alone (without it, it may refuse a call).
+    auto keep = [&](void **block, size_t bytes) {
+        if (!*block && ctx->pool.alloc(block, bytes) != hipSuccess) {
+            *block = nullptr;
             (void)hipGetLastError();
         }
+    };
+    if (P.split && !d->other.blob) {
+        P.reserve_bytes = flat_bytes_bound(*d, P.cases);
+        keep(&P.reserve, P.reserve_bytes);
+    }
+    if (P.split) {
+        const size_t rows = sizeof(float) * (size_t)P.n_slots * (size_t)P.cases, tables = P.planned_tables_bytes();
+        const size_t sums = sizeof(float2) * (size_t)P.n_reduce * (size_t)((P.cases + kWideCols - 1) / kWideCols);
+        if (rows <= kNoAllocScratchBytes && sums + rows + tables + 512 > kNoAllocScratchBytes)
+            keep(&P.noalloc_tables, tables);
     }
     return TGP_OK;
 }
@@ -2064,7 +2074,7 @@ static Plan *best_plan(tgp_ctx ctx, tgp_dag d, tgp_domain dom, int32_t want, boo
     *tables = want > 0;
     if (want > 0 && with) {
         const int64_t entries[2] = {with->n_tab[0], with->n_tab[1]};
-        *tables = dom->rows(with->split) == with->tab_rows || tables_fit_on(with->budget, entries, dom, with->split);
+        *tables = with->planned_shape(*dom) || tables_fit_on(with->budget, entries, dom, with->split);
     } else if (want > 0 && flat && flat->asked) {
         *tables = tables_fit_on(flat->budget, flat->refused, dom, flat->asked);
     }
@@ -2423,28 +2433,26 @@ static tgp_status fill_into(tgp_ctx ctx, tgp_dag d, tgp_domain dom, int K, float
 }
 
 static tgp_status run_fill(tgp_ctx ctx, tgp_dag d, tgp_domain dom, int K, float **cache_out) {
-    Plan &P = d->plan;
+    const Plan &P = d->plan;
     *cache_out = nullptr;
     ctx->fill_recorded = false;
     if (P.n_slots == 0 && P.tab_host.empty()) return TGP_OK;
     const size_t bytes = sizeof(float) * (size_t)P.n_slots * (size_t)dom->cases;
     if (P.n_slots) HCHK(ctx, ensure(ctx->cache, bytes));
-    // The tables belong to the plan: their addresses stay the same for its
-    // life (tgp_fitness_noalloc uses them too, perhaps inside a HIP graph).
+    // Like the cache rows, the tables hold one evaluation's values at a time.
+    // (tgp_fitness_noalloc has tables of its own: a captured call may be
+    // replayed beside this one on another stream.)
     const size_t tab = P.tables_bytes(*dom);
-    if (tab > P.tables_cap) {
-        if (P.tables) {
-            HCHK(ctx, hipStreamSynchronize(ctx->stream));
-            ctx->pool.release(P.tables);
-            P.tables = nullptr;
-            P.tables_cap = 0;
-        }
-        HCHK(ctx, ctx->pool.alloc(&P.tables, tab));
-        P.tables_cap = tab;
+    if (tab > ctx->tables.cap) {
+        if (ctx->tables.p) HCHK(ctx, hipStreamSynchronize(ctx->stream));
+        ctx->pool.release(ctx->tables.p);
+        ctx->tables = DevBuf{};
+        HCHK(ctx, ctx->pool.alloc(&ctx->tables.p, tab));
+        ctx->tables.cap = tab;
     }
     float *cache = P.n_slots ? (float *)ctx->cache.p : nullptr;
     *cache_out = cache;
-    return fill_into(ctx, d, dom, K, cache, (float *)P.tables);
+    return fill_into(ctx, d, dom, K, cache, (float *)ctx->tables.p);
 }
 
 // The plan of d for dom with its cache filled (fill launches queued on the
@@ -2525,7 +2533,7 @@ tgp_status tgp_fitness(tgp_ctx ctx, tgp_dag d, tgp_domain dom, const float *targ
     const int K = choose_K(ctx, dom->cases, P);
     InterpArgs a;
     fill_args(a, dom, P.code_roots_dev, cache);
-    fill_table_fields(a.job, P, dom, (float *)P.tables);
+    fill_table_fields(a.job, P, dom, (float *)ctx->tables.p);
     a.progs = P.reduce_dev;
     a.n_progs = P.n_reduce;
     choose_split(ctx, a.n_progs, dom->cases, K, &a.job.n_stripes, &a.job.tiles_per_stripe);
@@ -2565,11 +2573,11 @@ tgp_status tgp_fitness_noalloc(tgp_ctx ctx, tgp_dag d, tgp_domain dom, const flo
         return fail(ctx, TGP_EHIP, "no scratch address for device %d: %s", ctx->device,
                     ctx->device < kMaxDevices ? hipGetErrorString(g_scratch_err[ctx->device]) : "device index");
     // What a call with plan Q puts into the scratch: the partial sums, the cache
-    // rows and, where the plan's own block does not hold them, the tables.
+    // rows and the tables (unless the plan keeps a block for them).
     struct Layout {
         int32_t stripes, tiles;
         size_t partial, rows, tables, total;
-        bool own_tables;
+        float *own;
     };
     auto layout = [&](const Plan &Q) {
         auto up = [](size_t n) { return (n + 255) & ~(size_t)255; };
@@ -2577,9 +2585,9 @@ tgp_status tgp_fitness_noalloc(tgp_ctx ctx, tgp_dag d, tgp_domain dom, const flo
         choose_split(ctx, Q.n_reduce, dom->cases, choose_K(ctx, dom->cases, Q), &l.stripes, &l.tiles);
         l.partial = up(sizeof(float2) * (size_t)Q.n_reduce * (size_t)l.stripes);
         l.rows = sizeof(float) * (size_t)Q.n_slots * (size_t)dom->cases;
-        l.tables = Q.tables_bytes(*dom);
-        l.own_tables = l.tables <= Q.tables_cap;
-        l.total = l.own_tables ? l.partial + l.rows : up(l.partial + l.rows) + l.tables;
+        l.own = Q.planned_shape(*dom) ? static_cast<float *>(Q.noalloc_tables) : nullptr;
+        l.tables = l.own ? 0 : Q.tables_bytes(*dom);
+        l.total = l.tables ? up(l.partial + l.rows) + l.tables : l.partial + l.rows;
         return l;
     };
     // The best plan for dom's shape if it is on the device and fits; else any
@@ -2607,8 +2615,7 @@ tgp_status tgp_fitness_noalloc(tgp_ctx ctx, tgp_dag d, tgp_domain dom, const flo
         const Layout l = layout(Q);
         return fail(ctx, TGP_ENOMEM,
                     "needs %zu bytes of scratch (%zu of partial sums, %zu of cache rows, %zu of tables); "
-                    "tgp_fitness_noalloc has %zu", l.total, l.partial, l.rows, l.own_tables ? 0 : l.tables,
-                    kNoAllocScratchBytes);
+                    "tgp_fitness_noalloc has %zu", l.total, l.partial, l.rows, l.tables, kNoAllocScratchBytes);
     }
     if (chosen != &d->plan) std::swap(d->plan, d->other);
     st = put_flat(ctx, d->plan);
@@ -2626,7 +2633,7 @@ tgp_status tgp_fitness_noalloc(tgp_ctx ctx, tgp_dag d, tgp_domain dom, const flo
     // is read, so nothing in the scratch needs clearing between calls.
     char *base = static_cast<char *>(g_scratch_ptr[ctx->device]);
     float *cache = P.n_slots ? reinterpret_cast<float *>(base + l.partial) : nullptr;
-    float *tables = l.own_tables ? (float *)P.tables : reinterpret_cast<float *>(base + l.total - l.tables);
+    float *tables = l.own ? l.own : reinterpret_cast<float *>(base + l.total - l.tables);
     ctx->fill_recorded = false;
     if (P.n_slots || !P.tab_host.empty()) {
         st = fill_into(ctx, d, dom, K, cache, tables);
@@ -2663,7 +2670,7 @@ tgp_status tgp_evaluate(tgp_ctx ctx, tgp_dag d, tgp_domain dom, float *out_dev) 
     const int K = choose_K(ctx, dom->cases, P);
     InterpArgs a;
     fill_args(a, dom, P.code_roots_dev, cache);
-    fill_table_fields(a.job, P, dom, (float *)P.tables);
+    fill_table_fields(a.job, P, dom, (float *)ctx->tables.p);
     a.progs = P.store_dev;
     a.n_progs = P.n_store;
     choose_split(ctx, a.n_progs, dom->cases, K, &a.job.n_stripes, &a.job.tiles_per_stripe);

@@ -93,6 +93,7 @@ struct tgp_ctx_s {
     double cache_access_cost = 20.0;     // < 0: no benefit-driven caching
     DevBuf partial, cache;
     DevBuf fit_out;  // device copy of fitness values bound for host memory
+    DevBuf tables;   // tables of one evaluation, filled by it (a pool block)
     DevicePool pool;             // DAG, plan and population blocks
     void *pin = nullptr;         // pinned staging for uploads and readbacks
     size_t pin_cap = 0;
@@ -141,12 +142,9 @@ struct tgp_domain_s {
 };
 
 // Byte strides of the tables' subtrees on a domain split at axis s.
-inline size_t row_table_stride(const tgp_domain_s &d, int s) {
-    return sizeof(float) * (size_t)((d.rows(s) + 15) / 16 * 16);
-}
-inline size_t col_table_stride(const tgp_domain_s &d, int s) {
-    return sizeof(float) * (size_t)((d.cols(s) + 15) / 16 * 16);
-}
+inline size_t table_stride(int64_t entries) { return sizeof(float) * (size_t)((entries + 15) / 16 * 16); }
+inline size_t row_table_stride(const tgp_domain_s &d, int s) { return table_stride(d.rows(s)); }
+inline size_t col_table_stride(const tgp_domain_s &d, int s) { return table_stride(d.cols(s)); }
 
 // A compiled evaluation plan of one DAG for one case count.
 struct Plan {
@@ -173,6 +171,9 @@ struct Plan {
     std::vector<float> fold_val;
     void *reserve = nullptr;
     size_t reserve_bytes = 0;
+    // Tables on that shape for tgp_fitness_noalloc, where its own memory cannot
+    // hold them beside the rest (else null).  Nothing else uses the block.
+    void *noalloc_tables = nullptr;
     bool put = false;                   // the blob is still to be written (put_flat)
     int32_t n_tab[2] = {0, 0};          // subtrees in the row and column tables
     struct TabLevel {
@@ -183,12 +184,16 @@ struct Plan {
     ProgDesc *tab_dev = nullptr;
     int64_t tab_code_end = 0;           // the table programs' code comes first in code_host
     double exec_tab[2] = {0, 0};        // instructions run per table entry
-    void *tables = nullptr;             // the plain path's tables (pool block of tables_cap bytes)
-    size_t tables_cap = 0;
     int levels() const { return (int)std::max(level_first.empty() ? 0 : level_first.size() - 1, tab_level.size()); }
     size_t tables_bytes(const tgp_domain_s &d) const {
         if (!split) return 0;
         return row_bytes(d) + (size_t)n_tab[1] * col_table_stride(d, split);
+    }
+    // Of the shape that the tables were admitted for.
+    bool planned_shape(const tgp_domain_s &d) const { return split > 0 && d.rows(split) == tab_rows; }
+    size_t planned_tables_bytes() const {
+        const size_t rows = (size_t)n_tab[0] * table_stride(tab_rows);
+        return ((rows + 255) & ~(size_t)255) + (size_t)n_tab[1] * table_stride(cases / tab_rows);
     }
     size_t row_bytes(const tgp_domain_s &d) const {
         return ((size_t)n_tab[0] * row_table_stride(d, split) + 255) & ~(size_t)255;
@@ -230,11 +235,10 @@ struct Plan {
     void release(DevicePool &pool) {
         pool.release(blob);
         pool.release(blob_roots);
-        pool.release(tables);
         pool.release(reserve);
-        blob = blob_roots = tables = reserve = nullptr;
+        pool.release(noalloc_tables);
+        blob = blob_roots = reserve = noalloc_tables = nullptr;
         put = false;
-        tables_cap = 0;
         tab_dev = nullptr;
         code_dev = code_roots_dev = nullptr;
         fill_dev = reduce_dev = store_dev = nullptr;

@@ -1,6 +1,6 @@
 """tgp_fitness_noalloc on long thin grids: the tables of a plan made on a square
-grid of the same size need more than the fixed array there, so their entries'
-programs are run in place; the bits are those of tgp_fitness on a fresh DAG."""
+grid of the same size need more than the fixed array there, so the DAG is
+evaluated without them; the bits are those of tgp_fitness on a fresh DAG.  A captured call stays valid whatever the DAG is evaluated on between replays."""
 
 import numpy as np
 import pytest
@@ -75,3 +75,74 @@ def test_long_thin_grids(env, which, planned, shapes):
         tgp.fitness(ctx, tgp.build_dag(ctx, pop), thin, t, tgp.RMSE, ref)
         torch.cuda.synchronize()
         np.testing.assert_array_equal(out.cpu().numpy().view(np.uint64), ref.cpu().numpy().view(np.uint64))
+
+
+def test_tables_larger_than_the_array(env):
+    """17.6k one-sided subtrees of 1024 entries: 72 MB on the planned shape."""
+    tgp, ctx, torch = env
+    texts = [f"add(sin(mult(x, {i / 8192:.6f})), cos(mult(y, {1 - i / 8192:.6f})))" for i in range(8800)]
+    pop = pg.population_from_texts(texts)
+    t = torch.linspace(-1, 1, 1 << 20, device="cuda:0").reshape(1, -1).contiguous()
+    out, ref = (torch.full((len(texts),), -1.0, dtype=torch.float64, device="cuda:0") for _ in range(2))
+    dag = tgp.build_dag(ctx, pop)
+    for i, s in enumerate([(1024, 1024), (512, 2048), (1024, 1024)]):
+        dom = tgp.Domain(ctx, s)
+        say("planned" if s[0] == 1024 else "other", s)
+        if i == 0:
+            tgp.fitness(ctx, dag, dom, t, tgp.RMSE, ref)
+        else:
+            tgp.fitness(ctx, tgp.build_dag(ctx, pop), dom, t, tgp.RMSE, ref)
+        out.fill_(-1.0)
+        tgp.fitness_noalloc(ctx, dag, dom, t, tgp.RMSE, out)
+        assert s[0] != 1024 or ctx.last_work()["cached_nodes"] > 17000
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(out.cpu().numpy().view(np.uint64), ref.cpu().numpy().view(np.uint64))
+
+
+def test_replayed(env):
+    tgp, _, torch = env
+    pop, shapes = _plane(), [(1024, 1024), (8, 131072)]
+    n = pop.n_individuals
+    t = torch.linspace(-1, 1, 1 << 20, device="cuda:0").reshape(1, -1).contiguous()
+    stream = torch.cuda.Stream()
+    own = tgp.Context(0, stream=stream.cuda_stream)
+    own.set_cache_budget(1 << 34)
+    doms = [tgp.Domain(own, s) for s in shapes]
+    # the planned shape with other bounds: the same plan, other values
+    doms.append(tgp.Domain(own, shapes[0], lo=[-0.5, -3.0], hi=[2.0, 1.0]))
+    want, outs = [], [torch.full((n,), -1.0, dtype=torch.float64, device="cuda:0") for _ in doms]
+    with torch.cuda.stream(stream):
+        for d, o in zip(doms, outs):
+            tgp.fitness(own, tgp.build_dag(own, pop), d, t, tgp.RMSE, o)
+            torch.cuda.synchronize()
+            want.append(o.cpu().numpy().view(np.uint64).copy())
+    assert not np.array_equal(want[0], want[1]) and not np.array_equal(want[0], want[2])
+
+    def check():
+        torch.cuda.synchronize()
+        for o, w in zip(outs, want):
+            np.testing.assert_array_equal(o.cpu().numpy().view(np.uint64), w)
+            o.fill_(-1.0)
+        torch.cuda.synchronize()
+
+    dag = tgp.build_dag(own, pop)
+    with torch.cuda.stream(stream):
+        tgp.fitness(own, dag, doms[0], t, tgp.RMSE, outs[0])   # plans with tables
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            for d, o in zip(doms, outs):   # the second call's flat plan is made here
+                tgp.fitness_noalloc(own, dag, d, t, tgp.RMSE, o)
+    for rep in range(4):
+        say("replay", rep)
+        graph.replay()
+        check()
+        # the DAG's own calls between the replays, on every shape
+        with torch.cuda.stream(stream):
+            for d, o in list(zip(doms, outs))[::-1 if rep % 2 else 1]:
+                tgp.fitness(own, dag, d, t, tgp.RMSE, o)
+        check()
+        with torch.cuda.stream(stream):
+            for d, o in zip(doms, outs):
+                tgp.fitness_noalloc(own, dag, d, t, tgp.RMSE, o)
+        check()
