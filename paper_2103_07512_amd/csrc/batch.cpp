@@ -7,19 +7,20 @@
 // domain shapes, are evaluated together here.  Every job keeps its own plan
 // (DAG, cached subtrees, programs); the batch packs the plans into one set of
 // device buffers and runs
-//   * three launches per cache-fill level (level l of every job), one per
+//   * up to three launches per cache-fill level (level l of every job), one per
 //     form: the flat programs (the tables' among them), the wide, the ragged,
-//   * likewise three for every job's root programs fused with the error
+//   * likewise up to three for every job's root programs fused with the error
 //     reduction,
 //   * one finalize launch for every individual of every job.
 // Resident waves draw work items from partitioned atomic counters, longest
 // program first across all jobs, so small and large jobs share the GPU
 // without a tail (or, in the direct form, one wave per work item in that
 // order).  Launch arguments point at fixed device buffers whose contents
-// change from step to step, so the step is built once as a HIP graph of
-// kernel nodes and replayed; item counts are read on the device, and only the
-// grids that follow the step's sizes (direct form, finalize) are updated in
-// the instantiated graph between replays.
+// change from step to step, so the step is built as a HIP graph of kernel
+// nodes and replayed (built again when a step has programs of a level or form
+// that none had before); item counts are read on the device, and the grids,
+// which follow the step's sizes, are updated in the instantiated graph between
+// replays.
 #include <hip/hip_runtime.h>
 
 #include <stdio.h>
@@ -92,8 +93,11 @@ struct tgp_batch_s {
     bool ext = false;        // interpreter with the bitwise operators and warp
     int D = 0;               // stack slots: the register form's or the LDS form's
     int K = 4;               // cases per lane of the flat launches (others: kTableK)
-    int levels_cap = 4;  // fill levels the graph has launches for
+    int levels_cap = 4;      // fill levels the launch groups are numbered for
     int grid[3][2] = {};     // resident waves: [form][store]
+    bool grid_known = false; // for these K, D and ext
+    std::vector<uint8_t> used;          // groups the graph has launches for
+    std::vector<int> launched;          // the same as a list
     std::vector<uint32_t> group_items;  // items per group of the current step
     uint32_t n_ind = 0;
     // device buffers
@@ -117,7 +121,7 @@ struct tgp_batch_s {
     Pinned<int32_t> h_scalars;
     Pinned<uint2> h_code;
     Pinned<int32_t> h_rows;
-    // graph: reset, 3 levels_cap fill launches, three root launches, the finalize
+    // graph: reset (persistent waves), a launch of every used group, the finalize
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     std::vector<hipGraphNode_t> nodes;
@@ -143,21 +147,22 @@ static void batch_release_graph(tgp_batch b) {
 // Launch groups of a step: 3 l + f = programs of form f (0 flat, 1 wide, 2
 // ragged) of fill level l, l = levels_cap = root programs.
 static int n_groups(tgp_batch b) { return 3 * b->levels_cap + 3; }
-// Kernel launch i of a step: 0 = counter reset, i = group i - 1, then the
-// finalize.
-static int n_launches(tgp_batch b) { return n_groups(b) + 2; }
+// Kernel launches of a step: the counters' reset (persistent waves), the groups
+// in `launched`, the finalize.
+static int n_launches(tgp_batch b) { return (int)b->launched.size() + (b->persistent ? 2 : 1); }
 
 static hipKernelNodeParams launch_params(tgp_batch b, int i, void **args) {
     hipKernelNodeParams p{};
     p.blockDim = dim3(64);
+    if (!b->persistent) ++i;
     if (i == 0) {
         p.func = const_cast<void *>(reset_kernel());
         p.gridDim = dim3((b->n_counters + 255) / 256);
         p.blockDim = dim3(256);
         args[0] = &b->counters.d;
         args[1] = &b->n_counters;
-    } else if (i <= n_groups(b)) {
-        const int g = i - 1;
+    } else if (i <= (int)b->launched.size()) {
+        const int g = b->launched[i - 1];
         const bool store = g < 3 * b->levels_cap;
         const int f = g % 3;
         b->group_index[g] = g;
@@ -224,7 +229,7 @@ static hipError_t build_graph(tgp_batch b) {
 static hipError_t update_graph(tgp_batch b) {
     void *args[8];
     hipError_t e = hipSuccess;
-    for (int i = 1; i < n_launches(b) && e == hipSuccess; ++i) {
+    for (int i = b->persistent ? 1 : 0; i < n_launches(b) && e == hipSuccess; ++i) {
         hipKernelNodeParams p = launch_params(b, i, args);
         e = hipGraphExecKernelNodeSetParams(b->exec, b->nodes[i], &p);
     }
@@ -346,6 +351,7 @@ tgp_status batch_step(tgp_batch b, int32_t n_jobs, const StepJob *jobs, int64_t 
         b->K = K;
         b->ext = ext;
         b->D = D;
+        b->grid_known = false;
         b->stale = true;
     }
     const bool persistent = ctx->batch_persistent != 0;
@@ -359,8 +365,15 @@ tgp_status batch_step(tgp_batch b, int32_t n_jobs, const StepJob *jobs, int64_t 
     if (max_levels > kMaxLevels) return fail(ctx, TGP_EINVAL, "more than %d cache-fill levels", kMaxLevels);
     if (max_levels > b->levels_cap) {
         b->levels_cap = std::min(kMaxLevels, std::max(max_levels, 2 * b->levels_cap));
+        b->used.clear();  // the groups are numbered anew
         b->stale = true;
     }
+    for (int store = 0; store < 2 && !b->grid_known; ++store) {
+        b->grid[0][store] = batch_grid(K, D, store != 0, ext ? kExt : kFlat);
+        b->grid[1][store] = batch_grid(kTableK, interp_max_stack(), store != 0, kWide);
+        b->grid[2][store] = batch_grid(kTableK, interp_max_stack(), store != 0, kRagged);
+    }
+    b->grid_known = true;
     // ---- launch shape: tiles per item from the whole batch's work
     int64_t total_tiles = 0;
     std::vector<int64_t> ntiles(n_jobs), tps(n_jobs);
@@ -534,7 +547,24 @@ tgp_status batch_step(tgp_batch b, int32_t n_jobs, const StepJob *jobs, int64_t 
     b->h_first.h[pi] = (uint32_t)item;
     if (item > 0xffffffffull) return fail(ctx, TGP_EINVAL, "batch has more than 2^32 work items");
     b->group_items.resize(G);
-    for (int g = 0; g < G; ++g) b->group_items[g] = b->h_groups.h[g].item_end - b->h_groups.h[g].item_begin;
+    // Launches for the groups that hold programs in this step or held some in an
+    // earlier one (a step whose groups all have launches replays the graph).  With
+    // one for every form and level, and a reset of counters that one wave per item
+    // does not use, a batch on lines took 92, 123 and 84 us where it takes 67, 100
+    // and 55 (12 small populations, 12 larger ones, one).
+    b->used.resize(G, 0);
+    bool grown = false;
+    for (int g = 0; g < G; ++g) {
+        b->group_items[g] = b->h_groups.h[g].item_end - b->h_groups.h[g].item_begin;
+        grown |= b->group_items[g] && !b->used[g];
+        b->used[g] |= b->group_items[g] > 0;
+    }
+    if (grown || b->stale) {
+        b->launched.clear();
+        for (int g = 0; g < G; ++g)
+            if (b->used[g]) b->launched.push_back(g);
+        b->stale = true;
+    }
     b->n_ind = n_ind;
     b->h_scalars.h[0] = n_jobs;
     b->h_scalars.h[1] = (int32_t)n_ind;
@@ -555,11 +585,6 @@ tgp_status batch_step(tgp_batch b, int32_t n_jobs, const StepJob *jobs, int64_t 
     if (e == hipSuccess) e = hipEventRecord(b->staged_ev, ctx->stream);
     if (e != hipSuccess) return fail(ctx, TGP_EHIP, "batch upload: %s", hipGetErrorString(e));
     b->staged = true;
-    for (int store = 0; store < 2; ++store) {
-        b->grid[0][store] = batch_grid(K, D, store != 0, ext ? kExt : kFlat);
-        b->grid[1][store] = batch_grid(kTableK, interp_max_stack(), store != 0, kWide);
-        b->grid[2][store] = batch_grid(kTableK, interp_max_stack(), store != 0, kRagged);
-    }
     const double t1 = now_ms();
     record(ctx, 2);
     if (b->use_graph) {
