@@ -1883,16 +1883,18 @@ struct UploadPart {
     size_t bytes;
     uint32_t rebase;
 };
+// The block has `spare` bytes behind the parts, from *base + off[n] on.
 static hipError_t upload_parts(tgp_ctx ctx, int n, const UploadPart *part, void **blob, char **base,
-                               size_t *off) {
+                               size_t *off, size_t spare = 0) {
     size_t total = 0;
     for (int i = 0; i < n; ++i) {
         off[i] = total;
         total += (part[i].bytes + 255) & ~(size_t)255;
     }
     total = std::max<size_t>(total, 256);
+    off[n] = total;
     void *stage = nullptr;
-    hipError_t e = ctx->pool.alloc(blob, total);
+    hipError_t e = ctx->pool.alloc(blob, total + spare);
     if (e == hipSuccess) e = ctx_pinned(ctx, total, &stage);
     if (e != hipSuccess) return e;
     for (int i = 0; i < n; ++i) {
@@ -1915,7 +1917,7 @@ static tgp_status plan_upload_fill(tgp_ctx ctx, Plan &P) {
     const UploadPart part[3] = {{P.code_host.data(), sizeof(uint2) * (size_t)P.root_code_at, 0},
                                 {P.fill_host.data(), sizeof(ProgDesc) * P.fill_host.size(), 0},
                                 {P.tab_host.data(), sizeof(ProgDesc) * P.tab_host.size(), 0}};
-    size_t off[3];
+    size_t off[4];
     char *b = nullptr;
     hipError_t e = upload_parts(ctx, 3, part, &P.blob, &b, off);
     if (e != hipSuccess) {
@@ -1938,9 +1940,10 @@ static tgp_status plan_upload_roots(tgp_ctx ctx, tgp_dag d, Plan &P) {
         {P.reduce_host.data(), sizeof(ProgDesc) * P.reduce_host.size(), at},
         {P.store_host.data(), sizeof(ProgDesc) * P.store_host.size(), at},
         {P.ind_rows_host.data(), sizeof(int32_t) * P.ind_rows_host.size(), 0}};
-    size_t off[4];
+    size_t off[5];
     char *b = nullptr;
-    hipError_t e = upload_parts(ctx, 4, part, &P.blob_roots, &b, off);
+    P.reserve_bytes = P.split && !d->other.blob ? flat_bytes_bound(*d, P.cases) : 0;
+    hipError_t e = upload_parts(ctx, 4, part, &P.blob_roots, &b, off, P.reserve_bytes);
     if (e != hipSuccess) {
         hipStreamSynchronize(ctx->stream);
         P.release(ctx->pool);
@@ -1950,22 +1953,16 @@ static tgp_status plan_upload_roots(tgp_ctx ctx, tgp_dag d, Plan &P) {
     P.reduce_dev = reinterpret_cast<ProgDesc *>(b + off[1]);
     P.store_dev = reinterpret_cast<ProgDesc *>(b + off[2]);
     P.ind_rows_dev = reinterpret_cast<int32_t *>(b + off[3]);
-    // Memory for tgp_fitness_noalloc alone (without it, it may refuse a call).
-    auto keep = [&](void **block, size_t bytes) {
-        if (!*block && ctx->pool.alloc(block, bytes) != hipSuccess) {
-            *block = nullptr;
-            (void)hipGetLastError();
-        }
-    };
-    if (P.split && !d->other.blob) {
-        P.reserve_bytes = flat_bytes_bound(*d, P.cases);
-        keep(&P.reserve, P.reserve_bytes);
-    }
+    // Memory for tgp_fitness_noalloc alone.
+    if (P.reserve_bytes) P.reserve = b + off[4];
     if (P.split) {
         const size_t rows = sizeof(float) * (size_t)P.n_slots * (size_t)P.cases, tables = P.planned_tables_bytes();
         const size_t sums = sizeof(float2) * (size_t)P.n_reduce * (size_t)((P.cases + kWideCols - 1) / kWideCols);
-        if (rows <= kNoAllocScratchBytes && sums + rows + tables + 512 > kNoAllocScratchBytes)
-            keep(&P.noalloc_tables, tables);
+        if (rows <= kNoAllocScratchBytes && sums + rows + tables + 512 > kNoAllocScratchBytes &&
+            ctx->pool.alloc(&P.noalloc_tables, tables) != hipSuccess) {  // (it may then refuse a call)
+            P.noalloc_tables = nullptr;
+            (void)hipGetLastError();
+        }
     }
     return TGP_OK;
 }
@@ -2096,7 +2093,7 @@ static tgp_status choose_plan(tgp_ctx ctx, tgp_dag d, tgp_domain dom, int32_t wa
     }
     if (plan_current(ctx, d->plan, dom->cases)) std::swap(d->plan, d->other);
     for (Plan *Q : {&d->plan, &d->other})
-        if (!plan_current(ctx, *Q, dom->cases)) {
+        if (!plan_current(ctx, *Q, dom->cases) && !Q->store_rows.empty()) {  // (not a new DAG's)
             if (Q->blob) HCHK(ctx, hipStreamSynchronize(ctx->stream));  // no queued kernel reads it any more
             Q->release(ctx->pool);
             *Q = Plan();
@@ -2131,10 +2128,7 @@ tgp_status build_plan(tgp_ctx ctx, tgp_dag d, tgp_domain dom, const std::functio
         return st;
     }
     const int D = ctx_stack_slots(ctx);
-    if (!split) {  // a flat plan of its own: the room kept for one is not needed
-        ctx->pool.release(d->other.reserve);
-        d->other.reserve = nullptr;
-    }
+    if (!split) d->other.reserve = nullptr;  // a flat plan with a block of its own
     const size_t budget = plan_budget(ctx, d);
     PlanJob w(d, cases, D, rows_in(budget, cases));
     w.budget = budget;

@@ -166,8 +166,8 @@ struct Plan {
     int64_t refused[2] = {0, 0};
     size_t budget = 0;                  // the cache budget that the plan was made for
     // Beside tables: what the flat plan is made from where nothing may be
-    // allocated (flat_in_reserve): the folded constants, and a pool block that
-    // then holds its programs and is its blob.
+    // allocated (flat_in_reserve): the folded constants, and the end of blob_roots,
+    // which then holds its programs (the two plans are given up together).
     std::vector<float> fold_val;
     void *reserve = nullptr;
     size_t reserve_bytes = 0;
@@ -235,7 +235,6 @@ struct Plan {
     void release(DevicePool &pool) {
         pool.release(blob);
         pool.release(blob_roots);
-        pool.release(reserve);
         pool.release(noalloc_tables);
         blob = blob_roots = reserve = noalloc_tables = nullptr;
         put = false;
