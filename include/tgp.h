@@ -438,8 +438,10 @@ tgp_status tgp_autotune(tgp_ctx ctx, int32_t n_jobs, const tgp_job *jobs, const 
  * (device, tuning) and stays free for its owner to use. */
 typedef struct tgp_server_s *tgp_server;
 
-/* cache_budget_bytes: device memory reserved for resident subtree results (0:
- * a quarter of the device's memory); max_active: requests evaluated at once
+/* cache_budget_bytes: device memory reserved for resident subtree results and
+ * for the tables of the requests being evaluated (0: a quarter of the device's
+ * memory; a subtree that varies along a part of the axes only is in a table,
+ * which is not kept after the request); max_active: requests evaluated at once
  * (0: 16).  Blocks while the cache memory is allocated. */
 tgp_status tgp_server_create(tgp_ctx ctx, size_t cache_budget_bytes, int32_t max_active, tgp_server *out);
 /* Waits for the admitted requests to finish; requests not admitted yet end

@@ -2017,7 +2017,8 @@ int ctx_stack_slots(tgp_ctx ctx) { return ctx->stack_lds ? interp_lds_stack() : 
 // chosen two cases per lane, the LDS stack, "no caching" (a negative access
 // cost), unfolded constants and the image operators keep flat programs.
 static int32_t wanted_split(tgp_ctx ctx, tgp_dag d, tgp_domain dom) {
-    if (ctx->stack_lds || ctx->force_K == 2 || ctx->cache_access_cost < 0 || !ctx->fold || d->image_ops) return 0;
+    if (ctx->stack_lds || ctx->force_K == 2 || ctx->cache_access_cost < 0 || !ctx->fold) return 0;
+    if (d->image_ops || d->no_tables) return 0;
     return dom->split;
 }
 

@@ -253,6 +253,7 @@ struct tgp_dag_s : DagArrays {  // host copies
     DagDevice dev;
     bool image_ops = false;          // a bitwise operator or warp occurs
     std::vector<uint8_t> precached;  // nodes whose values are resident (empty: none)
+    bool no_tables = false;          // plans are flat on every domain
     // The plan in use.  other: the flat plan where that one has tables, or the
     // one with tables where it is flat; both are for one number of cases and
     // one set of the context's settings, and either stays as it is (a captured

@@ -100,6 +100,7 @@ struct Req {
     Plan plan;                         // host programs, cache slots mapped to arena rows
     std::vector<CacheEntry *> entry;   // per slot
     std::vector<uint8_t> writes;       // per slot: filled by this request
+    CacheEntry *tables = nullptr;      // the plan's tables, filled by the first slab's step
     int64_t dag_nodes = 0;
     int64_t slab = 0;
     int32_t n_slabs = 0, next_slab = 0, tps = 1;
@@ -108,7 +109,6 @@ struct Req {
     uint2 *code_dev = nullptr;
     int32_t *rows_dev = nullptr;
     double *acc = nullptr, *out_dev = nullptr;
-    float *tables = nullptr;  // table programs: filled by the first slab's step
     // outcome
     int status = TGP_EBUSY;
     bool finished = false;
@@ -188,12 +188,23 @@ void end_request_locked(tgp_server s, Req &r, int st, const std::string &msg) {
     r.plan = Plan();
     r.entry.clear();
     r.writes.clear();
+    r.tables = nullptr;
     s->cv_done.notify_all();
 }
 
 void end_request(tgp_server s, Req &r, int st, const std::string &msg) {
     std::lock_guard<std::mutex> lk(s->m);
     end_request_locked(s, r, st, msg);
+}
+
+// Gives back what r holds in the arena (called with the lock held); written:
+// its rows are complete.
+void unpin_locked(tgp_server s, Req &r, bool written) {
+    for (size_t q = 0; q < r.entry.size(); ++q)
+        if (r.entry[q]) s->cache->unpin(r.entry[q], written && r.writes[q]);
+    if (r.tables) s->cache->unpin(r.tables, false);
+    r.entry.clear();
+    r.tables = nullptr;
 }
 
 // ------------------------------------------------------------ preparation
@@ -228,54 +239,57 @@ void prepare(tgp_server s, tgp_ctx pc, const ReqP &rp) {
         k.dom = dk;
         return k;
     };
-    // Resident subtrees (pinned while this request may read them).
-    std::vector<CacheEntry *> hit(U, nullptr);
-    {
-        std::lock_guard<std::mutex> lk(s->m);
-        for (int64_t n = 0; n < U; ++n)
-            if (kArity[d->op[n] & 0xff] > 0) hit[n] = s->cache->find(key_of(n));
-    }
-    d->precached.assign(U, 0);
-    for (int64_t n = 0; n < U; ++n) d->precached[n] = hit[n] != nullptr;
-    auto unpin_hits = [&]() {
-        std::lock_guard<std::mutex> lk(s->m);
-        for (CacheEntry *e : hit)
-            if (e) s->cache->unpin(e, false);
-    };
-    st = build_plan(pc, d, r.dom);
-    if (st != TGP_OK) {
-        unpin_hits();
-        end_request(s, r, st, std::string("plan: ") + tgp_last_error(pc));
-        return;
-    }
-    const Plan &P = d->plan;
-    const int32_t n_slots = P.n_slots;
-    r.entry.assign(n_slots, nullptr);
-    r.writes.assign(n_slots, 0);
-    std::vector<uint8_t> read(U, 0);
-    for (int32_t q = 0; q < n_slots; ++q)
-        if (P.slot_pre[q]) {
-            read[P.slot_node[q]] = 1;
-            r.entry[q] = hit[P.slot_node[q]];
-        } else {
-            r.writes[q] = 1;
-        }
-    {
-        std::lock_guard<std::mutex> lk(s->m);
-        for (int64_t n = 0; n < U; ++n)
-            if (hit[n] && !read[n]) s->cache->unpin(hit[n], false);
-    }
-    r.prep_ms = s->now() - r.t_prep;
-    // Admission: a free slot, and arena rows for every subtree cached anew.
     const uint64_t len = (uint64_t)((r.dom->cases + kUnitFloats - 1) / kUnitFloats);
-    {
+    // Plans the request and waits for its place.  Returns whether it was
+    // admitted; if not, it has ended, or *flat asks for another try without
+    // tables: they lie in the arena in one piece, for which the rows that the
+    // request reads there may leave no room.
+    auto admit = [&](bool *flat) {
+        // Resident subtrees (pinned while this request may read them).
+        std::vector<CacheEntry *> hit(U, nullptr);
+        {
+            std::lock_guard<std::mutex> lk(s->m);
+            for (int64_t n = 0; n < U; ++n)
+                if (kArity[d->op[n] & 0xff] > 0) hit[n] = s->cache->find(key_of(n));
+        }
+        d->precached.assign(U, 0);
+        for (int64_t n = 0; n < U; ++n) d->precached[n] = hit[n] != nullptr;
+        d->no_tables = *flat;
+        st = build_plan(pc, d, r.dom);
+        if (st != TGP_OK) {
+            std::lock_guard<std::mutex> lk(s->m);
+            for (CacheEntry *e : hit)
+                if (e) s->cache->unpin(e, false);
+            end_request_locked(s, r, st, std::string("plan: ") + tgp_last_error(pc));
+            return false;
+        }
+        const Plan &P = d->plan;
+        const int32_t n_slots = P.n_slots;
+        r.entry.assign(n_slots, nullptr);
+        r.writes.assign(n_slots, 0);
+        std::vector<uint8_t> read(U, 0);
+        for (int32_t q = 0; q < n_slots; ++q)
+            if (P.slot_pre[q]) {
+                read[P.slot_node[q]] = 1;
+                r.entry[q] = hit[P.slot_node[q]];
+            } else {
+                r.writes[q] = 1;
+            }
+        {
+            std::lock_guard<std::mutex> lk(s->m);
+            for (int64_t n = 0; n < U; ++n)
+                if (hit[n] && !read[n]) s->cache->unpin(hit[n], false);
+        }
+        r.prep_ms = s->now() - r.t_prep;
+        // Admission: a free slot, and arena rows for every subtree cached anew
+        // and the tables.
+        const size_t tab = P.tables_bytes(*r.dom);
         std::unique_lock<std::mutex> lk(s->m);
         for (;;) {
             if (s->stop) {
-                for (int32_t q = 0; q < n_slots; ++q)
-                    if (r.entry[q]) s->cache->unpin(r.entry[q], false);
+                unpin_locked(s, r, false);
                 end_request_locked(s, r, TGP_EBUSY, "server shut down before admission");
-                return;
+                return false;
             }
             if (s->n_admitted < s->max_active) {
                 bool ok = true;
@@ -285,6 +299,10 @@ void prepare(tgp_server s, tgp_ctx pc, const ReqP &rp) {
                     r.entry[q] = s->cache->create(&k, len, r.run);
                     ok = r.entry[q] != nullptr;
                 }
+                if (ok && tab) {
+                    r.tables = s->cache->create(nullptr, (tab + kUnitFloats * 4 - 1) / (kUnitFloats * 4), r.run);
+                    ok = r.tables != nullptr;
+                }
                 if (ok) break;
                 for (int32_t q = 0; q < n_slots; ++q)
                     if (r.writes[q] && r.entry[q]) {
@@ -292,15 +310,18 @@ void prepare(tgp_server s, tgp_ctx pc, const ReqP &rp) {
                         r.entry[q] = nullptr;
                     }
                 if (s->n_admitted == 0) {
-                    // nothing else holds the arena: this request can never fit
-                    for (int32_t q = 0; q < n_slots; ++q)
-                        if (r.entry[q]) s->cache->unpin(r.entry[q], false);
+                    // nothing else holds the arena: this plan can never fit
+                    unpin_locked(s, r, false);
+                    if (tab) {
+                        *flat = true;
+                        return false;
+                    }
                     char msg[160];
                     snprintf(msg, sizeof msg, "cached subtrees need %llu bytes, the cache holds %llu",
                              (unsigned long long)(len * kUnitFloats * 4 * (uint64_t)n_slots),
                              (unsigned long long)s->arena_bytes);
                     end_request_locked(s, r, TGP_ENOMEM, msg);
-                    return;
+                    return false;
                 }
             }
             s->cv_done.wait(lk);
@@ -312,7 +333,11 @@ void prepare(tgp_server s, tgp_ctx pc, const ReqP &rp) {
         s->stats.cache_new += r.fresh;
         s->stats.bytes_peak =
             std::max<int64_t>(s->stats.bytes_peak, (int64_t)(s->cache->used_units() * kUnitFloats * 4));
-    }
+        return true;
+    };
+    bool flat = false;
+    if (!admit(&flat) && (!flat || !admit(&flat))) return;
+    const Plan &P = d->plan;
     // Programs with slots mapped to arena rows (in arena units).
     r.plan = P;
     // (the tables' programs, first in the code, name table entries instead)
@@ -379,8 +404,6 @@ void release_exec(tgp_server s, Req &r) {
     p.release(r.rows_dev);
     p.release(r.acc);
     p.release(r.out_dev);
-    p.release(r.tables);
-    r.tables = nullptr;
     r.code_dev = nullptr;
     r.rows_dev = nullptr;
     r.acc = r.out_dev = nullptr;
@@ -410,8 +433,7 @@ void retire(tgp_server s, Req &r, hipError_t e) {
     }
     release_exec(s, r);
     std::lock_guard<std::mutex> lk(s->m);
-    for (size_t q = 0; q < r.entry.size(); ++q)
-        if (r.entry[q]) s->cache->unpin(r.entry[q], st == TGP_OK && r.writes[q]);
+    unpin_locked(s, r, st == TGP_OK);
     s->n_admitted -= 1;
     end_request_locked(s, r, st, msg);
 }
@@ -443,8 +465,6 @@ void exec_loop(tgp_server s) {
             hipError_t e = pool_upload(s, &r->code_dev, r->plan.code_host);
             if (e == hipSuccess) e = pool_upload(s, &r->rows_dev, r->plan.ind_rows_host);
             if (e == hipSuccess) e = s->exec->pool.alloc((void **)&r->out_dev, sizeof(double) * r->n_ind);
-            const size_t tab = r->plan.tables_bytes(*r->dom);
-            if (e == hipSuccess && tab) e = s->exec->pool.alloc((void **)&r->tables, tab);
             if (e == hipSuccess && r->n_slabs > 1)
                 e = s->exec->pool.alloc((void **)&r->acc, sizeof(double) * r->n_ind);
             if (e != hipSuccess) {
@@ -485,7 +505,7 @@ void exec_loop(tgp_server s) {
                 j.tiles_per_item = r->tps;
                 j.code_dev = r->code_dev;
                 j.rows_dev = r->rows_dev;
-                j.tables = r->tables;
+                j.tables = r->tables ? s->arena + r->tables->off * kUnitFloats : nullptr;
                 j.fill_tables = k == 0;
                 jobs.push_back(j);
                 f.items.push_back({r, k == r->n_slabs - 1});
@@ -604,7 +624,7 @@ tgp_status tgp_server_create(tgp_ctx ctx, size_t cache_budget_bytes, int32_t max
         c->tile_cap = ctx->tile_cap;
         c->batch_persistent = ctx->batch_persistent;
     }
-    // A request may plan new cache rows for at most half the arena, so that
+    // A request may plan new cache rows and tables for at most half the arena, so that
     // it can be admitted beside the resident rows it reads (pinned while it
     // runs) even when the arena is fragmented; beyond that its plan
     // recomputes subtrees instead of caching them.
