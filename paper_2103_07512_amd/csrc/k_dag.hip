@@ -727,6 +727,12 @@ __global__ __launch_bounds__(256) void k_publish(const BuildStatus *st, const in
 // a small part of the build.
 constexpr size_t kPublishBytes = 8 << 20;
 
+// A DAG's block is allocated for as many nodes as tokens.  Of this size and four
+// times what the nodes need, it is worth a copy (where the block is published,
+// with a wait: 15 us, as long as a twentieth of a build that could save less).
+constexpr size_t kShrinkBytes = 4 << 20;
+static size_t pool_bytes(size_t bytes) { return (size_t)1 << DevicePool::class_of(bytes); }
+
 static inline dim3 grid_for(int64_t n, int b = 256) { return dim3((unsigned)((n + b - 1) / b)); }
 
 // A quarter of one block's words for each thread, on at most 256 blocks.
@@ -761,7 +767,7 @@ DagBuildResult build_dag_device(tgp_ctx ctx, const tgp_token *tok_dev, const int
     const bool commute = ctx->commute != 0, rewrite = ctx->rewrite != 0;
     const uint2 *tok = reinterpret_cast<const uint2 *>(tok_dev);
     // scratch, in one block: see the offsets below
-    char *scratch = nullptr;
+    char *scratch = nullptr, *old = nullptr;
     BuildStatus *st = nullptr, *hs = nullptr;
     int32_t *kid, *height, *stk, *root_tok, *list, *canon, *pos, *table, *sums, *blob, *cnt = nullptr;
     int4 *info;
@@ -916,15 +922,27 @@ DagBuildResult build_dag_device(tgp_ctx ctx, const tgp_token *tok_dev, const int
         DCHK(hipGetLastError());
         DCHK(hipStreamSynchronize(s));
         res.U = static_cast<BuildStatus *>(stage)->nodes;
+        const size_t bytes = DagDevice::blob_bytes(res.U, R);
+        // The block goes with the DAG for its life: one of its nodes' size takes
+        // its place where that saves much.
+        const size_t held = pool_bytes(kBlobHead + DagDevice::blob_bytes(T, R));
+        char *fit = nullptr;
+        if (held >= kShrinkBytes && held >= 4 * pool_bytes(bytes)) {
+            DCHK(pool.alloc((void **)&fit, bytes));
+            old = dev->block;
+            dev->block = fit;
+            DCHK(hipMemcpyAsync(fit, blob, bytes, hipMemcpyDeviceToDevice, s));
+        }
         if (publish) {
             *host = reinterpret_cast<const int32_t *>(static_cast<char *>(stage) + kBlobHead);
+            if (fit) DCHK(hipStreamSynchronize(s));
         } else {
-            const size_t bytes = DagDevice::blob_bytes(res.U, R);
             DCHK(ctx_pinned(ctx, bytes, &stage));
             DCHK(hipMemcpyAsync(stage, blob, bytes, hipMemcpyDeviceToHost, s));
             DCHK(hipStreamSynchronize(s));
             *host = static_cast<const int32_t *>(stage);
         }
+        if (fit) blob = reinterpret_cast<int32_t *>(fit);
     } else {
         res.U = hs->nodes;
         res.tree_internal = T - hs->cnt[0];
@@ -946,6 +964,7 @@ done:
     pool.release(st);
     pool.release(scratch);
     pool.release(cnt);
+    pool.release(old);
     return res;
 }
 
