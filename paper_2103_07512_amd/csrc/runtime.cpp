@@ -32,6 +32,7 @@
 #include <memory>
 #include <mutex>
 #include <string>
+#include <system_error>
 #include <thread>
 #include <unordered_map>
 #include <vector>
@@ -535,12 +536,19 @@ HostTeam::~HostTeam() {
     for (auto &t : workers_) t.join();
 }
 
-void HostTeam::run(int T, const std::function<void(int)> &fn) {
+int HostTeam::grow(int T) {
     T = std::min(T, kMaxWorkers + 1);
-    while ((int)workers_.size() < T - 1) {
-        const int id = (int)workers_.size() + 1;
-        workers_.emplace_back(&HostTeam::work, this, id, round_.load());
+    try {
+        while ((int)workers_.size() < T - 1) {
+            const int id = (int)workers_.size() + 1;
+            workers_.emplace_back(&HostTeam::work, this, id, round_.load());
+        }
+    } catch (const std::system_error &) {  // no more threads to be had
     }
+    return std::min(T, (int)workers_.size() + 1);
+}
+
+void HostTeam::run(int T, const std::function<void(int)> &fn) {
     {
         std::lock_guard<std::mutex> lk(m_);
         fn_ = &fn;
@@ -601,8 +609,11 @@ unsigned usable_cpus() {
     return n;
 }
 
-// Runs fn(t) for t = 0 .. T-1 on the team's threads, or (without a team) on
-// threads of its own; the caller's thread is t = 0.
+// T, or how many threads the team can run when that is fewer.
+int team_size(HostTeam *team, int T) { return team && T > 1 ? team->grow(T) : T; }
+
+// Runs fn(t) for t = 0 .. T-1 (T from team_size) on the team's threads, or
+// (without a team) on threads of its own; the caller's thread is t = 0.
 template <class F>
 void run_threads(HostTeam *team, int T, F &&fn) {
     if (T <= 1) {
@@ -1364,7 +1375,8 @@ void emit_all(Planner &pl, const std::vector<int32_t> &nodes, std::vector<uint2>
     out.assign(n, Emitted{0, 0, 0, 0.0, false, false});
     // (a thread for every 128 programs; threads of its own only for 512)
     const int per = pl.team ? 128 : 512;
-    const int T = std::max(1, std::min({(int)(n / per) * (pl.team ? 1 : threads), threads, (int)usable_cpus()}));
+    const int T = team_size(
+        pl.team, std::max(1, std::min({(int)(n / per) * (pl.team ? 1 : threads), threads, (int)usable_cpus()})));
     if (T == 1) {
         for (size_t i = 0; i < n; ++i) {
             Emitted &m = out[i];
@@ -1478,7 +1490,8 @@ static void plan_prepare(PlanJob &w, bool fold, int threads = 1) {
     };
     const int32_t *kid = d->kid.data();
     const int32_t *height = d->height.data();
-    const int T = (int)std::min<unsigned>((unsigned)std::max(threads, 1), usable_cpus());
+    int T = (int)std::min<unsigned>((unsigned)std::max(threads, 1), usable_cpus());
+    if (U >= kParallelDecideNodes) T = team_size(w.pl.team, T);
     if (U >= kParallelDecideNodes && T > 1) {
         // level by level on T threads; the height order is kept for the
         // parallel decisions
@@ -1671,7 +1684,8 @@ static tgp_status plan_decide_emit_fill(PlanJob &w, int D, bool reorder, double 
     pl.reorder = reorder;
     pl.access_cost = access_cost;
     const unsigned hw = usable_cpus();
-    const int dt = (int)std::min<unsigned>((unsigned)std::max(emit_threads, 1), hw);
+    int dt = (int)std::min<unsigned>((unsigned)std::max(emit_threads, 1), hw);
+    if (U >= kParallelDecideNodes) dt = team_size(pl.team, dt);
     auto decide = [&]() {
         return U >= kParallelDecideNodes && dt > 1 ? pl.decide_parallel(w.rootrefs, w.err, dt)
                                                    : pl.decide(w.rootrefs, w.err);
@@ -2269,7 +2283,7 @@ tgp_status build_plans(tgp_ctx ctx, int32_t n, const tgp_dag *dags, const tgp_do
         return a->d->stats.dag_nodes > b->d->stats.dag_nodes;
     });
     const unsigned hw = usable_cpus();
-    const int T = (int)std::min<size_t>(std::min<unsigned>(16, hw), jobs.size());
+    const int T = team_size(&ctx->team, (int)std::min<size_t>(std::min<unsigned>(16, hw), jobs.size()));
     auto parallel = [&](auto &&fn) {
         std::atomic<size_t> next{0};
         auto run = [&]() {

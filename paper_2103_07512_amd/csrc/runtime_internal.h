@@ -32,8 +32,11 @@ struct DevBuf {
 class HostTeam {
 public:
     ~HostTeam();
+    // Makes the threads for rounds of T; returns how many a round can have (fewer
+    // when the process gets no more threads).
+    int grow(int T);
     // Runs fn(t) for t = 0 .. T-1, t = 0 on the calling thread, and returns
-    // when all have returned.
+    // when all have returned.  T is at most what grow returned.
     void run(int T, const std::function<void(int)> &fn);
 
 private:

@@ -152,6 +152,20 @@ int main() {
         use(&c, d, domain(&c, {512, 1024}));
         CHECK(d.plan.split == 1 && d.other.cases < 0, "plans of another size kept\n");
     }
+    {   // a column table of 8191 entries of 512 KiB is within the offsets, one of 8192 is not
+        const tgp_domain_s b = domain(&c, {8, 131072});
+        for (int n : {8191, 8192}) {
+            tgp_dag_s d;
+            column_trees(d, &c, n);
+            for (int i = 0; i < 2; ++i) {
+                use(&c, d, domain(&c, {1024, 1024}));
+                CHECK(d.plan.split == 1, "%d entries of 4 KiB: no tables\n", n);
+                use(&c, d, b);
+                CHECK((d.plan.split == 1) == (n == 8191), "%d entries of 512 KiB: split %d\n", n, d.plan.split);
+            }
+        }
+        g_planned = 0;
+    }
     {   // the order does not matter: refused where they do not fit, planned where they do
         tgp_dag_s d;
         column_trees(d, &c, 18000);
