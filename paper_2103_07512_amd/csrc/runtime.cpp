@@ -191,6 +191,7 @@ void tgp_ctx_destroy(tgp_ctx ctx) {
     tgp_batch_destroy(ctx->batch);
     hipFree(ctx->partial.p);
     hipFree(ctx->cache.p);
+    hipFree(ctx->tables.p);
     hipFree(ctx->fit_out.p);
     ctx->pool.drain();
     if (ctx->pin) hipHostFree(ctx->pin);
@@ -2464,15 +2465,11 @@ static tgp_status run_fill(tgp_ctx ctx, tgp_dag d, tgp_domain dom, int K, float 
     if (P.n_slots) HCHK(ctx, ensure(ctx->cache, bytes));
     // Like the cache rows, the tables hold one evaluation's values at a time.
     // (tgp_fitness_noalloc has tables of its own: a captured call may be
-    // replayed beside this one on another stream.)
-    const size_t tab = P.tables_bytes(*dom);
-    if (tab > ctx->tables.cap) {
-        if (ctx->tables.p) HCHK(ctx, hipStreamSynchronize(ctx->stream));
-        ctx->pool.release(ctx->tables.p);
-        ctx->tables = DevBuf{};
-        HCHK(ctx, ctx->pool.alloc(&ctx->tables.p, tab));
-        ctx->tables.cap = tab;
-    }
+    // replayed beside this one on another stream.)  Their size differs from one
+    // generation to the next: they grow to powers of two.
+    size_t tab = 256;
+    while (tab < P.tables_bytes(*dom)) tab <<= 1;
+    if (P.split) HCHK(ctx, ensure(ctx->tables, tab));
     float *cache = P.n_slots ? (float *)ctx->cache.p : nullptr;
     *cache_out = cache;
     return fill_into(ctx, d, dom, K, cache, (float *)ctx->tables.p);

@@ -96,7 +96,7 @@ struct tgp_ctx_s {
     double cache_access_cost = 20.0;     // < 0: no benefit-driven caching
     DevBuf partial, cache;
     DevBuf fit_out;  // device copy of fitness values bound for host memory
-    DevBuf tables;   // tables of one evaluation, filled by it (a pool block)
+    DevBuf tables;   // tables of one evaluation, filled by it
     DevicePool pool;             // DAG, plan and population blocks
     void *pin = nullptr;         // pinned staging for uploads and readbacks
     size_t pin_cap = 0;
