@@ -727,9 +727,9 @@ __global__ __launch_bounds__(256) void k_publish(const BuildStatus *st, const in
 // a small part of the build.
 constexpr size_t kPublishBytes = 8 << 20;
 
-// A DAG's block is allocated for as many nodes as tokens.  Of this size and four
-// times what the nodes need, it is worth a copy (where the block is published,
-// with a wait: 15 us, as long as a twentieth of a build that could save less).
+// A DAG's block is allocated for as many nodes as tokens.  One of this size and
+// four times what the nodes need is worth a copy, which costs a published block
+// (and a build of 250 us or more) a wait of 15 us.
 constexpr size_t kShrinkBytes = 4 << 20;
 static size_t pool_bytes(size_t bytes) { return (size_t)1 << DevicePool::class_of(bytes); }
 

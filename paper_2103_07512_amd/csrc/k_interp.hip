@@ -354,11 +354,11 @@ __device__ __forceinline__ void run_item(const Job &a, const uint2 *code, int32_
 // kernels hold more descriptor state and spill a few values at seven; at six
 // they spill none, one wave per item, but a serving mix took 3.20 ms against
 // 3.09, and a batch of twelve 10.9 against 11.0.
-template <int MODE, int FORM>
+template <int MODE>
 constexpr int min_waves() { return MODE == MODE_REDUCE ? 7 : 6; }
 
 template <int K, int D, int MODE, int FORM>
-__global__ __launch_bounds__(64, (min_waves<MODE, FORM>())) void k_interp(const InterpArgs a) {
+__global__ __launch_bounds__(64, min_waves<MODE>()) void k_interp(const InterpArgs a) {
     const uint32_t item = blockIdx.x;
     const uint32_t p = item / (uint32_t)a.job.n_stripes;
     const uint32_t stripe = item - p * (uint32_t)a.job.n_stripes;
@@ -375,7 +375,7 @@ typedef const __attribute__((address_space(4))) JobDesc CJobDesc;
 // then those of the column table's, each over its own flat job, read in place
 // from the kernel's arguments.
 template <int K>
-__global__ __launch_bounds__(64, (min_waves<MODE_STORE, kFlat>())) void k_tables(const TableArgs a) {
+__global__ __launch_bounds__(64, min_waves<MODE_STORE>()) void k_tables(const TableArgs a) {
     const uint32_t items0 = (uint32_t)a.n_progs[0] * (uint32_t)a.job[0].n_stripes;
     const uint32_t sel = blockIdx.x >= items0 ? 1u : 0u;
     const uint32_t item = blockIdx.x - (sel ? items0 : 0u);
@@ -428,7 +428,7 @@ __device__ __forceinline__ uint32_t find_pair(const uint32_t *__restrict__ item_
 }
 
 template <int K, int D, int MODE, int FORM>
-__global__ __launch_bounds__(64, (min_waves<MODE, FORM>())) void k_batch(const JobDesc *__restrict__ jobs,
+__global__ __launch_bounds__(64, min_waves<MODE>()) void k_batch(const JobDesc *__restrict__ jobs,
                                               const PairDesc *__restrict__ pairs,
                                               const uint32_t *__restrict__ item_first,
                                               const GroupDesc *__restrict__ groups, int32_t g,
@@ -461,7 +461,7 @@ __global__ __launch_bounds__(64, (min_waves<MODE, FORM>())) void k_batch(const J
 // Direct form: one wave per item (grid = the group's item count, or more);
 // the hardware dispatcher hands out the waves in item order.
 template <int K, int D, int MODE, int FORM>
-__global__ __launch_bounds__(64, (min_waves<MODE, FORM>())) void k_batch_direct(const JobDesc *__restrict__ jobs,
+__global__ __launch_bounds__(64, min_waves<MODE>()) void k_batch_direct(const JobDesc *__restrict__ jobs,
                                                      const PairDesc *__restrict__ pairs,
                                                      const uint32_t *__restrict__ item_first,
                                                      const GroupDesc *__restrict__ groups, int32_t g) {

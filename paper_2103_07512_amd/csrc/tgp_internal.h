@@ -268,8 +268,10 @@ struct FoldDesc {
 hipError_t launch_fold_level(const FoldDesc *jobs, const int2 *list, int32_t n, hipStream_t s);
 // The same for one DAG in one launch: n nodes, those of height h from first[h];
 // list, first and out (a value per list entry) may be in pinned host memory.
-// d.val is overwritten.  At most kFoldNodes (their operands and values fill the
-// 64 KB of LDS that need no attribute) and kFoldHeights.
+// d.val is overwritten.  At most kFoldNodes and kFoldHeights: 44 KB of LDS (3072
+// nodes would take more than the 64 KB that need no attribute).  It is the
+// faster way up to there: with 1293 folded subtrees 47 us, by height 74; with 58,
+// 22 and 50.
 constexpr int32_t kFoldNodes = 2048, kFoldHeights = 1024;
 hipError_t launch_fold_all(const FoldDesc &d, const int32_t *list, int32_t n, const int32_t *first, int32_t heights,
                            float *out, hipStream_t s);
