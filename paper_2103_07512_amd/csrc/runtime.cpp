@@ -134,6 +134,13 @@ constexpr size_t kNoAllocScratchBytes = size_t(64) << 20;
 // Smallest domain evaluated by table programs (a smaller one is a few waves
 // per program either way, and the tables cost a launch).
 constexpr int64_t kTableCases = 1024;
+// A DAG below so many nodes has few cached rows, if any, so its tables are a
+// launch more, which pays from so many node-evals on.  A planned call, flat and
+// with tables, us (alone; one of many): 4 nodes on 512^2 cases 19.5 and 21.2 (8.6
+// and 11.8), 34 nodes 20.6 and 22.5 (9.3 and 13.5), 79 nodes 24.0 and 24.7 (12.3
+// and 14.9); on 1024^2 34 nodes 30.6 and 31.1, 47 nodes 33.5 and 31.9, 79 nodes
+// 43.4 and 39.9; 118 nodes on 64^2 27.4 and 24.6 (15.9 and 15.7).
+constexpr int64_t kTableNodes = 100, kTableWork = int64_t(1) << 25;
 __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
 
 namespace {
@@ -2030,10 +2037,12 @@ int ctx_stack_slots(tgp_ctx ctx) { return ctx->stack_lds ? interp_lds_stack() : 
 
 // The split that d's programs get on dom under the context's settings: a
 // chosen two cases per lane, the LDS stack, "no caching" (a negative access
-// cost), unfolded constants and the image operators keep flat programs.
+// cost), unfolded constants, the image operators and very small work keep flat
+// programs.
 static int32_t wanted_split(tgp_ctx ctx, tgp_dag d, tgp_domain dom) {
     if (ctx->stack_lds || ctx->force_K == 2 || ctx->cache_access_cost < 0 || !ctx->fold) return 0;
     if (d->image_ops || d->no_tables) return 0;
+    if (d->stats.dag_nodes < kTableNodes && d->stats.dag_nodes * dom->cases <= kTableWork) return 0;
     return dom->split;
 }
 
