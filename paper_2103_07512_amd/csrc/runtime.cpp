@@ -2126,6 +2126,13 @@ static tgp_status choose_plan(tgp_ctx ctx, tgp_dag d, tgp_domain dom, int32_t wa
     return TGP_OK;
 }
 
+void forget_plans(tgp_ctx ctx, tgp_dag d) {
+    for (Plan *P : {&d->plan, &d->other}) {
+        P->release(ctx->pool);
+        *P = Plan();
+    }
+}
+
 // The cache budget of a plan made now: its neighbour's, so that a budget that was
 // set for the DAG's first plan holds for every shape of its size.
 static size_t plan_budget(tgp_ctx ctx, tgp_dag d) { return d->other.cases >= 0 ? d->other.budget : ctx->cache_budget; }

@@ -343,6 +343,8 @@ extern const double kOpCost[TGP_NUM_OPS];
 // that the caller can queue the cache fill while the host emits the rest.
 tgp_status build_plan(tgp_ctx ctx, tgp_dag d, tgp_domain dom,
                       const std::function<tgp_status()> &after_fill = nullptr);
+// Gives up d's plans (no queued kernel reads them).
+void forget_plans(tgp_ctx ctx, tgp_dag d);
 // Plans many DAGs at once (host threads, one device round trip for constant
 // folding); programs stay on the host.  A DAG listed more than once is
 // planned once, for its largest domain.

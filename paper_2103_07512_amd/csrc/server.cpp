@@ -241,20 +241,23 @@ void prepare(tgp_server s, tgp_ctx pc, const ReqP &rp) {
     };
     const uint64_t len = (uint64_t)((r.dom->cases + kUnitFloats - 1) / kUnitFloats);
     // Plans the request and waits for its place.  Returns whether it was
-    // admitted; if not, it has ended, or *flat asks for another try without
-    // tables: they lie in the arena in one piece, for which the rows that the
-    // request reads there may leave no room.
-    auto admit = [&](bool *flat) {
+    // admitted; if not, it has ended, or *again asks for another try: without
+    // tables, which lie in the arena in one piece, then without reading resident
+    // rows either, since the ones it reads stay where they are and may leave no
+    // room even for rows.
+    enum Way { kAll, kNoTables, kNoReads };
+    auto admit = [&](Way way, bool *again) {
         // Resident subtrees (pinned while this request may read them).
         std::vector<CacheEntry *> hit(U, nullptr);
         {
             std::lock_guard<std::mutex> lk(s->m);
             for (int64_t n = 0; n < U; ++n)
-                if (kArity[d->op[n] & 0xff] > 0) hit[n] = s->cache->find(key_of(n));
+                if (way != kNoReads && kArity[d->op[n] & 0xff] > 0) hit[n] = s->cache->find(key_of(n));
         }
         d->precached.assign(U, 0);
         for (int64_t n = 0; n < U; ++n) d->precached[n] = hit[n] != nullptr;
-        d->no_tables = *flat;
+        d->no_tables = way != kAll;
+        *again = false;
         st = build_plan(pc, d, r.dom);
         if (st != TGP_OK) {
             std::lock_guard<std::mutex> lk(s->m);
@@ -312,8 +315,8 @@ void prepare(tgp_server s, tgp_ctx pc, const ReqP &rp) {
                 if (s->n_admitted == 0) {
                     // nothing else holds the arena: this plan can never fit
                     unpin_locked(s, r, false);
-                    if (tab) {
-                        *flat = true;
+                    if (way != kNoReads) {
+                        *again = true;
                         return false;
                     }
                     char msg[160];
@@ -335,8 +338,14 @@ void prepare(tgp_server s, tgp_ctx pc, const ReqP &rp) {
             std::max<int64_t>(s->stats.bytes_peak, (int64_t)(s->cache->used_units() * kUnitFloats * 4));
         return true;
     };
-    bool flat = false;
-    if (!admit(&flat) && (!flat || !admit(&flat))) return;
+    bool again = false, admitted = false;
+    for (Way way : {kAll, kNoTables, kNoReads}) {
+        // (a flat plan that is there already was made for what was resident then)
+        if (way != kAll) forget_plans(pc, d);
+        admitted = admit(way, &again);
+        if (!again) break;
+    }
+    if (!admitted) return;
     const Plan &P = d->plan;
     // Programs with slots mapped to arena rows (in arena units).
     r.plan = P;

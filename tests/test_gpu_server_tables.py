@@ -94,3 +94,34 @@ def test_no_room_in_one_piece(env):
     assert info["cache_hits"] == 8
     assert srv.stats()["failed"] == 0
     srv.close()
+
+
+def test_no_room_between_the_rows_it_reads(env):
+    """Rows of one grid lie so that none of another fits between them; a request
+    that reads them and needs new ones is planned without the reads."""
+    tgp, ctx, torch = env
+    small, large = tgp.Domain(ctx, (32, 32)), tgp.Domain(ctx, (64, 64))   # rows of 4 and 16 KiB
+    ts, tl = (torch.zeros(1, d.cases, dtype=torch.float32, device="cuda:0") for d in (small, large))
+
+    def rows(ids, per=8):
+        """`per` trees each that share one costly subtree of both sides."""
+        return [f"add(pow(sin(exp(mult(x, y))), cos(add(x, {i}.5))), {0.125 * j + i:.3f})" for i in ids for j in range(per)]
+
+    srv = tgp.Server(ctx, cache_budget_bytes=23 * 4096)
+
+    def serve(run, ids, dom, t):
+        pop = pg.population_from_texts(rows(ids))
+        k = srv.submit(run, pop, dom, t, tgp.MSE)
+        np.testing.assert_allclose(srv.wait(k), _plain(env, pop, dom, t), rtol=1e-6)
+        return srv.ticket_info(k)
+    # four large rows with a small one before each: holes of 4 KiB once the small ones go
+    for i in range(4):
+        assert serve(1, [i], small, ts)["cache_new"] == 1
+        assert serve(0, [i], large, tl)["cache_new"] == 1
+    assert srv.stats()["entries"] == 8 and srv.stats()["evictions"] == 0
+    srv.end_run(1)
+    info = serve(0, [0, 1, 2, 3, 30, 31, 32, 33], large, tl)   # four rows to read, two or more new ones
+    print(info, srv.stats(), flush=True)
+    assert info["status"] == 0 and info["cache_hits"] == 0
+    assert srv.stats()["failed"] == 0
+    srv.close()
