@@ -1994,7 +1994,9 @@ static tgp_status plan_upload(tgp_ctx ctx, tgp_dag d, Plan &P) {
     return st == TGP_OK ? plan_upload_roots(ctx, d, P) : st;
 }
 
-// Some words passed as a kernel argument.
+// Some words passed as a kernel argument.  One workgroup and 3840 bytes a launch
+// (an argument block holds 4 KB), 2.5 us each: the programs of 176 trees, 1582
+// words of code, take six, in a first call that plans for 0.1 ms as well.
 struct PutWords {
     uint32_t w[960];
 };
